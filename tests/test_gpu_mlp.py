@@ -51,6 +51,20 @@ def test_train_step_matches_reference(gpu, batch):
     assert np.abs(p - p_ref)[sure].max() <= 1e-5
 
 
+@pytest.mark.parametrize("batch", [1, 15, 16, 17, 127, 128, 129, 159, 160, 161, 257])
+def test_gradients_at_tile_edges(gpu, batch):
+    """Rows around the 16-row workgroups of the row kernels and the 128-row tiles
+    and 32-row double steps of the gradient chains. Bound as above: a sum of
+    `batch` fp32 terms is off by at most batch * 2^-24 of its absolute sum."""
+    flat, X, T, M = problem(40 + batch, batch)
+    tr = eg.MlpTrainer(dev(flat, gpu), batch)
+    tr.step(dev(X, gpu), dev(T, gpu), dev(M, gpu), lr=1e-3)
+    f64 = flat.astype(np.float64)
+    g_ref = mlp.gradient(f64, X, T, M)
+    assert np.linalg.norm(tr.grads.cpu().numpy() - g_ref) <= 1e-4 * np.linalg.norm(g_ref)
+    assert abs(float(tr.loss.item()) - mlp.loss(f64, X, T, M)) <= 1e-5 * mlp.loss(f64, X, T, M)
+
+
 def test_training_is_deterministic_and_learns(gpu):
     flat, X, _, M = problem(3, 512)
     W = np.random.default_rng(4).normal(size=(16, 16)).astype(np.float32)
