@@ -94,9 +94,10 @@ __device__ __forceinline__ int64_t wave_max_i64(int64_t v) {
 }
 
 // Exclusive scan over a workgroup of NT threads (T = uint32_t or uint64_t).
-// `scratch` must hold NT/64 + 1 values of T in LDS. Returns this thread's
-// exclusive prefix; *total gets the sum. Contains __syncthreads(): every
-// thread of the workgroup must call it.
+// `scratch` must hold NT/64 values of T in LDS. Returns this thread's
+// exclusive prefix; *total gets the sum. Every thread adds up the wave totals
+// itself (uniform LDS reads). Contains __syncthreads(): every thread of the
+// workgroup must call it.
 template <int NT, typename T>
 __device__ __forceinline__ T block_exclusive_scan(T v, T *scratch, T *total) {
   constexpr int NW = NT / 64;
@@ -105,20 +106,16 @@ __device__ __forceinline__ T block_exclusive_scan(T v, T *scratch, T *total) {
   T inc = wave_inclusive_scan<T>(v);
   if (lane == 63) scratch[wave] = inc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    T run = 0;
-    for (int w = 0; w < NW; ++w) {
-      T t = scratch[w];
-      scratch[w] = run;
-      run += t;
-    }
-    scratch[NW] = run;
+  T before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const T t = scratch[w];
+    before += w < wave ? t : T(0);
+    all += t;
   }
+  *total = all;
   __syncthreads();
-  T r = scratch[wave] + inc - v;
-  *total = scratch[NW];
-  __syncthreads();
-  return r;
+  return before + inc - v;
 }
 
 // Sum of a u64 over a workgroup (result valid in thread 0). `scratch` holds NT/64 u64.

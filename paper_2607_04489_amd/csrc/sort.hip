@@ -5,13 +5,17 @@
 // of at most 8 bits, least significant digit first; the number of passes follows
 // the key's significant width (the fused key's width), not its type.
 //
-// One pass = a per-tile digit histogram (k_sort_hist), one device-wide exclusive
-// scan over the digit-major count table, and a scatter (k_sort_scatter). The
-// scatter ranks each tile's items stably: every wave walks its own contiguous
-// segment 64 items at a time, finds the lanes holding the same digit with one
-// ballot per digit bit, and keeps per-wave running digit counts in LDS; items are
-// then placed digit-major into an LDS copy of the tile and leave it in order, so
-// each digit's run of the tile goes out as one contiguous block.
+// One pass = a per-tile digit histogram (k_sort_hist), an exclusive scan over the
+// count table, and a scatter (k_sort_scatter). The scatter ranks each tile's items
+// stably: every wave walks its own contiguous segment 64 items at a time, finds
+// the lanes holding the same digit with one ballot per digit bit, and keeps
+// per-wave running digit counts in LDS; keys, then each value lane, are placed
+// digit-major into one LDS copy of the tile and leave it in order, so each
+// digit's run of the tile goes out as one contiguous block. Few tiles are scanned
+// by the scatter's workgroups themselves; an input that fits one workgroup's LDS
+// goes through all its passes there (k_sort_block).
+#include <type_traits>
+
 #include "common.hpp"
 #include "sort.hpp"
 
@@ -19,25 +23,35 @@ namespace eiger {
 
 namespace {
 
-constexpr int kSNT = 256;
+constexpr int kHNT = 256;  // histogram workgroup
+constexpr int kSNT = 512;  // scatter workgroup
 constexpr int kSWaves = kSNT / 64;
 constexpr int kSDigitBits = 8;
 constexpr int kSDigits = 1 << kSDigitBits;
-static_assert(kSDigits == kSNT, "one thread per digit in the per-tile digit scan");
+static_assert(kSDigits == kHNT && kSDigits <= kSNT, "one thread per digit");
 
-// Tiles of 8,192 items (4,096 for 8-byte keys): each digit's run of a tile
-// averages 32 items, so its writes cover whole 128-byte lines more often
-// (measured per 4-byte pass at 2^28 items: 2,048 items 3.8 ms, 4,096 2.7 ms,
-// 6,144 1.9 ms, 8,192 1.7 ms).
-template <typename K>
-constexpr int items_per_thread() {
-  return sizeof(K) == 8 ? 16 : 32;
+// Tiles. Large inputs: 10,240 items (6,144 of 8-byte keys): longer runs per digit
+// against registers (2^28 4-byte pairs, 32 bits, all passes: 12 items per thread
+// 5.14 ms, 16 4.89, 20 4.77, 24 6.27, where they spill; 2^27 8-byte pairs: 8 items
+// 4.63 ms, 10 3.77, 12 3.76, 16 4.00). Small inputs: 4,096 items, so that there are
+// workgroups for the chip.
+constexpr int kItemsSmall = 8;
+template <typename K, int NW>
+constexpr int items_large() {
+  return sizeof(K) == 8 ? 12 : (NW > 1 ? 16 : 20);
 }
-// Workgroups per CU of the grids; workgroups loop over the remaining tiles. The
-// histogram keeps one tile per workgroup; the scatter, whose workgroups hold
-// up to 70 KB of LDS, runs best with a few resident workgroups per CU.
+// Large tiles from this many of them on (two per CU).
+constexpr uint64_t kLargeTiles = 512;
+template <typename K, int NW>
+bool use_large(uint64_t n) {
+  return n >= kLargeTiles * kSNT * items_large<K, NW>();
+}
+// Up to this many tiles the scatter's workgroups sum the count table's columns
+// themselves instead of three scan launches.
+constexpr uint64_t kSelfScanTiles = 256;
+// Workgroups per CU of the histogram's grid; they loop over the remaining tiles.
 constexpr uint64_t kHistPerCu = 64;
-constexpr uint64_t kScatPerCu = 8;
+constexpr uint32_t kXcds = 8;
 
 // Digit of a plain sort: bits [shift, shift + width) of the key.
 template <typename K>
@@ -52,8 +66,9 @@ struct KeyDigit {
 // (hash partitioning).
 template <typename K>
 struct PartDigit {
-  static constexpr bool kStore = true;  // a hash per item: kept in LDS for the write-out
-  int top;                              // 64 - partition bits
+  // 8-byte keys: a 64-bit hash per item is kept (its digit, in LDS) for the write-out
+  static constexpr bool kStore = sizeof(K) == 8;
+  int top;  // 64 - partition bits
   int shift;
   uint32_t mask;
   __device__ __forceinline__ uint32_t operator()(K k) const {
@@ -65,12 +80,14 @@ struct PartDigit {
 // per tile was limited by how fast workgroups are dispatched, not by memory.
 // kVec (16-byte aligned keys): each thread reads 16 bytes of consecutive keys
 // per load (counting does not depend on which thread holds which key).
-template <typename K, int kItems, typename D, bool kVec>
-__global__ void __launch_bounds__(kSNT) k_sort_hist(const K *__restrict__ keys, uint64_t n, D dig, uint32_t ntiles,
+// Counts go out digit-major (cnt[digit * ntiles + tile], for the scan) or, for the
+// self-scanning scatter (kTileMajor), as cnt[tile * 256 + digit].
+template <typename K, int T, typename D, bool kVec, bool kTileMajor>
+__global__ void __launch_bounds__(kHNT) k_sort_hist(const K *__restrict__ keys, uint64_t n, D dig, uint32_t ntiles,
                                                     uint32_t *__restrict__ cnt) {
-  constexpr int T = kSNT * kItems;
   constexpr int V = 16 / static_cast<int>(sizeof(K));  // keys per 16-byte load
-  constexpr int NV = T / V;                            // 16-byte loads per tile (T is a multiple of 256)
+  constexpr int NV = T / V;                            // 16-byte loads per tile
+  static_assert(NV % kHNT == 0, "whole loads");
   __shared__ uint32_t h[kSDigits];
   for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     h[threadIdx.x] = 0;
@@ -78,10 +95,8 @@ __global__ void __launch_bounds__(kSNT) k_sort_hist(const K *__restrict__ keys, 
     const uint64_t base = static_cast<uint64_t>(tile) * T;
     if constexpr (kVec) {
 #pragma unroll
-      for (int j = 0; j < (NV + kSNT - 1) / kSNT; ++j) {
-        const int q = j * kSNT + static_cast<int>(threadIdx.x);
-        if (q >= NV) break;
-        const uint64_t i = base + static_cast<uint64_t>(q) * V;
+      for (int j = 0; j < NV / kHNT; ++j) {
+        const uint64_t i = base + static_cast<uint64_t>(j * kHNT + static_cast<int>(threadIdx.x)) * V;
         if (i + V <= n) {
           K v[V];
           *reinterpret_cast<uint4 *>(v) = *reinterpret_cast<const uint4 *>(keys + i);
@@ -94,14 +109,17 @@ __global__ void __launch_bounds__(kSNT) k_sort_hist(const K *__restrict__ keys, 
         }
       }
     } else {
-#pragma unroll
-      for (int j = 0; j < kItems; ++j) {
-        const uint64_t i = base + static_cast<uint64_t>(j) * kSNT + threadIdx.x;
+#pragma unroll 16
+      for (int j = 0; j < T / kHNT; ++j) {
+        const uint64_t i = base + static_cast<uint64_t>(j) * kHNT + threadIdx.x;
         if (i < n) atomicAdd(&h[dig(keys[i])], 1u);
       }
     }
     __syncthreads();
-    if (threadIdx.x <= dig.mask) cnt[static_cast<uint64_t>(threadIdx.x) * ntiles + tile] = h[threadIdx.x];
+    if constexpr (kTileMajor)
+      cnt[static_cast<uint64_t>(tile) * kSDigits + threadIdx.x] = h[threadIdx.x];
+    else if (threadIdx.x <= dig.mask)
+      cnt[static_cast<uint64_t>(threadIdx.x) * ntiles + tile] = h[threadIdx.x];
     __syncthreads();
   }
 }
@@ -117,106 +135,295 @@ struct LanesOut {
   uint32_t *dst[kSortLanes];
 };
 
-// One LSD pass: rank each tile's items stably by digit, place them digit-major
-// in LDS, write each digit's run of the tile to its global position.
-template <typename K, int NW, int kItems, typename D>
-__global__ void __launch_bounds__(kSNT) k_sort_scatter(const K *__restrict__ kin, LanesIn vin, uint64_t n, D dig,
-                                                       int bits, uint32_t ntiles, const uint32_t *__restrict__ offs,
-                                                       K *__restrict__ kout, LanesOut vout) {
-  constexpr int T = kSNT * kItems;
-  constexpr int NL = NW > 0 ? NW : 1;
-  __shared__ K sk[T];
-  __shared__ uint32_t sv[NL][NW > 0 ? T : 1];
-  __shared__ uint8_t sd[D::kStore ? T : 1];
-  __shared__ uint32_t wcnt[kSWaves][kSDigits];
-  __shared__ uint32_t dstart[kSDigits];
-  __shared__ uint32_t adj[kSDigits];
-  __shared__ uint32_t scan_tmp[kSWaves + 1];
-  const int lane = __lane_id();
+// Stable ranks of a wave's items of one step among the wave's items so far:
+// lanes of the same digit are found with one ballot per digit bit, `cnt` (LDS, the
+// wave's own) holds the running counts. Returns the item's rank in its digit.
+__device__ __forceinline__ uint32_t wave_rank(uint32_t d, bool ok, int bits, uint16_t *cnt) {
+  const uint64_t all = __ballot(ok);
+  uint32_t plo = static_cast<uint32_t>(all), phi = static_cast<uint32_t>(all >> 32);
+#pragma unroll
+  for (int b = 0; b < kSDigitBits; ++b) {
+    if (b < bits) {
+      const uint32_t m = static_cast<uint32_t>(static_cast<int32_t>(d << (31 - b)) >> 31);  // all ones when bit b is set
+      const uint64_t bb = __ballot(m != 0);
+      plo &= ~(static_cast<uint32_t>(bb) ^ m);
+      phi &= ~(static_cast<uint32_t>(bb >> 32) ^ m);
+    }
+  }
+  const uint32_t before = __builtin_amdgcn_mbcnt_hi(phi, __builtin_amdgcn_mbcnt_lo(plo, 0u));
+  // every lane reads the wave's running count before the group's first lane
+  // (the only writer of this digit in this step) stores the new one; LDS
+  // operations of one wave complete in order
+  const uint32_t pre = ok ? cnt[d] : 0u;
+  if (ok && before == 0) cnt[d] = static_cast<uint16_t>(pre + __popc(plo) + __popc(phi));
+  return pre + before;
+}
+
+// Turns the waves' digit counts of a tile into start positions in the tile's
+// digit-major order (wave order = item order) and returns, in thread t < kSDigits,
+// the start of digit t. All threads call it (barriers).
+template <int NT>
+__device__ __forceinline__ uint32_t tile_starts(uint16_t (*wcnt)[kSDigits], uint32_t *scan_tmp) {
+  constexpr int NW = NT / 64;
+  const int t = threadIdx.x;
+  uint32_t c[NW], tot = 0;
+  if (t < kSDigits) {
+#pragma unroll
+    for (int x = 0; x < NW; ++x) {
+      c[x] = wcnt[x][t];
+      tot += c[x];
+    }
+  }
+  uint32_t all;
+  const uint32_t ds = block_exclusive_scan<NT, uint32_t>(tot, scan_tmp, &all);
+  if (t < kSDigits) {
+    uint32_t run = ds;
+#pragma unroll
+    for (int x = 0; x < NW; ++x) {
+      wcnt[x][t] = static_cast<uint16_t>(run);
+      run += c[x];
+    }
+  }
+  return ds;
+}
+
+template <typename K, int kItems, bool kStoreDigit>
+struct ScatterLds {
+  K sk[kSNT * kItems];  // the tile's keys, then each value lane
+  uint8_t sd[kStoreDigit ? kSNT * kItems : 4];
+  __align__(4) uint16_t wcnt[kSWaves][kSDigits];
+  uint32_t adj[kSDigits];
+  uint32_t scan_tmp[kSWaves];
+};
+
+// Keeps the compiler from interleaving more than a few items' address
+// arithmetic, which cost registers beyond the 128 that two workgroups per CU allow.
+template <int kEvery>
+__device__ __forceinline__ void item_fence(int j) {
+  if (j % kEvery == kEvery - 1) __builtin_amdgcn_sched_barrier(0);
+}
+
+// One tile of a scatter pass. kFull: the tile has all its items. Uniform across
+// the workgroup (barriers).
+template <typename K, int NW, int kItems, typename D, bool kSelfScan, bool kFull>
+__device__ __forceinline__ void scatter_tile(ScatterLds<K, kItems, D::kStore> &L, const K *__restrict__ kin,
+                                             const LanesIn &vin, uint64_t base, uint32_t in_tile, const D &dig, int bits,
+                                             uint32_t tile, uint32_t ntiles, const uint32_t *__restrict__ offs,
+                                             K *__restrict__ kout, const LanesOut &vout) {
+  uint32_t *sv = reinterpret_cast<uint32_t *>(L.sk);
   const int w = threadIdx.x / 64;
-  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+  const uint32_t first = static_cast<uint32_t>(w) * (64 * kItems) + __lane_id();  // this thread's items: first + 64 j
+  auto has = [&](uint32_t i) { return kFull || i < in_tile; };
+  for (int x = threadIdx.x; x < kSWaves * kSDigits / 2; x += kSNT) reinterpret_cast<uint32_t *>(L.wcnt)[x] = 0;
+  K key[kItems];
+  {
+    const K *src = kin + base;
 #pragma unroll
-    for (int x = 0; x < kSWaves; ++x) wcnt[x][threadIdx.x] = 0;
-    __syncthreads();
-    const uint64_t base = static_cast<uint64_t>(tile) * T;
-    const uint64_t wbase = base + static_cast<uint64_t>(w) * (64 * kItems);
-    K key[kItems];
-    uint32_t val[NL][kItems], lo[kItems], dg[kItems];
+    for (int j = 0; j < kItems; ++j) key[j] = has(first + j * 64) ? src[first + j * 64] : K(0);
+  }
+  __syncthreads();
+  uint32_t pos[(kItems + 1) / 2];  // two 16-bit positions each
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-      const uint64_t i = wbase + static_cast<uint64_t>(j) * 64 + lane;
-      const bool ok = i < n;
-      key[j] = ok ? kin[i] : K(0);
-#pragma unroll
-      for (int v = 0; v < NW; ++v)
-        val[v][j] = ok ? (vin.src[v] ? vin.src[v][i * vin.stride[v]] : static_cast<uint32_t>(i)) : 0u;
+  for (int j = 0; j < kItems; ++j) {
+    const uint32_t r = wave_rank(dig(key[j]), has(first + j * 64), bits, L.wcnt[w]);
+    pos[j / 2] = j % 2 ? pos[j / 2] | r << 16 : r;
+    item_fence<2>(j);
+  }
+  __syncthreads();
+  const uint32_t ds = tile_starts<kSNT>(L.wcnt, L.scan_tmp);
+  // global start of this tile's run of digit t, minus its start inside the tile
+  const uint32_t t = threadIdx.x;
+  if constexpr (kSelfScan) {
+    // wave w sums tiles w, w + kSWaves, ...; a lane takes four digits
+    uint4 total = make_uint4(0, 0, 0, 0), before = total;
+#pragma unroll 8
+    for (uint32_t x = w; x < ntiles; x += kSWaves) {
+      const uint4 c = reinterpret_cast<const uint4 *>(offs)[x * (kSDigits / 4) + __lane_id()];
+      const uint32_t m = x < tile ? ~0u : 0u;
+      total.x += c.x; total.y += c.y; total.z += c.z; total.w += c.w;
+      before.x += c.x & m; before.y += c.y & m; before.z += c.z & m; before.w += c.w & m;
     }
+    static_assert(sizeof(L.sk) >= 2 * kSWaves * kSDigits * 4, "the waves' sums fit the tile's LDS");
+    uint4 *part = reinterpret_cast<uint4 *>(L.sk);  // free until the keys are placed
+    part[w * (kSDigits / 4) + __lane_id()] = total;
+    part[(kSWaves + w) * (kSDigits / 4) + __lane_id()] = before;
+    __syncthreads();
+    uint32_t tot = 0, bef = 0;
+    if (t < kSDigits) {
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) {
-      const uint64_t i = wbase + static_cast<uint64_t>(j) * 64 + lane;
-      const bool ok = i < n;
-      const uint32_t d = dig(key[j]);
-      dg[j] = d;
-      uint64_t peers = __ballot(ok);
-#pragma unroll
-      for (int b = 0; b < kSDigitBits; ++b) {
-        if (b < bits) {
-          const bool set = (d >> b) & 1u;
-          const uint64_t bb = __ballot(set);
-          peers &= set ? bb : ~bb;
-        }
+      for (int x = 0; x < kSWaves; ++x) {
+        tot += sv[x * kSDigits + t];
+        bef += sv[(kSWaves + x) * kSDigits + t];
       }
-      const uint32_t before = lane_prefix(peers);
-      // every lane reads the wave's running count before the group's first lane
-      // (the only writer of this digit in this step) stores the new one; LDS
-      // operations of one wave complete in order
-      const uint32_t pre = ok ? wcnt[w][d] : 0u;
-      if (ok && before == 0) wcnt[w][d] = pre + static_cast<uint32_t>(__popcll(peers));
-      lo[j] = pre + before;
-    }
-    __syncthreads();
-    // digit t: exclusive prefix over the waves (wave order = item order), tile total
-    const int t = threadIdx.x;
-    uint32_t tot = 0;
-#pragma unroll
-    for (int x = 0; x < kSWaves; ++x) {
-      const uint32_t c = wcnt[x][t];
-      wcnt[x][t] = tot;
-      tot += c;
     }
     uint32_t all;
-    const uint32_t ds = block_exclusive_scan<kSNT, uint32_t>(tot, scan_tmp, &all);
-    dstart[t] = ds;
-    // global start of this tile's run of digit t, minus its start inside the tile
-    adj[t] = static_cast<uint32_t>(t) <= dig.mask ? offs[static_cast<uint64_t>(t) * ntiles + tile] - ds : 0u;
+    const uint32_t start = block_exclusive_scan<kSNT, uint32_t>(tot, L.scan_tmp, &all);
+    if (t < kSDigits) L.adj[t] = start + bef - ds;
+  } else {
+    if (t < kSDigits) L.adj[t] = t <= dig.mask ? offs[static_cast<uint64_t>(t) * ntiles + tile] - ds : 0u;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const uint32_t d = dig(key[j]);
+    const uint32_t p = ((pos[j / 2] >> (j % 2 * 16)) & 0xFFFFu) + L.wcnt[w][d];
+    pos[j / 2] = j % 2 ? (pos[j / 2] & 0xFFFFu) | p << 16 : (pos[j / 2] & 0xFFFF0000u) | p;
+    if (has(first + j * 64)) {
+      L.sk[p] = key[j];
+      if constexpr (D::kStore) L.sd[p] = static_cast<uint8_t>(d);
+    }
+    item_fence<8>(j);
+  }
+  uint32_t val[kItems];
+  auto load_lane = [&](int v) {
+    if (!vin.src[v]) {  // the row ids
+#pragma unroll
+      for (int j = 0; j < kItems; ++j) val[j] = static_cast<uint32_t>(base) + first + j * 64;
+    } else if (vin.stride[v] == 1) {
+      const uint32_t *src = vin.src[v] + base;
+#pragma unroll
+      for (int j = 0; j < kItems; ++j) val[j] = has(first + j * 64) ? src[first + j * 64] : 0u;
+    } else {
+      const uint32_t st = vin.stride[v];
+      const uint32_t *src = vin.src[v] + base * st;
+#pragma unroll
+      for (int j = 0; j < kItems; ++j) val[j] = has(first + j * 64) ? src[(first + j * 64) * st] : 0u;
+    }
+  };
+  if constexpr (NW > 0) load_lane(0);  // in flight while the keys go out
+  __syncthreads();
+  uint32_t o[kItems];  // where tile position t + j * kSNT goes
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const uint32_t p = t + j * kSNT;
+    o[j] = 0;
+    if (has(p)) {
+      const K k = L.sk[p];
+      uint32_t d;
+      if constexpr (D::kStore)
+        d = L.sd[p];
+      else
+        d = dig(k);
+      o[j] = L.adj[d] + p;
+      kout[o[j]] = k;
+    }
+    item_fence<8>(j);
+  }
+#pragma unroll
+  for (int v = 0; v < NW; ++v) {
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
-      const uint64_t i = wbase + static_cast<uint64_t>(j) * 64 + lane;
-      if (i < n) {
-        const uint32_t d = D::kStore ? dg[j] : dig(key[j]);
-        const uint32_t p = dstart[d] + wcnt[w][d] + lo[j];
-        sk[p] = key[j];
+      if (has(first + j * 64)) sv[(pos[j / 2] >> (j % 2 * 16)) & 0xFFFFu] = val[j];
+      item_fence<8>(j);
+    }
+    if (v + 1 < NW) load_lane(v + 1);
+    __syncthreads();
+    uint32_t *__restrict__ dst = vout.dst[v];
 #pragma unroll
-        for (int v = 0; v < NW; ++v) sv[v][p] = val[v][j];
-        if constexpr (D::kStore) sd[p] = static_cast<uint8_t>(d);
+    for (int j = 0; j < kItems; ++j) {
+      if (has(t + j * kSNT)) dst[o[j]] = sv[t + j * kSNT];
+      item_fence<8>(j);
+    }
+  }
+  __syncthreads();
+}
+
+// One LSD pass: rank each tile's items stably by digit, place them digit-major
+// in LDS, write each digit's run of the tile to its global position. Keys and
+// value lanes take turns in one LDS copy of the tile, so the tile's size does not
+// depend on the row's width. Bound by memory: 2^28 4-byte pairs move 4.3 GB in
+// 0.93 ms a pass (4.6 TB/s, what a copy reaches); each XCD takes a contiguous
+// eighth of the tiles, so that the partial lines at the ends of neighbouring
+// tiles' runs meet in one L2 (with tiles dealt round-robin: 1.5 ms).
+// One tile per workgroup: a loop over tiles made the compiler keep every item's
+// addresses across tiles, and the registers spilled.
+// kSelfScan: `offs` holds the raw counts, tile-major, and each workgroup sums
+// the columns it needs; else the scanned counts, digit-major.
+template <typename K, int NW, int kItems, typename D, bool kSelfScan>
+__global__ void __launch_bounds__(kSNT, 4) k_sort_scatter(const K *__restrict__ kin, LanesIn vin, uint64_t n, D dig,
+                                                          int bits, uint32_t ntiles, const uint32_t *__restrict__ offs,
+                                                          K *__restrict__ kout, LanesOut vout) {
+  constexpr uint32_t T = kSNT * kItems;
+  static_assert(T < 65536, "counts and positions of a tile fit 16 bits");
+  __shared__ ScatterLds<K, kItems, D::kStore> L;
+  const uint32_t per_xcd = (ntiles + kXcds - 1) / kXcds;
+  const uint32_t tile = blockIdx.x % kXcds * per_xcd + blockIdx.x / kXcds;
+  if (tile >= ntiles) return;
+  const uint64_t base = static_cast<uint64_t>(tile) * T;
+  if (n - base >= T)
+    scatter_tile<K, NW, kItems, D, kSelfScan, true>(L, kin, vin, base, T, dig, bits, tile, ntiles, offs, kout, vout);
+  else
+    scatter_tile<K, NW, kItems, D, kSelfScan, false>(L, kin, vin, base, static_cast<uint32_t>(n - base), dig, bits,
+                                                     tile, ntiles, offs, kout, vout);
+}
+
+// All passes of an input that fits one workgroup's LDS: the pairs stay there
+// between passes. (A sort of 1,000 pairs by 32 bits was 20 launches, 210 us.)
+constexpr int kBNT = 1024;
+template <typename K>
+constexpr int block_items_max() {
+  return sizeof(K) == 8 ? 8 : 16;
+}
+template <typename K, int kItems>
+__global__ void __launch_bounds__(kBNT) k_sort_block(const K *__restrict__ kin, const uint32_t *__restrict__ vin,
+                                                     uint32_t n, int key_bits, K *__restrict__ kout,
+                                                     uint32_t *__restrict__ vout) {
+  constexpr int T = kBNT * kItems;
+  __shared__ K sk[T];
+  __shared__ uint32_t sv[T];
+  __shared__ __align__(4) uint16_t wcnt[kBNT / 64][kSDigits];
+  __shared__ uint32_t scan_tmp[kBNT / 64];
+  const int lane = __lane_id();
+  const int w = threadIdx.x / 64;
+  const uint32_t first = static_cast<uint32_t>(w) * (64 * kItems) + lane;
+  K key[kItems];
+  uint32_t val[kItems], r[kItems];
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const uint32_t i = first + j * 64;
+    key[j] = i < n ? kin[i] : K(0);
+    val[j] = i < n && vin ? vin[i] : i;
+  }
+  const int passes = (key_bits + kSDigitBits - 1) / kSDigitBits;
+  int shift = 0;
+  for (int p = 0; p < passes; ++p) {
+    const int bits = (key_bits - shift + (passes - p) - 1) / (passes - p);
+    const KeyDigit<K> dig{shift, (1u << bits) - 1u};
+    for (int x = threadIdx.x; x < kBNT / 64 * kSDigits / 2; x += kBNT) reinterpret_cast<uint32_t *>(wcnt)[x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) r[j] = wave_rank(dig(key[j]), first + j * 64 < n, bits, wcnt[w]);
+    __syncthreads();
+    tile_starts<kBNT>(wcnt, scan_tmp);
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+      if (first + j * 64 < n) {
+        const uint32_t at = wcnt[w][dig(key[j])] + r[j];
+        sk[at] = key[j];
+        sv[at] = val[j];
       }
     }
     __syncthreads();
-    const uint32_t in_tile = static_cast<uint32_t>(min<uint64_t>(T, n - base));
-    for (uint32_t p = threadIdx.x; p < in_tile; p += kSNT) {
-      const K k = sk[p];
-      uint32_t d;
-      if constexpr (D::kStore)
-        d = sd[p];
-      else
-        d = dig(k);
-      const uint32_t o = adj[d] + p;
-      kout[o] = k;
+    // (the next pass writes sk and sv only after two more barriers)
 #pragma unroll
-      for (int v = 0; v < NW; ++v) vout.dst[v][o] = sv[v][p];
+    for (int j = 0; j < kItems; ++j) {
+      const uint32_t i = first + j * 64;
+      if (i < n) {
+        key[j] = sk[i];
+        val[j] = sv[i];
+      }
     }
-    __syncthreads();
+    shift += bits;
+  }
+#pragma unroll
+  for (int j = 0; j < kItems; ++j) {
+    const uint32_t i = first + j * 64;
+    if (i < n) {
+      kout[i] = key[j];
+      vout[i] = val[j];
+    }
   }
 }
 
@@ -260,11 +467,13 @@ PassBufs<K, NW> pass_bufs(Workspace &ws, uint64_t n, int T) {
 template <typename K, int NW, int kItems, typename MakeDigit>
 int lsd_passes(const K *kin, LanesIn vin, uint64_t n, int total_bits, int digit_bits, K *kout, LanesOut vout,
                const PassBufs<K, NW> &b, MakeDigit make, hipStream_t s) {
+  constexpr int T = kSNT * kItems;
   const int passes = (total_bits + digit_bits - 1) / digit_bits;
   const unsigned hist_grid =
       static_cast<unsigned>(std::min<uint64_t>(b.ntiles, uint64_t(device_cu_count()) * kHistPerCu));
-  const unsigned scat_grid =
-      static_cast<unsigned>(std::min<uint64_t>(b.ntiles, uint64_t(device_cu_count()) * kScatPerCu));
+  const unsigned scat_grid = static_cast<unsigned>((b.ntiles + kXcds - 1) / kXcds * kXcds);
+  const uint32_t nt = static_cast<uint32_t>(b.ntiles);
+  const bool self_scan = b.ntiles <= kSelfScanTiles;
   int shift = 0;
   const K *src_k = kin;
   LanesIn src_v = vin;
@@ -275,16 +484,22 @@ int lsd_passes(const K *kin, LanesIn vin, uint64_t n, int total_bits, int digit_
     LanesOut dv{};
     for (int v = 0; v < NW; ++v) dv.dst[v] = to_out ? vout.dst[v] : b.v2[v];
     const auto dig = make(shift, (1u << bits) - 1u);
-    if (reinterpret_cast<uintptr_t>(src_k) % 16 == 0)
-      EIGER_LAUNCH("sort_hist", (k_sort_hist<K, kItems, decltype(dig), true>), dim3(hist_grid), dim3(kSNT), 0, s,
-                   src_k, n, dig, static_cast<uint32_t>(b.ntiles), b.cnt);
-    else
-      EIGER_LAUNCH("sort_hist", (k_sort_hist<K, kItems, decltype(dig), false>), dim3(hist_grid), dim3(kSNT), 0, s,
-                   src_k, n, dig, static_cast<uint32_t>(b.ntiles), b.cnt);
-    int rc = exclusive_scan_u32(b.cnt, b.cnt, (static_cast<uint64_t>(dig.mask) + 1) * b.ntiles, b.tmp, b.total, s);
-    if (rc) return rc;
-    EIGER_LAUNCH("sort_scatter", (k_sort_scatter<K, NW, kItems, decltype(dig)>), dim3(scat_grid), dim3(kSNT), 0, s,
-                 src_k, src_v, n, dig, bits, static_cast<uint32_t>(b.ntiles), b.cnt, dk, dv);
+    using D = std::remove_const_t<decltype(dig)>;
+    const bool vec = reinterpret_cast<uintptr_t>(src_k) % 16 == 0;
+#define EIGER_HIST(VEC, TM)                                                                                        \
+  EIGER_LAUNCH("sort_hist", (k_sort_hist<K, T, D, VEC, TM>), dim3(hist_grid), dim3(kHNT), 0, s, src_k, n, dig, nt, b.cnt)
+    if (self_scan) {
+      if (vec) EIGER_HIST(true, true); else EIGER_HIST(false, true);
+      EIGER_LAUNCH("sort_scatter", (k_sort_scatter<K, NW, kItems, D, true>), dim3(scat_grid), dim3(kSNT), 0, s, src_k,
+                   src_v, n, dig, bits, nt, b.cnt, dk, dv);
+    } else {
+      if (vec) EIGER_HIST(true, false); else EIGER_HIST(false, false);
+      int rc = exclusive_scan_u32(b.cnt, b.cnt, (static_cast<uint64_t>(dig.mask) + 1) * b.ntiles, b.tmp, b.total, s);
+      if (rc) return rc;
+      EIGER_LAUNCH("sort_scatter", (k_sort_scatter<K, NW, kItems, D, false>), dim3(scat_grid), dim3(kSNT), 0, s, src_k,
+                   src_v, n, dig, bits, nt, b.cnt, dk, dv);
+    }
+#undef EIGER_HIST
     src_k = dk;
     for (int v = 0; v < NW; ++v) {
       src_v.src[v] = dv.dst[v];
@@ -295,11 +510,18 @@ int lsd_passes(const K *kin, LanesIn vin, uint64_t n, int total_bits, int digit_
   return EIGER_OK;
 }
 
+template <typename K, int kItems>
+int sort_block(const K *kin, const uint32_t *vin, uint64_t n, int key_bits, K *kout, uint32_t *vout, hipStream_t s) {
+  EIGER_LAUNCH("sort_block", (k_sort_block<K, kItems>), dim3(1), dim3(kBNT), 0, s, kin, vin, static_cast<uint32_t>(n),
+               key_bits, kout, vout);
+  return EIGER_OK;
+}
+
 template <typename K>
 int sort_impl(const K *kin, const uint32_t *vin, uint64_t n, int key_bits, K *kout, uint32_t *vout, Workspace &ws,
               hipStream_t s) {
-  constexpr int kItems = items_per_thread<K>();
-  const PassBufs<K, 1> b = pass_bufs<K, 1>(ws, n, kSNT * kItems);
+  const bool large = use_large<K, 1>(n);
+  const PassBufs<K, 1> b = pass_bufs<K, 1>(ws, n, kSNT * (large ? items_large<K, 1>() : kItemsSmall));
   if (!ws.base || n == 0) return EIGER_OK;
   const int passes = (key_bits + kSDigitBits - 1) / kSDigitBits;
   if (passes == 0 || n == 1) {
@@ -307,13 +529,17 @@ int sort_impl(const K *kin, const uint32_t *vin, uint64_t n, int key_bits, K *ko
     EIGER_LAUNCH("sort_copy", k_sort_copy<K>, dim3(grid), dim3(256), 0, s, kin, vin, n, kout, vout);
     return EIGER_OK;
   }
+  if (n <= kBNT) return sort_block<K, 1>(kin, vin, n, key_bits, kout, vout, s);
+  if (n <= kBNT * 4) return sort_block<K, 4>(kin, vin, n, key_bits, kout, vout, s);
+  if (n <= kBNT * block_items_max<K>()) return sort_block<K, block_items_max<K>()>(kin, vin, n, key_bits, kout, vout, s);
   LanesIn in{};
   in.src[0] = vin;
   in.stride[0] = 1;
   LanesOut out{};
   out.dst[0] = vout;
-  return lsd_passes<K, 1, kItems>(kin, in, n, key_bits, kSDigitBits, kout, out, b,
-                                  [](int shift, uint32_t mask) { return KeyDigit<K>{shift, mask}; }, s);
+  const auto make = [](int shift, uint32_t mask) { return KeyDigit<K>{shift, mask}; };
+  if (large) return lsd_passes<K, 1, items_large<K, 1>()>(kin, in, n, key_bits, kSDigitBits, kout, out, b, make, s);
+  return lsd_passes<K, 1, kItemsSmall>(kin, in, n, key_bits, kSDigitBits, kout, out, b, make, s);
 }
 
 // Partition bounds: off[p] = first position whose partition id is >= p (the
@@ -335,34 +561,16 @@ __global__ void __launch_bounds__(256) k_part_bounds(const K *__restrict__ keys,
   }
 }
 
-// Tile items for hash partitioning: the largest count (at most 32 per thread)
-// whose LDS copy (key, lanes, digit byte) stays within 64 KB, two workgroups per CU.
-template <typename K, int NW>
-constexpr int part_items() {
-  constexpr int per = 65536 / (kSNT * static_cast<int>(sizeof(K) + 4 * NW + 1));
-  return per > 32 ? 32 : per;
-}
-
-// Widest digit of a partitioning pass: at least 32 items of a tile per digit on
-// average, so each digit's run of the tile is written in whole lines more often
-// (2^28 rows, 4-byte keys and two 4-byte lanes, 4,864-item tiles: 14 bits in
-// two 7-bit passes 7.6 ms, 16 bits in two 8-bit passes 11.2 ms).
-constexpr int part_digit_bits(int tile) {
-  int b = 1;
-  while (b < kSDigitBits && (tile >> (b + 1)) >= 32) ++b;
-  return b;
-}
-
 template <typename K, int NW>
 int partition_impl(const K *keys, uint64_t n, const PartLanes &cols, int bits, Workspace &ws, PartitionOut *out,
                    hipStream_t s, bool run) {
-  constexpr int kItems = part_items<K, NW>();
+  const bool large = use_large<K, NW>(n);
   const uint32_t F = 1u << bits;
   K *ok = ws.take<K>(n ? n : 1);
   LanesOut ov{};
   for (int v = 0; v < NW; ++v) ov.dst[v] = ws.take<uint32_t>(n ? n : 1);
   uint32_t *off = ws.take<uint32_t>(uint64_t(F) + 1);
-  const PassBufs<K, NW> b = pass_bufs<K, NW>(ws, n, kSNT * kItems);
+  const PassBufs<K, NW> b = pass_bufs<K, NW>(ws, n, kSNT * (large ? items_large<K, NW>() : kItemsSmall));
   out->keys = ok;
   for (int v = 0; v < kSortLanes; ++v) out->words[v] = v < NW ? ov.dst[v] : nullptr;
   out->off = off;
@@ -374,9 +582,9 @@ int partition_impl(const K *keys, uint64_t n, const PartLanes &cols, int bits, W
       in.stride[v] = cols.stride[v];
     }
     const int top = 64 - bits;
-    int rc = lsd_passes<K, NW, kItems>(
-        keys, in, n, bits, part_digit_bits(kSNT * kItems), ok, ov, b,
-        [top](int shift, uint32_t mask) { return PartDigit<K>{top, shift, mask}; }, s);
+    const auto make = [top](int shift, uint32_t mask) { return PartDigit<K>{top, shift, mask}; };
+    const int rc = large ? lsd_passes<K, NW, items_large<K, NW>()>(keys, in, n, bits, kSDigitBits, ok, ov, b, make, s)
+                         : lsd_passes<K, NW, kItemsSmall>(keys, in, n, bits, kSDigitBits, ok, ov, b, make, s);
     if (rc) return rc;
   }
   EIGER_LAUNCH("part_bounds", k_part_bounds<K>, dim3(static_cast<unsigned>(std::min<uint64_t>((F + 256) / 256, 1024))),

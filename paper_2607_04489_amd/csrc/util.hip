@@ -62,25 +62,15 @@ __global__ void __launch_bounds__(kScanThreads) k_scan_reduce(const uint32_t *__
 __global__ void __launch_bounds__(1024) k_scan_tiles(uint64_t *__restrict__ tile_sums,
                                                      uint64_t ntiles,
                                                      uint64_t *__restrict__ total) {
-  __shared__ uint64_t part[1024];
+  __shared__ uint64_t scratch[1024 / 64];
   const uint64_t per = (ntiles + 1023) / 1024;
-  const uint64_t lo = threadIdx.x * per;
-  const uint64_t hi = lo + per < ntiles ? lo + per : ntiles;
+  const uint64_t lo = min(ntiles, threadIdx.x * per);
+  const uint64_t hi = min(ntiles, lo + per);
   uint64_t s = 0;
   for (uint64_t i = lo; i < hi; ++i) s += tile_sums[i];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint64_t run = 0;
-    for (int t = 0; t < 1024; ++t) {
-      uint64_t v = part[t];
-      part[t] = run;
-      run += v;
-    }
-    *total = run;
-  }
-  __syncthreads();
-  uint64_t run = part[threadIdx.x];
+  uint64_t all;
+  uint64_t run = block_exclusive_scan<1024, uint64_t>(s, scratch, &all);
+  if (threadIdx.x == 0) *total = all;
   for (uint64_t i = lo; i < hi; ++i) {
     uint64_t v = tile_sums[i];
     tile_sums[i] = run;

@@ -50,6 +50,16 @@ def test_groupby_int64_keys_and_values(gpu, variant):
     check(keys, vals, res)
 
 
+@pytest.mark.parametrize("key,val,nv,n", [(torch.int32, torch.int32, 2, 512 * 8192 + 3), (torch.int32, torch.int64, 2, 512 * 8192 + 3),
+                                          (torch.int32, torch.int32, 0, 512 * 10240 + 3), (torch.int64, torch.int64, 2, 512 * 6144 + 3),
+                                          (torch.int64, torch.int32, 1, 512 * 6144 - 1)])
+def test_groupby_partition_tiles(gpu, key, val, nv, n):
+    """Partition passes of rows of 0 to 4 value lanes (stride 1 and 2), on both sides
+    of the row count from which they take the larger tiles."""
+    keys, vals = synth.groupby_input(seed=n, n=n, groups=90_000, key_dtype=key, n_vals=nv, val_dtype=val, device=gpu)
+    check(keys, vals, eg.groupby(keys, vals, forced(keys, eg.GB_PARTITION, 9)))
+
+
 def test_groupby_rule_follows_the_estimate(gpu):
     small, sv = synth.groupby_input(seed=1, n=2_000_000, groups=600, device=gpu)
     big, bv = synth.groupby_input(seed=2, n=2_000_000, groups=1_500_000, device=gpu)

@@ -47,6 +47,28 @@ def test_sort_pairs(gpu, key_bytes, key_bits, n):
     assert np.array_equal(host(vo).astype(np.int64), want_p)
 
 
+# One workgroup sorts up to 1,024 / 4,096 / 16,384 (8-byte keys: 8,192) pairs; beyond, tiles of
+# 4,096, whose counts the scatter sums itself up to 256 tiles; from 512 tiles of 10,240 (6,144)
+# pairs on, tiles of that size.
+@pytest.mark.parametrize("key_bytes,n", [(4, 2), (4, 1024), (4, 1025), (4, 4096), (4, 16384), (4, 16385),
+                                         (4, 256 * 4096), (4, 256 * 4096 + 1), (4, 512 * 10240 - 1),
+                                         (4, 512 * 10240 + 77), (8, 1023), (8, 8192), (8, 8193),
+                                         (8, 256 * 4096), (8, 256 * 4096 + 1), (8, 512 * 6144 - 1),
+                                         (8, 512 * 6144 + 77)])
+@pytest.mark.parametrize("key_bits", [5, 19, 32])
+def test_sort_pairs_at_dispatch_edges(gpu, key_bytes, n, key_bits):
+    """Each path on both sides of its bound, from keys that do not start on a 16-byte
+    boundary, with values and with generated row ids; few distinct keys (5 bits)
+    show any loss of stability."""
+    keys = rand_keys(key_bits + n, n + 1, key_bytes, key_bits, gpu)[1:]
+    vals = torch.arange(n, dtype=torch.int32, device=gpu) * 3 + 1
+    want_k, want_p = skf.sort_pairs(host(keys), key_bits)
+    for v in (None, vals):
+        ko, vo = eg.sort_pairs(keys, key_bits, v)
+        assert np.array_equal(host(ko).view(np.uint32 if key_bytes == 4 else np.uint64).astype(np.uint64), want_k)
+        assert np.array_equal(host(vo).astype(np.int64), want_p if v is None else want_p * 3 + 1)
+
+
 def test_sort_pairs_values_and_empty(gpu):
     keys = rand_keys(3, 70001, 4, 20, gpu)
     vals = torch.arange(70001, dtype=torch.int32, device=gpu).flip(0)
