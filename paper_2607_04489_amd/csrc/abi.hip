@@ -433,6 +433,7 @@ int join_checked(const eiger_column &bk, const eiger_column &bp, const eiger_col
   JoinCounters host{};
   EIGER_HIP(hipMemcpyAsync(&host, ctr, sizeof(host), hipMemcpyDeviceToHost, a.s));
   EIGER_HIP(hipStreamSynchronize(a.s));
+  add_stripes(host);
   if (host.flags & kFlagBuildOutOfRange)
     return fail(EIGER_ERR_INVALID_ARG, "eiger_join: a build key lies outside the plan's [build_min, build_max]");
   *out_count = static_cast<int64_t>(host.count);

@@ -37,8 +37,6 @@ namespace {
 
 constexpr uint32_t kBuildTile = 2048;
 constexpr int kBNT = 256;
-constexpr int kBIPT = 4;
-constexpr int kBSCAP = 4096;
 constexpr uint32_t kVarDirect = 0, kVarHash = 1, kVarRadix = 2;
 
 struct BatchJoinDev {
@@ -168,8 +166,9 @@ __global__ void __launch_bounds__(256) k_batch_build(XcdItems items, const Batch
           tab[static_cast<uint64_t>(sext(key[u])) - mn] = v;  // < range <= slots
           continue;
         }
-        uint64_t s = fmix64(static_cast<uint64_t>(sext(key[u]))) & mask;
-        for (;;) {  // slots >= 2 rows: an empty slot exists
+        const uint64_t home = fmix64(static_cast<uint64_t>(sext(key[u]))) & mask;
+        for (uint32_t step = 0;; ++step) {  // slots >= 2 rows: an empty slot exists
+          const uint64_t s = line_walk<Slot<K, P>>(home, step, mask);
           if (by_key) {
             const W old = atomicCAS(reinterpret_cast<W *>(&tab[s].key), ~W(0), static_cast<W>(key[u]));
             if (old == ~W(0)) {
@@ -183,7 +182,6 @@ __global__ void __launch_bounds__(256) k_batch_build(XcdItems items, const Batch
             tab[s].pay = pv[u];
             break;
           }
-          s = (s + 1) & mask;
         }
       }
     }
@@ -214,13 +212,12 @@ __global__ void __launch_bounds__(256) k_batch_unique(XcdItems items, const Batc
         dup |= tab[static_cast<uint64_t>(sext(key)) - mn].rowid != static_cast<uint32_t>(r);
         continue;
       }
-      uint64_t s = fmix64(static_cast<uint64_t>(sext(key))) & mask;
+      const uint64_t home = fmix64(static_cast<uint64_t>(sext(key))) & mask;
       uint32_t c = 0;
-      for (;;) {
-        const Slot<K, P> v = tab[s];
+      for (uint32_t step = 0;; ++step) {
+        const Slot<K, P> v = tab[line_walk<Slot<K, P>>(home, step, mask)];
         if (v.rowid == kEmpty) break;
         c += v.key == key;
-        s = (s + 1) & mask;
       }
       dup |= c > 1;
     }
@@ -230,79 +227,61 @@ __global__ void __launch_bounds__(256) k_batch_unique(XcdItems items, const Batc
 
 template <typename K, typename P>
 struct BatchDirectTab {
-  static constexpr bool kHashed = false;
-  static constexpr bool kRuns = false;
+  static constexpr bool kWalk = false;
+  static constexpr bool unique = true;
+  using SlotT = Slot<K, P>;
+  using Index = uint64_t;
   const Slot<K, P> *slots;
   uint64_t mn, range;
-  __device__ __forceinline__ uint32_t lookup(K key, uint32_t &first, uint64_t &psum) const {
+  __device__ __forceinline__ uint64_t start(K key, bool &in) const {
     const uint64_t d = static_cast<uint64_t>(sext(key)) - mn;
-    if (d >= range) return 0;
-    const Slot<K, P> s = slots[d];
-    if (s.rowid == kEmpty || s.key != key) return 0;
-    first = s.rowid;
-    psum += static_cast<uint64_t>(sext(s.pay));
-    return 1;
+    in = d < range;
+    return in ? d : 0;
   }
-  template <class F>
-  __device__ __forceinline__ void for_each(K key, F f) const {
-    uint32_t first;
-    uint64_t ps = 0;
-    if (lookup(key, first, ps)) f(first);
-  }
+  __device__ __forceinline__ SlotT load(uint64_t i) const { return slots[i]; }
 };
 
 template <typename K, typename P>
 struct BatchHashTab {
-  static constexpr bool kHashed = true;
-  static constexpr bool kRuns = false;
+  static constexpr bool kWalk = true;
+  static constexpr bool unique = true;
   using SlotT = Slot<K, P>;
   using Index = uint64_t;
   const Slot<K, P> *slots;
   uint64_t mask;
-  bool unique;
-  __device__ __forceinline__ uint64_t home(K key) const {
+  __device__ __forceinline__ uint64_t start(K key, bool &in) const {
+    in = true;
     return fmix64(static_cast<uint64_t>(sext(key))) & mask;
   }
-  __device__ __forceinline__ uint64_t next(uint64_t i) const { return (i + 1) & mask; }
+  __device__ __forceinline__ uint64_t walk(uint64_t i, uint32_t steps) const { return line_walk<SlotT>(i, steps, mask); }
   __device__ __forceinline__ SlotT load(uint64_t i) const { return slots[i]; }
-  template <class F>
-  __device__ __forceinline__ void for_each(K key, F f) const {
-    uint64_t i = home(key);
-    for (;;) {
-      const SlotT s = slots[i];
-      if (s.rowid == kEmpty) break;
-      if (s.key == key) f(s.rowid);
-      i = next(i);
-    }
-  }
 };
 
+// An item's rows go to the workgroup's waves in turn.
 template <typename K, typename P>
-__global__ void __launch_bounds__(kBNT) k_batch_probe(XcdItems items,
-                                                      const BatchJoinDev *__restrict__ J, BatchState *__restrict__ st,
-                                                      const Slot<K, P> *__restrict__ arena, uint32_t *ob,
-                                                      uint32_t *op) {
-  __shared__ EmitLds<kBNT, kBSCAP> L;
+__global__ void __launch_bounds__(kBNT) k_batch_probe(XcdItems items, const BatchJoinDev *__restrict__ J,
+                                                      BatchState *__restrict__ st, const Slot<K, P> *__restrict__ arena,
+                                                      uint32_t *ob, uint32_t *op) {
+  __shared__ WaveLds<K, P> L[kBNT / 64];
+  const uint32_t wave = threadIdx.x / 64;
+  constexpr uint64_t block = 64 * kWaveRows, sub = kBNT * kWaveRows;
   for (uint32_t it = items.begin(); it < items.end(); it += items.step()) {
     const Item w = items.items[it];
     const BatchJoinDev d = J[w.join];
     BatchState *s = st + w.join;
-    EmitOut o{ob + d.out_off, op + d.out_off, d.nS, &s->count, &s->checksum};
-    uint64_t fill = 0, cs = 0;
+    const EmitOut o{ob + d.out_off, op + d.out_off, d.nS, &s->count, &s->checksum};
     const K *pk = static_cast<const K *>(d.pk);
     const P *pp = static_cast<const P *>(d.pp);
     if (s->variant == kVarDirect) {
       const uint64_t mn = static_cast<uint64_t>(s->mn);
-      BatchDirectTab<K, P> tab{arena + d.tab_off, mn, static_cast<uint64_t>(s->mx) - mn + 1};
-      probe_range<kBNT, kBIPT, kBSCAP>(tab, pk, pp, static_cast<const uint32_t *>(nullptr), w.lo, w.hi, L, fill,
-                                       o, cs);
+      const BatchDirectTab<K, P> tab{arena + d.tab_off, mn, static_cast<uint64_t>(s->mx) - mn + 1};
+      WaveProbe<BatchDirectTab<K, P>, K, P> p(tab, L[wave], o);
+      p.template run<1>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, nullptr);
     } else {
-      BatchHashTab<K, P> tab{arena + d.tab_off, d.slots - 1, true};
-      probe_range<kBNT, kBIPT, kBSCAP>(tab, pk, pp, static_cast<const uint32_t *>(nullptr), w.lo, w.hi, L, fill,
-                                       o, cs);
+      const BatchHashTab<K, P> tab{arena + d.tab_off, d.slots - 1};
+      WaveProbe<BatchHashTab<K, P>, K, P, 2> p(tab, L[wave], o);
+      p.template run<1>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, nullptr);
     }
-    finish(L, o, fill, cs);
-    __syncthreads();
   }
 }
 
@@ -491,7 +470,8 @@ int enqueue_batch(const BatchPlan &bp, const BatchLayout &L, uint32_t *ob, uint3
                  L.state, arena);
   }
   if (np) {
-    EIGER_LAUNCH("batch_probe", (k_batch_probe<K, P>), dim3(xcd_grid(np, cus, 4)), dim3(kBNT), 0, s, pi, L.joins, L.state, static_cast<const Slot<K, P> *>(L.arena), ob, op);
+    EIGER_LAUNCH("batch_probe", (k_batch_probe<K, P>), dim3(xcd_grid(np, cus, static_cast<unsigned>(163840 / (sizeof(WaveLds<K, P>) * (kBNT / 64))))), dim3(kBNT), 0, s,
+                 pi, L.joins, L.state, static_cast<const Slot<K, P> *>(L.arena), ob, op);
   }
   for (const RadixJob &job : bp.radix) {
     JoinArgs a = job.args;

@@ -10,6 +10,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "variants.hpp"
 
 namespace eiger {
 
@@ -23,6 +24,17 @@ struct alignas((sizeof(K) + sizeof(P) + 4 <= 16) ? 16 : 32) Slot {
   P pay;
 };
 
+// Probe sequence of the open-addressing tables in device memory (power-of-two
+// slots): the slots of the home slot's 64 bytes, wrapping inside them, then the
+// next 64 bytes', and so on, so that the second slot costs no second memory access
+// (2^28 probes of a 1 GiB table of 32-byte slots, two slots a step: 5.78 ms; in
+// 128-byte groups 6.09; first slot and then plain linear probing 6.12).
+template <typename SlotT>
+__device__ __forceinline__ uint64_t line_walk(uint64_t home, uint32_t steps, uint64_t mask) {
+  constexpr uint64_t per = 64 / sizeof(SlotT);
+  return (((home | (per - 1)) + 1 - per + (steps & ~uint32_t(per - 1))) & mask) | ((home + steps) & (per - 1));
+}
+
 // Where pairs go. ob/op may be null (count-only); positions >= cap are dropped.
 struct EmitOut {
   uint32_t *ob;
@@ -30,6 +42,7 @@ struct EmitOut {
   uint64_t cap;
   uint64_t *cursor;    // device u64, zero before the first launch
   uint64_t *checksum;  // device u64, zero before the first launch
+  JoinStripe *stripes = nullptr;  // kStripes of them, or null: take cursor and checksum alone
 };
 
 template <int NT, int SCAP>
@@ -84,6 +97,271 @@ __device__ __forceinline__ void finish(EmitLds<NT, SCAP> &L, const EmitOut &o, u
   if (threadIdx.x == 0 && s != 0)
     atomicAdd(reinterpret_cast<unsigned long long *>(o.checksum), static_cast<unsigned long long>(s));
 }
+
+// ---- wave probes of tables in device memory ----------------------------------
+//
+// A wave probes on its own. Rows are taken 64 * kWaveRows at a time, their first
+// kEager slots loaded at once. Rows whose walk goes on are packed into a queue in
+// LDS, from which full waves take the next two slots of 64 * kWaveQueued rows. So
+// every round trip carries full waves; when a wave walked its rows until the last
+// one ended, it made 8 to 10 for rows that need 1.5 on average. A match is staged
+// the moment it is found. Bound by random accesses: 255 G/s of them from a table
+// in an XCD's L2, 55-59 G/s from a larger one.
+constexpr int kWaveRows = 4;     // rows a lane takes from the input together
+constexpr int kWaveQueued = 2;   // rows a lane takes from the queue together
+constexpr uint32_t kWaveStage = 504;
+static_assert(kWaveStage >= 64 * kWaveRows && kWaveStage >= 64 * 2 * kWaveQueued, "a step's matches fit an empty stage");
+constexpr uint32_t kWaveQueue = 64 * (kWaveRows + kWaveQueued);
+
+template <typename K, typename PS>
+struct WaveLds {
+  K key[kWaveQueue];
+  PS pay[kWaveQueue];
+  uint32_t row[kWaveQueue], step[kWaveQueue];
+  uint32_t ob[kWaveStage], op[kWaveStage];
+};
+
+// What the waves of a workgroup share to write their stages out together; two
+// copies, used in turn.
+template <int NW>
+struct WaveJoint {
+  uint64_t base[2];
+  uint32_t fill[2][NW];  // bit 31: the wave has more to do
+  uint64_t sum[NW], count[NW];
+};
+
+// Orders this wave's LDS accesses for the compiler (the hardware keeps a wave's
+// LDS operations in order).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Tab: SlotT, Index; start(key, in) -> first slot (in: false when the key cannot be
+// there), walk(first, steps) -> the slot `steps` further, load(slot); kWalk: keys may
+// lie further on; unique: build keys known to be distinct.
+template <class Tab, typename K, typename PS, int kEager = 1>
+struct WaveProbe {
+  static_assert(kEager == 1 || kEager == 2, "one or two slots at first");
+  const Tab &tab;
+  WaveLds<K, PS> &L;
+  const EmitOut &o;
+  uint64_t fill = 0;    // staged pairs; count-only: all pairs (uniform)
+  uint32_t queued = 0;  // uniform
+  uint64_t cs = 0;      // this lane's share of the checksum
+
+  __device__ __forceinline__ WaveProbe(const Tab &t, WaveLds<K, PS> &l, const EmitOut &e) : tab(t), L(l), o(e) {}
+
+  // The staged pairs to output positions base, base + 1, ...
+  __device__ __forceinline__ void write_out(uint64_t base) {
+    wave_lds_fence();
+    for (uint32_t i = __lane_id(); i < static_cast<uint32_t>(fill); i += 64) put_pair(o, base + i, L.ob[i], L.op[i]);
+    wave_lds_fence();
+    fill = 0;
+  }
+
+  // Whether the stage takes R more matches a lane.
+  __device__ __forceinline__ bool room(int R) const { return !o.ob || fill + 64 * R <= kWaveStage; }
+
+  // The stage written out by the wave alone.
+  __device__ __forceinline__ void flush_own() {
+    unsigned long long at = 0;
+    if (__lane_id() == 0)
+      at = atomicAdd(reinterpret_cast<unsigned long long *>(o.cursor), static_cast<unsigned long long>(fill));
+    write_out((uint64_t(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(at >> 32))) << 32) |
+              static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(at))));
+  }
+
+  // Between two slots of the same rows: distinct build keys match once in all
+  // their slots, so there is room; others may match in each.
+  __device__ __forceinline__ void make_room(int R) {
+    if (!tab.unique && !room(R)) flush_own();
+  }
+
+  // The next slot of R rows a lane: matches are staged; live: the walks that go on.
+  template <int R>
+  __device__ __forceinline__ void visit(const K (&key)[R], const PS (&pay)[R], const uint32_t (&row)[R], bool (&live)[R],
+                                        const typename Tab::SlotT (&sl)[R]) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      live[r] = live[r] && sl[r].rowid != kEmpty;
+      const bool hit = live[r] && sl[r].key == key[r];
+      if (hit) cs += static_cast<uint64_t>(sext(sl[r].pay)) * static_cast<uint64_t>(sext(pay[r]));
+      const uint64_t hits = __ballot(hit);
+      if (o.ob && hit) {
+        const uint32_t at = static_cast<uint32_t>(fill) + lane_prefix(hits);
+        L.ob[at] = sl[r].rowid;
+        L.op[at] = row[r];
+      }
+      fill += __popcll(hits);
+      live[r] = live[r] && !(hit && tab.unique);
+    }
+  }
+
+  // Queues the rows whose walk goes on, `step` slots from their first.
+  template <int R>
+  __device__ __forceinline__ void enqueue(const K (&key)[R], const PS (&pay)[R], const uint32_t (&row)[R],
+                                          const uint32_t (&step)[R], const bool (&live)[R]) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint64_t ons = __ballot(live[r]);
+      if (live[r]) {
+        const uint32_t at = queued + lane_prefix(ons);
+        L.key[at] = key[r];
+        L.pay[at] = pay[r];
+        L.row[at] = row[r];
+        L.step[at] = step[r];
+      }
+      queued += static_cast<uint32_t>(__popcll(ons));
+    }
+    wave_lds_fence();
+  }
+
+  // Two more steps of the last n queued rows (n <= 64 * kWaveQueued, n <= queued).
+  __device__ __forceinline__ void advance(uint32_t n) {
+    K key[kWaveQueued];
+    PS pay[kWaveQueued];
+    uint32_t row[kWaveQueued], step[kWaveQueued];
+    bool live[kWaveQueued];
+    typename Tab::SlotT s0[kWaveQueued], s1[kWaveQueued];
+    queued -= n;
+#pragma unroll
+    for (int r = 0; r < kWaveQueued; ++r) {
+      const uint32_t i = r * 64 + __lane_id();
+      live[r] = i < n;
+      const uint32_t e = queued + (live[r] ? i : 0);
+      key[r] = L.key[e];
+      pay[r] = L.pay[e];
+      row[r] = L.row[e];
+      step[r] = L.step[e];
+    }
+#pragma unroll
+    for (int r = 0; r < kWaveQueued; ++r) {
+      bool in;
+      const typename Tab::Index i = tab.start(key[r], in);
+      s0[r] = tab.load(tab.walk(i, step[r]));
+      s1[r] = tab.load(tab.walk(i, step[r] + 1));
+      step[r] += 2;
+    }
+    wave_lds_fence();
+    visit<kWaveQueued>(key, pay, row, live, s0);
+    make_room(kWaveQueued);
+    visit<kWaveQueued>(key, pay, row, live, s1);
+    enqueue<kWaveQueued>(key, pay, row, step, live);
+  }
+
+  // Probe rows [lo, hi) in blocks of 64 * kWaveRows rows, `stride` rows apart,
+  // until every match is written out; a block's columns are loaded while the one
+  // before is probed. J null: the wave reserves output for its own stage. Else
+  // the waves of the workgroup (all NW call this) write their stages out together
+  // whenever one is full, for one atomic: atomics on one cursor run at 10 ns each
+  // (2^27 probes, 121M matches: 3.2 ms of them with 380 pairs each).
+  template <int NW>
+  __device__ __forceinline__ void run(const K *__restrict__ pk, const PS *__restrict__ pp,
+                                      const uint32_t *__restrict__ prow, uint64_t lo, uint64_t hi, uint64_t stride,
+                                      WaveJoint<NW> *J) {
+    K key[kWaveRows], nkey[kWaveRows];
+    PS pay[kWaveRows], npay[kWaveRows];
+    uint32_t row[kWaveRows], nrow[kWaveRows], step[kWaveRows];
+    auto load = [&](uint64_t t) {
+#pragma unroll
+      for (int r = 0; r < kWaveRows; ++r) {
+        const uint64_t j = t + r * 64 + __lane_id(), i = j < hi ? j : hi - 1;
+        nkey[r] = pk[i];
+        npay[r] = pp[i];
+        nrow[r] = prow ? prow[i] : static_cast<uint32_t>(i);
+      }
+    };
+    uint64_t t = lo;
+    if (t < hi) load(t);
+    for (uint32_t round = 0;; ++round) {
+      for (;;) {
+        if (Tab::kWalk && (queued >= 64 * kWaveQueued || (t >= hi && queued))) {
+          if (!room(kWaveQueued)) break;
+          if constexpr (Tab::kWalk) advance(queued < 64 * kWaveQueued ? queued : 64 * kWaveQueued);
+        } else if (t < hi) {
+          if (!room(kWaveRows)) break;
+          bool live[kWaveRows];
+          typename Tab::Index home[kWaveRows];
+          typename Tab::SlotT s0[kWaveRows], s1[kWaveRows];
+#pragma unroll
+          for (int r = 0; r < kWaveRows; ++r) {
+            key[r] = nkey[r];
+            pay[r] = npay[r];
+            row[r] = nrow[r];
+            step[r] = kEager;
+            bool in;
+            home[r] = tab.start(key[r], in);
+            live[r] = in && t + r * 64 + __lane_id() < hi;
+            s0[r] = tab.load(home[r]);
+            if constexpr (Tab::kWalk && kEager > 1) s1[r] = tab.load(tab.walk(home[r], 1));
+          }
+          t += stride;
+          if (t < hi) load(t);
+          visit<kWaveRows>(key, pay, row, live, s0);
+          if constexpr (Tab::kWalk) {
+            if constexpr (kEager > 1) {
+              make_room(kWaveRows);
+              visit<kWaveRows>(key, pay, row, live, s1);
+            }
+            enqueue<kWaveRows>(key, pay, row, step, live);
+          } else {
+            wave_lds_fence();
+          }
+        } else {
+          break;
+        }
+      }
+      bool done = t >= hi && queued == 0;  // nothing left but the stage
+      if (!o.ob) break;
+      if (!J) {
+        if (fill) flush_own();
+      } else {
+        const uint32_t w = threadIdx.x / 64, par = round & 1;
+        if (__lane_id() == 0) J->fill[par][w] = static_cast<uint32_t>(fill) | (done ? 0u : 1u << 31);
+        __syncthreads();
+        uint32_t total = 0, before = 0, busy = 0;
+#pragma unroll
+        for (uint32_t x = 0; x < NW; ++x) {
+          const uint32_t f = J->fill[par][x];
+          before += x < w ? f & 0x7FFFFFFFu : 0u;
+          total += f & 0x7FFFFFFFu;
+          busy |= f >> 31;
+        }
+        if (threadIdx.x == 0 && total)
+          J->base[par] = atomicAdd(reinterpret_cast<unsigned long long *>(o.cursor), static_cast<unsigned long long>(total));
+        __syncthreads();
+        write_out(J->base[par] + before);
+        done = !busy;
+      }
+      if (done) break;
+    }
+    // totals: the workgroup's in one atomic each, or the wave's
+    uint64_t sum = wave_sum_u64(cs), count = o.ob ? 0 : fill;
+    uint64_t *to_sum = o.checksum, *to_count = o.cursor;
+    if (J) {
+      if (__lane_id() == 0) {
+        J->sum[threadIdx.x / 64] = sum;
+        J->count[threadIdx.x / 64] = count;
+      }
+      __syncthreads();
+      if (threadIdx.x != 0) return;
+      sum = count = 0;
+      for (int x = 0; x < NW; ++x) {
+        sum += J->sum[x];
+        count += J->count[x];
+      }
+      if (o.stripes) {
+        to_sum = &o.stripes[blockIdx.x % kStripes].checksum;
+        to_count = &o.stripes[blockIdx.x % kStripes].count;
+      }
+    } else if (__lane_id() != 0) {
+      return;
+    }
+    if (sum) atomicAdd(reinterpret_cast<unsigned long long *>(to_sum), static_cast<unsigned long long>(sum));
+    if (count) atomicAdd(reinterpret_cast<unsigned long long *>(to_count), static_cast<unsigned long long>(count));
+  }
+};
 
 // Registers of one probe sub-tile: up to IPT rows per thread, rows
 // lo + k * NT + threadIdx.x. (Holding the next sub-tile in registers as well

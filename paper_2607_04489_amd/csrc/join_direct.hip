@@ -117,7 +117,7 @@ int direct_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   if (!ws.base) return EIGER_OK;
   hipStream_t s = a.s;
   int rc;
-  if ((rc = fill_u64(reinterpret_cast<uint64_t *>(c), 4, 0, s))) return rc;
+  if ((rc = zero_counters(c, s))) return rc;
   if ((rc = fill_u32(off, range, 0, s))) return rc;
   const K *bk = static_cast<const K *>(a.bk);
   if (a.nR) {

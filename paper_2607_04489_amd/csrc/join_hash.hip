@@ -10,7 +10,7 @@
 // keys reach both ends of the key domain, by CAS on the row-id word followed
 // by a duplicate check. Empty slots have row id 0xFFFFFFFF either way. The
 // table is a multiset: duplicate build keys occupy several slots and a probe
-// walks the whole cluster (linear probing) until an empty slot.
+// walks (line_walk) until an empty slot.
 #include <limits>
 #include <type_traits>
 
@@ -21,14 +21,15 @@ namespace eiger {
 
 namespace {
 
-constexpr int kNT = 256;
-constexpr int kIPT = 5;
-constexpr int kSCAP = 4096;
+constexpr uint64_t kL2Bytes = 4u << 20;  // one XCD's L2
+
+// Probe workgroup: two share a CU's 160 KB of LDS.
+template <typename K, typename PS>
+constexpr int kPNT = sizeof(K) + sizeof(PS) == 8 ? 512 : 384;
 
 template <typename K, typename PB>
 struct HashTab {
-  static constexpr bool kHashed = true;
-  static constexpr bool kRuns = false;
+  static constexpr bool kWalk = true;
   using SlotT = Slot<K, PB>;
   using Index = uint64_t;  // a table may hold more than 2^32 slots
   const Slot<K, PB> *__restrict__ slots;
@@ -40,16 +41,19 @@ struct HashTab {
   __device__ __forceinline__ uint64_t home(K key) const {
     return fmix64(static_cast<uint64_t>(sext(key))) & mask;
   }
-  __device__ __forceinline__ uint64_t next(uint64_t i) const { return (i + 1) & mask; }
+  __device__ __forceinline__ uint64_t start(K key, bool &in) const {
+    in = true;
+    return home(key);
+  }
+  __device__ __forceinline__ uint64_t walk(uint64_t i, uint32_t steps) const { return line_walk<SlotT>(i, steps, mask); }
   __device__ __forceinline__ SlotT load(uint64_t i) const { return slots[i]; }
   template <class F>
   __device__ __forceinline__ void for_each(K key, F f) const {
-    uint64_t i = home(key);
-    for (;;) {
-      const Slot<K, PB> s = slots[i];
+    const uint64_t i = home(key);
+    for (uint32_t step = 0;; ++step) {
+      const Slot<K, PB> s = slots[walk(i, step)];
       if (s.rowid == kEmpty) break;
       if (s.key == key) f(s.rowid);
-      i = next(i);
     }
   }
 };
@@ -76,15 +80,15 @@ __global__ void k_hash_build(const K *__restrict__ keys, const PB *__restrict__ 
   const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
   for (uint64_t r = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; r < n; r += stride) {
     const K key = keys[r];
-    uint64_t i = fmix64(static_cast<uint64_t>(sext(key))) & mask;
+    const uint64_t home = fmix64(static_cast<uint64_t>(sext(key))) & mask;
     // The table has more slots than rows, so an empty slot is always found.
-    for (;;) {
+    for (uint32_t step = 0;; ++step) {
+      const uint64_t i = line_walk<Slot<K, PB>>(home, step, mask);
       if (atomicCAS(&slots[i].rowid, kEmpty, static_cast<uint32_t>(r)) == kEmpty) {
         slots[i].key = key;
         slots[i].pay = pay[r];
         break;
       }
-      i = (i + 1) & mask;
     }
   }
 }
@@ -127,9 +131,10 @@ __global__ void k_hash_build_keys(const K *__restrict__ keys, const PB *__restri
       atomicOr(reinterpret_cast<unsigned long long *>(flags), kFlagBuildOutOfRange);
       continue;
     }
-    uint64_t i = fmix64(static_cast<uint64_t>(sext(key))) & mask;
+    const uint64_t home = fmix64(static_cast<uint64_t>(sext(key))) & mask;
     // The table has more slots than rows, so an empty slot is always found.
-    for (;;) {
+    for (uint32_t step = 0;; ++step) {
+      const uint64_t i = line_walk<Slot<K, PB>>(home, step, mask);
       const W old = atomicCAS(reinterpret_cast<W *>(&slots[i].key), empty, static_cast<W>(key));
       if (old == empty) {
         slots[i].rowid = static_cast<uint32_t>(r);
@@ -137,7 +142,6 @@ __global__ void k_hash_build_keys(const K *__restrict__ keys, const PB *__restri
         break;
       }
       seen |= old == static_cast<W>(key);
-      i = (i + 1) & mask;
     }
   }
   if (seen) atomicOr(dup, 1u);
@@ -160,22 +164,27 @@ bool hash_sentinel(const JoinArgs &a, K *out) {
 }
 
 // Each workgroup streams a contiguous range of probe rows (an equal share of
-// whole sub-tiles).
-template <class Tab, typename K, typename PS>
-__global__ void __launch_bounds__(kNT) k_probe(Tab tab, const K *__restrict__ pk,
+// whole blocks), its waves taking blocks in turn.
+template <class Tab, typename K, typename PS, int kEager>
+__global__ void __launch_bounds__((kPNT<K, PS>)) k_probe(Tab tab, const K *__restrict__ pk,
                                                const PS *__restrict__ pp, uint64_t n, EmitOut o) {
-  __shared__ EmitLds<kNT, kSCAP> L;
-  uint64_t fill = 0;
-  uint64_t cs = 0;
+  __shared__ WaveLds<K, PS> L[kPNT<K, PS> / 64];
+  __shared__ WaveJoint<kPNT<K, PS> / 64> J;
   tab.init();
-  constexpr uint64_t sub = uint64_t(kNT) * kIPT;
+  constexpr uint64_t block = 64 * kWaveRows, sub = kPNT<K, PS> * kWaveRows;
+  const uint32_t w = threadIdx.x / 64;
   const uint64_t nsub = (n + sub - 1) / sub;
   const uint64_t per = (nsub + gridDim.x - 1) / gridDim.x;
   const uint64_t lo = blockIdx.x * per * sub;
   const uint64_t hi = lo + per * sub < n ? lo + per * sub : n;
-  probe_range<kNT, kIPT, kSCAP>(tab, pk, pp, static_cast<const uint32_t *>(nullptr), lo, hi, L, fill,
-                                o, cs);
-  finish(L, o, fill, cs);
+  WaveProbe<Tab, K, PS, kEager> p(tab, L[w], o);
+  p.template run<kPNT<K, PS> / 64>(pk, pp, nullptr, lo + w * block, hi, sub, &J);
+}
+
+// Workgroups of a CU by the LDS they take (160 KB).
+template <typename K, typename PS>
+constexpr int probe_per_cu() {
+  return static_cast<int>(163840 / (sizeof(WaveLds<K, PS>) * (kPNT<K, PS> / 64) + sizeof(WaveJoint<kPNT<K, PS> / 64>)));
 }
 
 unsigned grid_for(uint64_t work, uint64_t per_block, int per_cu) {
@@ -195,7 +204,7 @@ int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   if (!ws.base) return EIGER_OK;
   hipStream_t s = a.s;
   int rc;
-  if ((rc = fill_u64(reinterpret_cast<uint64_t *>(c), 4, 0, s))) return rc;
+  if ((rc = zero_counters(c, s))) return rc;
   if (a.nR == 0 || a.nS == 0) return EIGER_OK;
   if ((rc = fill_u32(dup, 1, 0, s))) return rc;
   HashTab<K, PB> tab{slots, nslots - 1, dup, false};
@@ -216,10 +225,18 @@ int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
     EIGER_LAUNCH("hash_unique", (k_hash_unique<K, PB>), dim3(grid_for(a.nR, 256 * 2, 8)), dim3(256), 0, s,
                  static_cast<const K *>(a.bk), a.nR, tab, dup);
   }
-  EmitOut o{a.ob, a.op, a.cap, &c->count, &c->checksum};
-  EIGER_LAUNCH("hash_probe", (k_probe<HashTab<K, PB>, K, PS>),
-               dim3(grid_for(a.nS, uint64_t(kNT) * kIPT, 4)), dim3(kNT), 0, s, tab,
-               static_cast<const K *>(a.pk), static_cast<const PS *>(a.pp), a.nS, o);
+  EmitOut o{a.ob, a.op, a.cap, &c->count, &c->checksum, c->stripe};
+  const dim3 grid(grid_for(a.nS, uint64_t(kPNT<K, PS>) * kWaveRows, probe_per_cu<K, PS>()));
+  const K *pk = static_cast<const K *>(a.pk);
+  const PS *pp = static_cast<const PS *>(a.pp);
+  // A table in an XCD's L2 is bound by the L1's fills, and loading two slots of
+  // every row costs more of them than it saves (2^27 probes of a 2 MiB table: one
+  // 0.97 ms, two 1.14); from larger ones the second slot comes with the first
+  // (33.5M probes of a 64 MiB table: one 0.82 ms, two 0.72; 2^26 of 32 MiB: 1.43 and 1.28).
+  if (nslots * sizeof(Slot<K, PB>) <= kL2Bytes)
+    EIGER_LAUNCH("hash_probe", (k_probe<HashTab<K, PB>, K, PS, 1>), grid, dim3(kPNT<K, PS>), 0, s, tab, pk, pp, a.nS, o);
+  else
+    EIGER_LAUNCH("hash_probe", (k_probe<HashTab<K, PB>, K, PS, 2>), grid, dim3(kPNT<K, PS>), 0, s, tab, pk, pp, a.nS, o);
   return EIGER_OK;
 }
 

@@ -836,7 +836,7 @@ int radix_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   if (!ws.base) return EIGER_OK;
   hipStream_t s = a.s;
   int rc;
-  if ((rc = fill_u64(reinterpret_cast<uint64_t *>(c), 4, 0, s))) return rc;
+  if ((rc = zero_counters(c, s))) return rc;
   if (a.nR == 0 || a.nS == 0) return EIGER_OK;
   Side<K, PB> fr;
   Side<K, PS> fs;
@@ -1061,7 +1061,7 @@ int radix_wide_impl(const JoinArgs &a, const WordCols &colsR, const WordCols &co
   if (!ws.base) return EIGER_OK;
   hipStream_t s = a.s;
   int rc;
-  if ((rc = fill_u64(reinterpret_cast<uint64_t *>(c), 4, 0, s))) return rc;
+  if ((rc = zero_counters(c, s))) return rc;
   if (a.nR == 0 || a.nS == 0) return EIGER_OK;
   Lanes lr{}, ls{};
   lr.n = colsR.n;
@@ -1303,7 +1303,7 @@ int radix_cache_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   if (!ws.base) return EIGER_OK;
   hipStream_t s = a.s;
   int rc;
-  if ((rc = fill_u64(reinterpret_cast<uint64_t *>(c), 4, 0, s))) return rc;
+  if ((rc = zero_counters(c, s))) return rc;
   if (a.nR == 0 || a.nS == 0) return EIGER_OK;
   const K *bk = static_cast<const K *>(a.bk);
   // build side: partition sizes only (histogram + scan), no scatter

@@ -159,7 +159,7 @@ int smj_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr, uint64_t span
   if (!ws.base) return EIGER_OK;
   hipStream_t s = a.s;
   int rc;
-  if ((rc = fill_u64(reinterpret_cast<uint64_t *>(c), 4, 0, s))) return rc;
+  if ((rc = zero_counters(c, s))) return rc;
   if (a.nR == 0 || a.nS == 0) return EIGER_OK;
   const uint64_t min = static_cast<uint64_t>(a.plan.build_min);
   EIGER_LAUNCH("smj_encode", (k_smj_encode<K, U>), dim3(smj_grid(a.nR, 256 * 4, 8)), dim3(256), 0, s,

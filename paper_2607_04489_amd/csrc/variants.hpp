@@ -15,13 +15,31 @@ struct JoinArgs {
   hipStream_t s;
 };
 
-// Device words every variant leaves behind for the host to read.
+// Part of a join's totals on a cache line of its own: atomics on one address run
+// at 10 ns each, so that workgroups spread theirs over kStripes lines.
+constexpr int kStripes = 8;
+struct alignas(128) JoinStripe {
+  uint64_t checksum, count;
+};
+
+// Device words every variant leaves behind for the host to read: the totals are
+// count and checksum plus all the stripes'.
 struct JoinCounters {
   uint64_t count;     // pairs found (may exceed cap)
   uint64_t checksum;  // sum of payload products mod 2^64
   uint64_t flags;     // kFlag* bits
   uint64_t pad;
+  JoinStripe stripe[kStripes];
 };
+inline int zero_counters(JoinCounters *c, hipStream_t s) {
+  return fill_u64(reinterpret_cast<uint64_t *>(c), sizeof(JoinCounters) / 8, 0, s);
+}
+inline void add_stripes(JoinCounters &host) {
+  for (const JoinStripe &t : host.stripe) {
+    host.count += t.count;
+    host.checksum += t.checksum;
+  }
+}
 
 constexpr uint64_t kFlagBuildOutOfRange = 1;  // DIRECT: a build key outside [build_min, build_max]
 

@@ -36,6 +36,32 @@ def test_sparse_unique64(gpu, spec):
     assert_exact(inp, run(inp, spec))
 
 
+# 131,071 and 131,072 build rows at load factor 0.5: a table of 4 MiB of 16-byte slots, whose
+# probe loads one slot of a row at first, and one of 8 MiB, whose probe loads two (32-byte
+# slots: from 65,536 rows on).
+@pytest.mark.parametrize("n_build", [65535, 65536, 131071, 131072])
+@pytest.mark.parametrize("key,pay", [(torch.int32, torch.int32), (torch.int32, torch.int64), (torch.int64, torch.int64)])
+@pytest.mark.parametrize("shape", ["distinct", "repeated"])
+def test_hash_probe_paths(gpu, n_build, key, pay, shape):
+    """Distinct keys (one match per row) and repeated ones (keys of 3 rows, and two of
+    300, so that a block of rows overflows a wave's stage), probe rows one short of and
+    beyond whole blocks, pairs and count-only."""
+    g = torch.Generator().manual_seed(n_build)
+    for n_probe in (3 * 4096 - 1, 70001):
+        i = torch.arange(n_build)
+        keys = (i if shape == "distinct" else torch.where(i < 600, i % 2, i // 3)) * 7919 - 5000
+        keys = keys[torch.randperm(n_build, generator=g)]
+        pk = torch.randint(0, n_build + n_build // 4, (n_probe,), generator=g) * 7919 - 5000
+        if shape == "repeated":
+            pk[1000:1700] = -5000  # 700 rows of 300 matches each, together
+        inp = synth.JoinInput("hash_paths", keys.to(key).to(gpu), torch.randint(-999, 999, (n_build,), generator=g).to(pay).to(gpu),
+                              pk.to(key).to(gpu), torch.randint(-999, 999, (n_probe,), generator=g).to(pay).to(gpu))
+        res = run(inp, ("hash", eg.GLOBAL_HASH, 0, 0, 0.5))
+        assert_exact(inp, res)
+        cnt = run(inp, ("hash", eg.GLOBAL_HASH, 0, 0, 0.5), count_only=True)
+        assert (cnt.count, cnt.checksum) == (res.count, res.checksum)
+
+
 def test_direct_refuses_sparse_range(gpu):
     inp = synth.sparse_unique64(seed=4, n_build=1000, n_probe=1000, device=gpu)
     with pytest.raises(eg.EigerError) as e:
