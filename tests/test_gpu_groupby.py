@@ -60,6 +60,34 @@ def test_groupby_partition_tiles(gpu, key, val, nv, n):
     check(keys, vals, eg.groupby(keys, vals, forced(keys, eg.GB_PARTITION, 9)))
 
 
+@pytest.mark.parametrize("vals", [(), (torch.int32,), (torch.int64,), (torch.int32, torch.int32), (torch.int32, torch.int64),
+                                  (torch.int64, torch.int32), (torch.int64, torch.int64)],
+                         ids=lambda v: "_".join(str(t)[6:] for t in v) or "count")
+@pytest.mark.parametrize("groups", [1, 16, 17, 128, 600, 1024])
+@pytest.mark.parametrize("key", [torch.int32, torch.int64])
+def test_groupby_hash_shapes(gpu, key, groups, vals):
+    """LDS tables of 64 to 2,048 slots with 32 to one accumulator a slot, every
+    combination of value widths, a ragged last step, columns that start one row in."""
+    keys, _ = synth.groupby_input(seed=groups, n=150_002, groups=groups, key_dtype=key, n_vals=0, device=gpu)
+    cols = [synth.groupby_input(seed=groups + c, n=150_002, groups=1, n_vals=1, val_dtype=t, device=gpu)[1][0]
+            for c, t in enumerate(vals)]
+    keys, cols = keys[1:], [c[1:] for c in cols]
+    check(keys, cols, eg.groupby(keys, cols, forced(keys, eg.GB_HASH)))
+
+
+@pytest.mark.parametrize("value", [-(1 << 31), (1 << 31) - 1, -1])
+def test_groupby_packed_sums_at_their_bounds(gpu, value):
+    """Workgroups of more rows than a packed count holds, one group, the values at
+    the ends of int32: exact sums known in closed form."""
+    n = 768 * 65536 + 5
+    keys = torch.full((n,), 3, dtype=torch.int32, device=gpu)
+    keys[n // 2] = 4
+    vals = torch.full((n,), value, dtype=torch.int32, device=gpu)
+    res = eg.groupby(keys, [vals, vals], forced(keys, eg.GB_HASH))
+    got = {int(k): (int(c), int(a), int(b)) for k, c, a, b in zip(res.keys, res.counts, *res.sums)}
+    assert got == {3: (n - 1, (n - 1) * value, (n - 1) * value), 4: (1, value, value)}
+
+
 def test_groupby_rule_follows_the_estimate(gpu):
     small, sv = synth.groupby_input(seed=1, n=2_000_000, groups=600, device=gpu)
     big, bv = synth.groupby_input(seed=2, n=2_000_000, groups=1_500_000, device=gpu)
