@@ -199,6 +199,19 @@ int run_variant(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
 
 int run_join_variant(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) { return run_variant(a, ws, ctr); }
 
+int read_counters(int32_t variant, const JoinCounters *ctr, JoinCounters *host, hipStream_t s) {
+  HashCounters h{};
+  const size_t bytes = variant == EIGER_GLOBAL_HASH ? sizeof(HashCounters) : sizeof(JoinCounters);
+  EIGER_HIP(hipMemcpyAsync(&h, ctr, bytes, hipMemcpyDeviceToHost, s));
+  EIGER_HIP(hipStreamSynchronize(s));
+  *host = h.total;
+  for (const JoinStripe &t : h.stripe) {
+    host->count += t.count;
+    host->checksum += t.checksum;
+  }
+  return EIGER_OK;
+}
+
 int check_join_inputs_public(const eiger_column &bk, const eiger_column &bp, const eiger_column &pk,
                              const eiger_column &pp, const eiger_plan_t *plan) {
   return check_join_inputs(bk, bp, pk, pp, plan);
@@ -431,9 +444,7 @@ int join_checked(const eiger_column &bk, const eiger_column &bp, const eiger_col
   JoinCounters *ctr = nullptr;
   if ((rc = run_variant(a, ws, &ctr))) return rc;
   JoinCounters host{};
-  EIGER_HIP(hipMemcpyAsync(&host, ctr, sizeof(host), hipMemcpyDeviceToHost, a.s));
-  EIGER_HIP(hipStreamSynchronize(a.s));
-  add_stripes(host);
+  if ((rc = read_counters(a.plan.variant, ctr, &host, a.s))) return rc;
   if (host.flags & kFlagBuildOutOfRange)
     return fail(EIGER_ERR_INVALID_ARG, "eiger_join: a build key lies outside the plan's [build_min, build_max]");
   *out_count = static_cast<int64_t>(host.count);

@@ -197,14 +197,15 @@ unsigned grid_for(uint64_t work, uint64_t per_block, int per_cu) {
 template <typename K, typename PB, typename PS>
 int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   const uint64_t nslots = hash_slots(a.nR, a.plan.load_factor);
-  JoinCounters *c = ws.take<JoinCounters>(1);
+  HashCounters *hc = ws.take<HashCounters>(1);
+  JoinCounters *c = &hc->total;
   uint32_t *dup = ws.take<uint32_t>(1);
   Slot<K, PB> *slots = ws.take<Slot<K, PB>>(nslots);
   *ctr = c;
   if (!ws.base) return EIGER_OK;
   hipStream_t s = a.s;
   int rc;
-  if ((rc = zero_counters(c, s))) return rc;
+  if ((rc = fill_u64(reinterpret_cast<uint64_t *>(hc), sizeof(HashCounters) / 8, 0, s))) return rc;
   if (a.nR == 0 || a.nS == 0) return EIGER_OK;
   if ((rc = fill_u32(dup, 1, 0, s))) return rc;
   HashTab<K, PB> tab{slots, nslots - 1, dup, false};
@@ -225,7 +226,7 @@ int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
     EIGER_LAUNCH("hash_unique", (k_hash_unique<K, PB>), dim3(grid_for(a.nR, 256 * 2, 8)), dim3(256), 0, s,
                  static_cast<const K *>(a.bk), a.nR, tab, dup);
   }
-  EmitOut o{a.ob, a.op, a.cap, &c->count, &c->checksum, c->stripe};
+  EmitOut o{a.ob, a.op, a.cap, &c->count, &c->checksum, hc->stripe};
   const dim3 grid(grid_for(a.nS, uint64_t(kPNT<K, PS>) * kWaveRows, probe_per_cu<K, PS>()));
   const K *pk = static_cast<const K *>(a.pk);
   const PS *pp = static_cast<const PS *>(a.pp);

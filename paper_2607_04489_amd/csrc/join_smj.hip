@@ -147,14 +147,17 @@ int smj_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr, uint64_t span
   JoinCounters *c = ws.take<JoinCounters>(1);
   U *uR = ws.take<U>(a.nR), *uRs = ws.take<U>(a.nR);
   uint32_t *ridR = ws.take<uint32_t>(a.nR);
-  PB *payR = ws.take<PB>(a.nR);
   U *uS = ws.take<U>(a.nS), *uSs = ws.take<U>(a.nS);
   uint32_t *ridS = ws.take<uint32_t>(a.nS);
-  PS *payS = ws.take<PS>(a.nS);
-  // one region for both sorts (they run one after the other on the stream)
+  // one region for both sorts (they run one after the other on the stream); the
+  // gathered payloads, written after the sorts, lie in the same place
   Workspace probe_size(nullptr, 0);
   radix_sort_pairs(sizeof(U), nullptr, nullptr, std::max(a.nR, a.nS), bits, nullptr, nullptr, probe_size, nullptr);
+  Workspace pay = ws;
   char *sort_ws = ws.take<char>(probe_size.used + 256);
+  PB *payR = pay.take<PB>(a.nR);
+  PS *payS = pay.take<PS>(a.nS);
+  ws.used = std::max(ws.used, pay.used);
   *ctr = c;
   if (!ws.base) return EIGER_OK;
   hipStream_t s = a.s;

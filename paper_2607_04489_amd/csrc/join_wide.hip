@@ -269,9 +269,7 @@ extern "C" int eiger_join_wide(eiger_column build_keys, const eiger_column *buil
                  out_probe_rowid, ctr, want, gr, gp);
   }
   JoinCounters host{};
-  EIGER_HIP(hipMemcpyAsync(&host, ctr, sizeof(host), hipMemcpyDeviceToHost, s));
-  EIGER_HIP(hipStreamSynchronize(s));
-  add_stripes(host);
+  if ((rc = read_counters(plan->variant, ctr, &host, s))) return rc;
   if (host.flags & kFlagBuildOutOfRange)
     return fail(EIGER_ERR_INVALID_ARG, "eiger_join_wide: a build key lies outside the plan's [build_min, build_max]");
   *out_count = static_cast<int64_t>(host.count);

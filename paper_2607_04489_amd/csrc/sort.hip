@@ -36,15 +36,15 @@ static_assert(kSDigits == kHNT && kSDigits <= kSNT, "one thread per digit");
 // 4.63 ms, 10 3.77, 12 3.76, 16 4.00). Small inputs: 4,096 items, so that there are
 // workgroups for the chip.
 constexpr int kItemsSmall = 8;
-template <typename K, int NW>
+template <typename K>
 constexpr int items_large() {
-  return sizeof(K) == 8 ? 12 : (NW > 1 ? 16 : 20);
+  return sizeof(K) == 8 ? 12 : 20;
 }
 // Large tiles from this many of them on (two per CU).
 constexpr uint64_t kLargeTiles = 512;
-template <typename K, int NW>
+template <typename K>
 bool use_large(uint64_t n) {
-  return n >= kLargeTiles * kSNT * items_large<K, NW>();
+  return n >= kLargeTiles * kSNT * items_large<K>();
 }
 // Up to this many tiles the scatter's workgroups sum the count table's columns
 // themselves instead of three scan launches.
@@ -126,13 +126,13 @@ __global__ void __launch_bounds__(kHNT) k_sort_hist(const K *__restrict__ keys, 
 
 // 32-bit value lanes moved along with the keys. Lane w of row i is
 // src[w][i * stride[w]]; a NULL source lane means the row id i itself.
-constexpr int kSortLanes = 4;
 struct LanesIn {
-  const uint32_t *src[kSortLanes];
-  uint32_t stride[kSortLanes];
+  const uint32_t *src[kMaxLanes];
+  uint32_t stride[kMaxLanes];
+  int n;
 };
 struct LanesOut {
-  uint32_t *dst[kSortLanes];
+  uint32_t *dst[kMaxLanes];
 };
 
 // Stable ranks of a wave's items of one step among the wave's items so far:
@@ -205,7 +205,7 @@ __device__ __forceinline__ void item_fence(int j) {
 
 // One tile of a scatter pass. kFull: the tile has all its items. Uniform across
 // the workgroup (barriers).
-template <typename K, int NW, int kItems, typename D, bool kSelfScan, bool kFull>
+template <typename K, int kItems, typename D, bool kSelfScan, bool kFull>
 __device__ __forceinline__ void scatter_tile(ScatterLds<K, kItems, D::kStore> &L, const K *__restrict__ kin,
                                              const LanesIn &vin, uint64_t base, uint32_t in_tile, const D &dig, int bits,
                                              uint32_t tile, uint32_t ntiles, const uint32_t *__restrict__ offs,
@@ -290,7 +290,7 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<K, kItems, D::kStore> &L
       for (int j = 0; j < kItems; ++j) val[j] = has(first + j * 64) ? src[(first + j * 64) * st] : 0u;
     }
   };
-  if constexpr (NW > 0) load_lane(0);  // in flight while the keys go out
+  if (vin.n > 0) load_lane(0);  // in flight while the keys go out
   __syncthreads();
   uint32_t o[kItems];  // where tile position t + j * kSNT goes
 #pragma unroll
@@ -309,15 +309,14 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<K, kItems, D::kStore> &L
     }
     item_fence<8>(j);
   }
-#pragma unroll
-  for (int v = 0; v < NW; ++v) {
+  for (int v = 0; v < vin.n; ++v) {
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
       if (has(first + j * 64)) sv[(pos[j / 2] >> (j % 2 * 16)) & 0xFFFFu] = val[j];
       item_fence<8>(j);
     }
-    if (v + 1 < NW) load_lane(v + 1);
+    if (v + 1 < vin.n) load_lane(v + 1);
     __syncthreads();
     uint32_t *__restrict__ dst = vout.dst[v];
 #pragma unroll
@@ -340,7 +339,7 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<K, kItems, D::kStore> &L
 // addresses across tiles, and the registers spilled.
 // kSelfScan: `offs` holds the raw counts, tile-major, and each workgroup sums
 // the columns it needs; else the scanned counts, digit-major.
-template <typename K, int NW, int kItems, typename D, bool kSelfScan>
+template <typename K, int kItems, typename D, bool kSelfScan>
 __global__ void __launch_bounds__(kSNT, 4) k_sort_scatter(const K *__restrict__ kin, LanesIn vin, uint64_t n, D dig,
                                                           int bits, uint32_t ntiles, const uint32_t *__restrict__ offs,
                                                           K *__restrict__ kout, LanesOut vout) {
@@ -352,9 +351,9 @@ __global__ void __launch_bounds__(kSNT, 4) k_sort_scatter(const K *__restrict__ 
   if (tile >= ntiles) return;
   const uint64_t base = static_cast<uint64_t>(tile) * T;
   if (n - base >= T)
-    scatter_tile<K, NW, kItems, D, kSelfScan, true>(L, kin, vin, base, T, dig, bits, tile, ntiles, offs, kout, vout);
+    scatter_tile<K, kItems, D, kSelfScan, true>(L, kin, vin, base, T, dig, bits, tile, ntiles, offs, kout, vout);
   else
-    scatter_tile<K, NW, kItems, D, kSelfScan, false>(L, kin, vin, base, static_cast<uint32_t>(n - base), dig, bits,
+    scatter_tile<K, kItems, D, kSelfScan, false>(L, kin, vin, base, static_cast<uint32_t>(n - base), dig, bits,
                                                      tile, ntiles, offs, kout, vout);
 }
 
@@ -437,43 +436,47 @@ __global__ void __launch_bounds__(256) k_sort_copy(const K *__restrict__ kin, co
   }
 }
 
-// Count-table and temporaries of the passes over n items in tiles of T.
-template <typename K, int NW>
+// Count-table and temporaries of `passes` passes over n items in tiles of T.
+template <typename K>
 struct PassBufs {
   uint64_t ntiles;
   uint32_t *cnt;
   uint64_t *tmp, *total;
   K *k2;
-  uint32_t *v2[NW > 0 ? NW : 1];
+  uint32_t *v2[kMaxLanes];
 };
 
-template <typename K, int NW>
-PassBufs<K, NW> pass_bufs(Workspace &ws, uint64_t n, int T) {
-  PassBufs<K, NW> b{};
+template <typename K>
+PassBufs<K> pass_bufs(Workspace &ws, uint64_t n, int T, int lanes, int passes) {
+  PassBufs<K> b{};
   b.ntiles = (n + T - 1) / T;
   const uint64_t ncnt = b.ntiles * kSDigits;
   b.cnt = ws.take<uint32_t>(ncnt);
   b.tmp = ws.take<uint64_t>(scan_tmp_elems(ncnt));
   b.total = ws.take<uint64_t>(1);
-  b.k2 = ws.take<K>(n);
-  for (int v = 0; v < NW; ++v) b.v2[v] = ws.take<uint32_t>(n);
+  if (passes > 1) {
+    b.k2 = ws.take<K>(n);
+    for (int v = 0; v < lanes; ++v) b.v2[v] = ws.take<uint32_t>(n);
+  }
   return b;
 }
 
-// ceil(total_bits / digit_bits) stable passes of balanced digit widths, least
+int pass_count(int bits) { return (bits + kSDigitBits - 1) / kSDigitBits; }
+
+// pass_count(total_bits) stable passes of balanced digit widths, least
 // significant digit first, alternating between (kout, vout) and the
 // temporaries so that the last pass lands in (kout, vout). make(shift, mask)
 // gives the pass's digit functor.
-template <typename K, int NW, int kItems, typename MakeDigit>
-int lsd_passes(const K *kin, LanesIn vin, uint64_t n, int total_bits, int digit_bits, K *kout, LanesOut vout,
-               const PassBufs<K, NW> &b, MakeDigit make, hipStream_t s) {
+template <typename K, int kItems, typename MakeDigit>
+int lsd_passes(const K *kin, LanesIn vin, uint64_t n, int total_bits, K *kout, LanesOut vout, const PassBufs<K> &b,
+               MakeDigit make, hipStream_t s) {
   constexpr int T = kSNT * kItems;
-  const int passes = (total_bits + digit_bits - 1) / digit_bits;
+  const int passes = pass_count(total_bits);
   const unsigned hist_grid =
       static_cast<unsigned>(std::min<uint64_t>(b.ntiles, uint64_t(device_cu_count()) * kHistPerCu));
   const unsigned scat_grid = static_cast<unsigned>((b.ntiles + kXcds - 1) / kXcds * kXcds);
   const uint32_t nt = static_cast<uint32_t>(b.ntiles);
-  const bool self_scan = b.ntiles <= kSelfScanTiles;
+  const bool self_scan = kItems == kItemsSmall && b.ntiles <= kSelfScanTiles;
   int shift = 0;
   const K *src_k = kin;
   LanesIn src_v = vin;
@@ -482,26 +485,28 @@ int lsd_passes(const K *kin, LanesIn vin, uint64_t n, int total_bits, int digit_
     const bool to_out = ((passes - 1 - p) % 2) == 0;
     K *dk = to_out ? kout : b.k2;
     LanesOut dv{};
-    for (int v = 0; v < NW; ++v) dv.dst[v] = to_out ? vout.dst[v] : b.v2[v];
+    for (int v = 0; v < vin.n; ++v) dv.dst[v] = to_out ? vout.dst[v] : b.v2[v];
     const auto dig = make(shift, (1u << bits) - 1u);
     using D = std::remove_const_t<decltype(dig)>;
     const bool vec = reinterpret_cast<uintptr_t>(src_k) % 16 == 0;
 #define EIGER_HIST(VEC, TM)                                                                                        \
   EIGER_LAUNCH("sort_hist", (k_sort_hist<K, T, D, VEC, TM>), dim3(hist_grid), dim3(kHNT), 0, s, src_k, n, dig, nt, b.cnt)
     if (self_scan) {
-      if (vec) EIGER_HIST(true, true); else EIGER_HIST(false, true);
-      EIGER_LAUNCH("sort_scatter", (k_sort_scatter<K, NW, kItems, D, true>), dim3(scat_grid), dim3(kSNT), 0, s, src_k,
-                   src_v, n, dig, bits, nt, b.cnt, dk, dv);
+      if constexpr (kItems == kItemsSmall) {  // large tiles are never that few
+        if (vec) EIGER_HIST(true, true); else EIGER_HIST(false, true);
+        EIGER_LAUNCH("sort_scatter", (k_sort_scatter<K, kItems, D, true>), dim3(scat_grid), dim3(kSNT), 0, s, src_k,
+                     src_v, n, dig, bits, nt, b.cnt, dk, dv);
+      }
     } else {
       if (vec) EIGER_HIST(true, false); else EIGER_HIST(false, false);
       int rc = exclusive_scan_u32(b.cnt, b.cnt, (static_cast<uint64_t>(dig.mask) + 1) * b.ntiles, b.tmp, b.total, s);
       if (rc) return rc;
-      EIGER_LAUNCH("sort_scatter", (k_sort_scatter<K, NW, kItems, D, false>), dim3(scat_grid), dim3(kSNT), 0, s, src_k,
+      EIGER_LAUNCH("sort_scatter", (k_sort_scatter<K, kItems, D, false>), dim3(scat_grid), dim3(kSNT), 0, s, src_k,
                    src_v, n, dig, bits, nt, b.cnt, dk, dv);
     }
 #undef EIGER_HIST
     src_k = dk;
-    for (int v = 0; v < NW; ++v) {
+    for (int v = 0; v < vin.n; ++v) {
       src_v.src[v] = dv.dst[v];
       src_v.stride[v] = 1;
     }
@@ -520,11 +525,10 @@ int sort_block(const K *kin, const uint32_t *vin, uint64_t n, int key_bits, K *k
 template <typename K>
 int sort_impl(const K *kin, const uint32_t *vin, uint64_t n, int key_bits, K *kout, uint32_t *vout, Workspace &ws,
               hipStream_t s) {
-  const bool large = use_large<K, 1>(n);
-  const PassBufs<K, 1> b = pass_bufs<K, 1>(ws, n, kSNT * (large ? items_large<K, 1>() : kItemsSmall));
+  const bool large = use_large<K>(n);
+  const PassBufs<K> b = pass_bufs<K>(ws, n, kSNT * (large ? items_large<K>() : kItemsSmall), 1, 2);
   if (!ws.base || n == 0) return EIGER_OK;
-  const int passes = (key_bits + kSDigitBits - 1) / kSDigitBits;
-  if (passes == 0 || n == 1) {
+  if (key_bits == 0 || n == 1) {
     const unsigned grid = static_cast<unsigned>(std::min<uint64_t>((n + 255) / 256, 4096));
     EIGER_LAUNCH("sort_copy", k_sort_copy<K>, dim3(grid), dim3(256), 0, s, kin, vin, n, kout, vout);
     return EIGER_OK;
@@ -535,11 +539,12 @@ int sort_impl(const K *kin, const uint32_t *vin, uint64_t n, int key_bits, K *ko
   LanesIn in{};
   in.src[0] = vin;
   in.stride[0] = 1;
+  in.n = 1;
   LanesOut out{};
   out.dst[0] = vout;
   const auto make = [](int shift, uint32_t mask) { return KeyDigit<K>{shift, mask}; };
-  if (large) return lsd_passes<K, 1, items_large<K, 1>()>(kin, in, n, key_bits, kSDigitBits, kout, out, b, make, s);
-  return lsd_passes<K, 1, kItemsSmall>(kin, in, n, key_bits, kSDigitBits, kout, out, b, make, s);
+  if (large) return lsd_passes<K, items_large<K>()>(kin, in, n, key_bits, kout, out, b, make, s);
+  return lsd_passes<K, kItemsSmall>(kin, in, n, key_bits, kout, out, b, make, s);
 }
 
 // Partition bounds: off[p] = first position whose partition id is >= p (the
@@ -561,58 +566,77 @@ __global__ void __launch_bounds__(256) k_part_bounds(const K *__restrict__ keys,
   }
 }
 
-template <typename K, int NW>
-int partition_impl(const K *keys, uint64_t n, const PartLanes &cols, int bits, Workspace &ws, PartitionOut *out,
-                   hipStream_t s, bool run) {
-  const bool large = use_large<K, NW>(n);
-  const uint32_t F = 1u << bits;
-  K *ok = ws.take<K>(n ? n : 1);
-  LanesOut ov{};
-  for (int v = 0; v < NW; ++v) ov.dst[v] = ws.take<uint32_t>(n ? n : 1);
-  uint32_t *off = ws.take<uint32_t>(uint64_t(F) + 1);
-  const PassBufs<K, NW> b = pass_bufs<K, NW>(ws, n, kSNT * (large ? items_large<K, NW>() : kItemsSmall));
-  out->keys = ok;
-  for (int v = 0; v < kSortLanes; ++v) out->words[v] = v < NW ? ov.dst[v] : nullptr;
-  out->off = off;
-  if (!ws.base || !run) return EIGER_OK;
-  if (n > 0) {
-    LanesIn in{};
-    for (int v = 0; v < NW; ++v) {
-      in.src[v] = cols.src[v];
-      in.stride[v] = cols.stride[v];
-    }
-    const int top = 64 - bits;
-    const auto make = [top](int shift, uint32_t mask) { return PartDigit<K>{top, shift, mask}; };
-    const int rc = large ? lsd_passes<K, NW, items_large<K, NW>()>(keys, in, n, bits, kSDigitBits, ok, ov, b, make, s)
-                         : lsd_passes<K, NW, kItemsSmall>(keys, in, n, bits, kSDigitBits, ok, ov, b, make, s);
-    if (rc) return rc;
-  }
-  EIGER_LAUNCH("part_bounds", k_part_bounds<K>, dim3(static_cast<unsigned>(std::min<uint64_t>((F + 256) / 256, 1024))),
-               dim3(256), 0, s, ok, n, bits, F, off);
-  return EIGER_OK;
+template <typename K>
+void partition_results(uint64_t n, const PartLanes &cols, int bits, Workspace &ws, PartitionOut *out) {
+  *out = PartitionOut{};
+  out->keys = ws.take<K>(n ? n : 1);
+  for (int v = 0; v < cols.n; ++v) out->words[v] = ws.take<uint32_t>(n ? n : 1);
+  out->off = ws.take<uint32_t>((uint64_t(1) << bits) + 1);
 }
 
 template <typename K>
-int partition_lanes(const K *keys, uint64_t n, const PartLanes &cols, int bits, Workspace &ws, PartitionOut *out,
-                    hipStream_t s, bool run) {
-  switch (cols.n) {
-    case 0: return partition_impl<K, 0>(keys, n, cols, bits, ws, out, s, run);
-    case 1: return partition_impl<K, 1>(keys, n, cols, bits, ws, out, s, run);
-    case 2: return partition_impl<K, 2>(keys, n, cols, bits, ws, out, s, run);
-    case 3: return partition_impl<K, 3>(keys, n, cols, bits, ws, out, s, run);
-    default: return partition_impl<K, 4>(keys, n, cols, bits, ws, out, s, run);
+PassBufs<K> partition_temps(uint64_t n, const PartLanes &cols, int bits, Workspace &ws) {
+  return pass_bufs<K>(ws, n, kSNT * (use_large<K>(n) ? items_large<K>() : kItemsSmall), cols.n, pass_count(bits));
+}
+
+template <typename K>
+int partition_run(const K *keys, uint64_t n, const PartLanes &cols, int bits, Workspace &ws, const PartitionOut &out,
+                  hipStream_t s) {
+  const PassBufs<K> b = partition_temps<K>(n, cols, bits, ws);
+  const uint32_t F = 1u << bits;
+  K *ok = static_cast<K *>(out.keys);
+  if (n > 0) {
+    LanesIn in{};
+    LanesOut ov{};
+    in.n = cols.n;
+    for (int v = 0; v < cols.n; ++v) {
+      in.src[v] = cols.src[v];
+      in.stride[v] = cols.stride[v];
+      ov.dst[v] = out.words[v];
+    }
+    const int top = 64 - bits;
+    const auto make = [top](int shift, uint32_t mask) { return PartDigit<K>{top, shift, mask}; };
+    const int rc = use_large<K>(n) ? lsd_passes<K, items_large<K>()>(keys, in, n, bits, ok, ov, b, make, s)
+                                   : lsd_passes<K, kItemsSmall>(keys, in, n, bits, ok, ov, b, make, s);
+    if (rc) return rc;
   }
+  EIGER_LAUNCH("part_bounds", k_part_bounds<K>, dim3(static_cast<unsigned>(std::min<uint64_t>((F + 256) / 256, 1024))),
+               dim3(256), 0, s, ok, n, bits, F, out.off);
+  return EIGER_OK;
 }
 
 }  // namespace
 
+int radix_partition_results(int key_bytes, uint64_t n, const PartLanes &cols, int bits, Workspace &ws,
+                            PartitionOut *out) {
+  if (bits < 1 || bits > 24 || cols.n < 0 || cols.n > kMaxLanes)
+    return fail(EIGER_ERR_INVALID_ARG, "radix partition: bits in [1, 24], at most 9 lanes");
+  if (key_bytes == 8)
+    partition_results<int64_t>(n, cols, bits, ws, out);
+  else
+    partition_results<int32_t>(n, cols, bits, ws, out);
+  return EIGER_OK;
+}
+
+void radix_partition_temps(int key_bytes, uint64_t n, const PartLanes &cols, int bits, Workspace &ws) {
+  if (key_bytes == 8)
+    partition_temps<int64_t>(n, cols, bits, ws);
+  else
+    partition_temps<int32_t>(n, cols, bits, ws);
+}
+
+int radix_partition_run(int key_bytes, const void *keys, uint64_t n, const PartLanes &cols, int bits, Workspace &ws,
+                        const PartitionOut &out, hipStream_t s) {
+  if (key_bytes == 8) return partition_run<int64_t>(static_cast<const int64_t *>(keys), n, cols, bits, ws, out, s);
+  return partition_run<int32_t>(static_cast<const int32_t *>(keys), n, cols, bits, ws, out, s);
+}
+
 int radix_partition_lanes(int key_bytes, const void *keys, uint64_t n, const PartLanes &cols, int bits, Workspace &ws,
                           PartitionOut *out, hipStream_t s, bool run) {
-  if (bits < 1 || bits > 24 || cols.n < 0 || cols.n > kSortLanes)
-    return fail(EIGER_ERR_INVALID_ARG, "radix partition: bits in [1, 24], at most 4 lanes");
-  if (key_bytes == 8)
-    return partition_lanes<int64_t>(static_cast<const int64_t *>(keys), n, cols, bits, ws, out, s, run);
-  return partition_lanes<int32_t>(static_cast<const int32_t *>(keys), n, cols, bits, ws, out, s, run);
+  if (int rc = radix_partition_results(key_bytes, n, cols, bits, ws, out)) return rc;
+  if (ws.base && run) return radix_partition_run(key_bytes, keys, n, cols, bits, ws, *out, s);
+  radix_partition_temps(key_bytes, n, cols, bits, ws);
+  return EIGER_OK;
 }
 
 int radix_sort_pairs(int key_bytes, const void *kin, const uint32_t *vin, uint64_t n, int key_bits, void *kout,

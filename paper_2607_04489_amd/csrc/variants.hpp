@@ -15,31 +15,30 @@ struct JoinArgs {
   hipStream_t s;
 };
 
-// Part of a join's totals on a cache line of its own: atomics on one address run
-// at 10 ns each, so that workgroups spread theirs over kStripes lines.
-constexpr int kStripes = 8;
-struct alignas(128) JoinStripe {
-  uint64_t checksum, count;
-};
-
-// Device words every variant leaves behind for the host to read: the totals are
-// count and checksum plus all the stripes'.
+// Device words every variant leaves behind for the host to read.
 struct JoinCounters {
   uint64_t count;     // pairs found (may exceed cap)
   uint64_t checksum;  // sum of payload products mod 2^64
   uint64_t flags;     // kFlag* bits
   uint64_t pad;
-  JoinStripe stripe[kStripes];
 };
 inline int zero_counters(JoinCounters *c, hipStream_t s) {
   return fill_u64(reinterpret_cast<uint64_t *>(c), sizeof(JoinCounters) / 8, 0, s);
 }
-inline void add_stripes(JoinCounters &host) {
-  for (const JoinStripe &t : host.stripe) {
-    host.count += t.count;
-    host.checksum += t.checksum;
-  }
-}
+
+// Part of a join's totals on a cache line of its own: atomics on one address run
+// at 10 ns each, so that GLOBAL_HASH's workgroups spread theirs over kStripes
+// lines. Its totals are count and checksum plus all the stripes'.
+constexpr int kStripes = 8;
+struct alignas(128) JoinStripe {
+  uint64_t checksum, count;
+};
+struct HashCounters {
+  JoinCounters total;
+  JoinStripe stripe[kStripes];
+};
+// The counters of a join of `variant`, totalled; waits for the stream (abi.hip).
+int read_counters(int32_t variant, const JoinCounters *ctr, JoinCounters *host, hipStream_t s);
 
 constexpr uint64_t kFlagBuildOutOfRange = 1;  // DIRECT: a build key outside [build_min, build_max]
 
