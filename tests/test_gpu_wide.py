@@ -63,6 +63,18 @@ def test_wide_paper_shape(gpu, plan_spec, match):
         check_wide(inp, inp.meta["build_cols"], inp.meta["probe_cols"], res)
 
 
+@pytest.mark.parametrize("n_probe", [1, 2, 3, 4, 5, 1023, 1026])
+def test_wide_ragged_results(gpu, n_probe):
+    """Results whose last group of four rows is short, columns of both widths, gathered
+    from the caller's columns and from the partitioned ones."""
+    inp = synth.wide_join(seed=n_probe, n_build=701, n_probe=n_probe, match_per_mille=1000, device=gpu)
+    b, s = mixed_cols(inp, torch.Generator().manual_seed(n_probe))
+    b, s = [c.to(gpu) for c in b], [c.to(gpu) for c in s]
+    plan = forced_plan(inp, ("radix", eg.RADIX, 6, 1, 0.5))
+    for mat in (eg.MAT_GFUR, eg.MAT_GFTR):
+        check_wide(inp, b, s, eg.join_wide(inp.build_keys, b, inp.probe_keys, s, plan, mat))
+
+
 @pytest.mark.parametrize("plan_spec", [p for p in PLANS if p[1] != eg.DIRECT], ids=[p[0] for p in PLANS if p[1] != eg.DIRECT])
 def test_wide_int64_keys_mixed_columns_duplicates(gpu, plan_spec):
     """int64 keys over a narrow range (duplicates on both sides), mixed
