@@ -283,13 +283,14 @@ __device__ __forceinline__ void agg_rows(AggLds<NV, W0> &L, const AggShape &h, c
       bool any = false;
 #pragma unroll
       for (int q = 0; q < kARows; ++q) {
-        if (at[q] != k[q] && at[q] != g.sentinel) {
-          slot[q] = (slot[q] + 1) & (h.slots - 1);
-          at[q] = __atomic_load_n(&L.key[slot[q]], __ATOMIC_RELAXED);
-          any = true;
-        }
+        const bool on = at[q] != k[q] && at[q] != g.sentinel;
+        slot[q] = on ? (slot[q] + 1) & (h.slots - 1) : slot[q];
+        any |= on;
       }
       if (!any) break;
+      // (unconditional: a read under a condition is waited for on the spot)
+#pragma unroll
+      for (int q = 0; q < kARows; ++q) at[q] = __atomic_load_n(&L.key[slot[q]], __ATOMIC_RELAXED);
     }
 #pragma unroll
     for (int q = 0; q < kARows; ++q) {
