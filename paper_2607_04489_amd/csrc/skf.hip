@@ -9,13 +9,15 @@
 //   3. the pairs are radix-sorted by value (width of max - min);
 //   4. scatter: the slot of the i-th smallest value receives code i;
 //   5. gather: each row reads the code of its slot -- done inside the fusion
-//      kernel, so codes are never stored on their own.
+//      kernel, so codes are never stored on their own. Where the fusion looks a few
+//      values up by themselves, step 1 records no slots.
 // The slot id plays the role of the leader's row id as group id: it indexes an
 // array of table size instead of one of column size, which stays in L2.
 //
 // Fusion: one kernel reads every key column (frame-of-reference keys) or slot
 // ids (dictionary keys) of a row, forms each code, complements it within its
 // width for a descending key, and ORs it into place: 4- or 8-byte output.
+#include <algorithm>
 #include <cmath>
 
 #include "common.hpp"
@@ -197,6 +199,87 @@ __global__ void __launch_bounds__(kDeNT) k_de_insert_lds(Rows<K> rows, DeTable t
   }
 }
 
+// Step 1 where no row's slot is needed (the fusion looks the values up itself):
+// only values new to the workgroup reach the global table. Rows are read 16 bytes
+// at a time and their walks through the LDS table step together (2^28 4-byte rows, 256
+// values: 0.34 ms; with a slot per row found and written, 1.06; 16 rows a thread 0.37).
+constexpr int kDsNT = 512;
+constexpr int kDsRows = 8;
+constexpr uint32_t kDsSlots = 4096;
+
+__device__ __forceinline__ uint32_t small_hash(unsigned long long k, uint32_t shift) {
+  uint32_t x = static_cast<uint32_t>(k) ^ static_cast<uint32_t>(k >> 32) * 0x85ebca6bu;
+  x ^= x >> 16;
+  return (x * 0x9e3779b1u) >> shift;
+}
+
+// (at least 16 and no more than 2^31 slots)
+inline uint32_t hash_shift(uint32_t slots) { return 32u - static_cast<uint32_t>(__builtin_ctz(slots)); }
+
+template <typename K>
+__global__ void __launch_bounds__(kDsNT) k_de_discover(const K *__restrict__ keys, uint64_t n, DeTable t,
+                                                       uint32_t slots, uint32_t shift) {
+  __shared__ unsigned long long lk[kDsSlots];
+  for (uint32_t j = threadIdx.x; j < slots; j += kDsNT) lk[j] = kDeEmpty;
+  __syncthreads();
+  constexpr uint64_t span = uint64_t(kDsNT) * kDsRows;
+  constexpr int V = 16 / static_cast<int>(sizeof(K));
+  for (uint64_t base = uint64_t(blockIdx.x) * span; base < n; base += uint64_t(gridDim.x) * span) {
+    unsigned long long k[kDsRows], at[kDsRows];
+    uint32_t h[kDsRows];
+    if (base + span <= n) {
+      K v[kDsRows];
+#pragma unroll
+      for (int q = 0; q < kDsRows; q += V)
+        *reinterpret_cast<uint4 *>(v + q) = *reinterpret_cast<const uint4 *>(keys + base + (q / V * kDsNT + threadIdx.x) * V);
+#pragma unroll
+      for (int q = 0; q < kDsRows; ++q) k[q] = static_cast<unsigned long long>(static_cast<int64_t>(v[q]));
+    } else {
+#pragma unroll
+      for (int q = 0; q < kDsRows; ++q) {  // the last row again for those past it
+        const uint64_t i = std::min(base + q * kDsNT + threadIdx.x, n - 1);
+        k[q] = static_cast<unsigned long long>(static_cast<int64_t>(keys[i]));
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < kDsRows; ++q) {
+      h[q] = small_hash(k[q], shift);
+      at[q] = __atomic_load_n(&lk[h[q]], __ATOMIC_RELAXED);
+    }
+    for (uint32_t step = 1; step < kDeLdsProbe; ++step) {
+      bool any = false;
+#pragma unroll
+      for (int q = 0; q < kDsRows; ++q) {
+        const bool on = at[q] != k[q] && at[q] != kDeEmpty;
+        h[q] = on ? (h[q] + 1) & (slots - 1) : h[q];
+        any |= on;
+      }
+      if (!any) break;
+      // (unconditional: a read under a condition is waited for on the spot)
+#pragma unroll
+      for (int q = 0; q < kDsRows; ++q) at[q] = __atomic_load_n(&lk[h[q]], __ATOMIC_RELAXED);
+    }
+#pragma unroll
+    for (int q = 0; q < kDsRows; ++q) {
+      if (at[q] == k[q] && k[q] != kDeEmpty) continue;
+      // new to the workgroup (or INT64_MIN, which has its own flag): enter it here,
+      // and in the global table if this thread entered it; without a place here, there
+      bool mine = true;
+      if (k[q] != kDeEmpty) {
+        for (uint32_t step = 0; step < kDeLdsProbe; ++step) {
+          const unsigned long long old = atomicCAS(&lk[h[q]], kDeEmpty, k[q]);
+          if (old == kDeEmpty || old == k[q]) {
+            mine = old == kDeEmpty;
+            break;
+          }
+          h[q] = (h[q] + 1) & (slots - 1);
+        }
+      }
+      if (mine) (void)de_slot(t, k[q]);
+    }
+  }
+}
+
 // Compacts occupied slots into (key - base, slot) pairs; one atomic per wave.
 __global__ void __launch_bounds__(kDeNT) k_de_retrieve(DeTable t, uint64_t base, unsigned long long *__restrict__ ukey,
                                                        uint32_t *__restrict__ uslot) {
@@ -257,7 +340,10 @@ struct FuseKey {
   uint64_t flip;                 // all-ones over the width for a descending key, else 0
   int32_t wide;                  // 8-byte key column
   int32_t dict;
-  uint32_t slots1;               // DICT: entries of code_of_slot (table slots + 1)
+  const unsigned long long *skey;  // DICT looked up by value: the sorted values less vbase, code = position
+  uint64_t vbase;
+  uint32_t ndv;
+  uint32_t lds_slots, lds_shift, lds_at;  // its table in LDS (in 8-byte words); 0 slots: through loc
   int32_t bits;
   int32_t shift;
 };
@@ -418,37 +504,93 @@ struct SkfLayout {
 // Fusion over 16-byte accesses: each thread takes groups of four consecutive
 // rows, reads each key column (or dictionary slot ids) four rows at a time and
 // writes four fused keys at once. Used when every column is one array with
-// 16-byte aligned rows. With kLdsCodes the dictionaries' code tables (at most
-// kFuseLdsCodes entries in all) are first copied into LDS, so the per-row code
-// lookups are LDS reads.
-constexpr uint32_t kFuseLdsCodes = 9216;  // 36 KB
-constexpr int kFuseGroups = 2;            // groups of four rows per thread and step
+// 16-byte aligned rows. kLds: some dictionary keys are looked up by value in a
+// table the workgroup builds from the sorted values, instead of reading back a slot
+// per row that the insertion would have had to write (2^28 rows, two such keys of
+// 256 values beside two narrow ones: 1.31 ms, 4.1 TB/s; through slots 1.10, but the
+// insertion then took 1.4 ms more).
+constexpr uint32_t kFuseLdsWords = 6144;  // 48 KB
+constexpr int kFuseNT = 256;
+constexpr int kFuseGroups = 1;  // groups of four rows per thread and step
+constexpr uint32_t kFuseNone = 0xFFFFFFFFu;
 
-template <typename F, bool kLdsCodes>
-__global__ void __launch_bounds__(kDeNT) k_skf_fuse_vec(FuseArgs A, uint32_t lds_off0, uint32_t lds_total) {
-  __shared__ uint32_t codes[kLdsCodes ? kFuseLdsCodes : 1];
-  uint32_t lds_off[EIGER_SKF_MAX_KEYS];
-  if constexpr (kLdsCodes) {
-    uint32_t o = lds_off0;
-    for (int c = 0; c < A.nk; ++c) {
-      lds_off[c] = o;
-      if (A.k[c].dict && A.k[c].bits) {
-        const uint32_t m = A.k[c].slots1;
-        for (uint32_t j = threadIdx.x; j < m; j += kDeNT) codes[o + j] = A.k[c].code_of_slot[j];
-        o += m;
+// A 4-byte key's slot is one word, value << 32 | code; an 8-byte key's a word of
+// value, the codes following all the values. Code kFuseNone: empty.
+inline __host__ __device__ uint32_t fuse_lds_words(bool wide, uint32_t slots) { return wide ? slots + slots / 2 : slots; }
+
+__device__ __forceinline__ void fuse_table(const FuseKey &k, unsigned long long *lds) {
+  unsigned long long *tab = lds + k.lds_at;
+  uint32_t *codes = reinterpret_cast<uint32_t *>(tab + k.lds_slots);
+  const uint32_t words = fuse_lds_words(k.wide, k.lds_slots);
+  for (uint32_t j = threadIdx.x; j < words; j += kFuseNT) tab[j] = ~0ull;  // every code kFuseNone
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < k.ndv; i += kFuseNT) {
+    const unsigned long long v = k.skey[i] + k.vbase;
+    uint32_t h = small_hash(v, k.lds_shift);
+    for (;;) {  // at least twice as many slots as values
+      if (k.wide) {
+        if (atomicCAS(&codes[h], kFuseNone, i) == kFuseNone) {
+          tab[h] = v;
+          break;
+        }
+      } else if (atomicCAS(&tab[h], ~0ull, (v << 32) | i) == ~0ull) {
+        break;
       }
+      h = (h + 1) & (k.lds_slots - 1);
     }
-    (void)lds_total;
+  }
+}
+
+// Codes of kFuseGroups * 4 values; every value is in the table. The walks step together.
+__device__ __forceinline__ void fuse_lookup(const FuseKey &k, const unsigned long long *lds,
+                                            const unsigned long long (&v)[kFuseGroups * 4],
+                                            uint32_t (&code)[kFuseGroups * 4]) {
+  constexpr int R = kFuseGroups * 4;
+  const unsigned long long *tab = lds + k.lds_at;
+  const uint32_t *codes = reinterpret_cast<const uint32_t *>(tab + k.lds_slots);
+  uint32_t h[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) h[q] = small_hash(v[q], k.lds_shift);
+  for (uint32_t step = 0; step < k.lds_slots; ++step) {
+    // all reads before any is looked at
+    unsigned long long w[R];
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < R; ++q) w[q] = tab[h[q]];
+    if (k.wide) {
+#pragma unroll
+      for (int q = 0; q < R; ++q) code[q] = codes[h[q]];
+    }
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      if (!k.wide) {
+        code[q] = static_cast<uint32_t>(w[q]);
+        w[q] = static_cast<unsigned long long>(static_cast<int64_t>(static_cast<int32_t>(w[q] >> 32)));
+      }
+      const bool on = w[q] != v[q] || code[q] == kFuseNone;
+      h[q] = on ? (h[q] + 1) & (k.lds_slots - 1) : h[q];
+      any |= on;
+    }
+    if (!any) break;
+  }
+}
+
+template <typename F, bool kLds>
+__global__ void __launch_bounds__(kFuseNT) k_skf_fuse_vec(FuseArgs A) {
+  extern __shared__ unsigned long long lds[];  // the keys' tables
+  if constexpr (kLds) {
+    for (int c = 0; c < A.nk; ++c)
+      if (A.k[c].lds_slots && A.k[c].bits) fuse_table(A.k[c], lds);
     __syncthreads();
   }
-  constexpr uint64_t span = uint64_t(kDeNT) * 4 * kFuseGroups;
+  constexpr uint64_t span = uint64_t(kFuseNT) * 4 * kFuseGroups;
   const uint64_t stride = static_cast<uint64_t>(gridDim.x) * span;
   for (uint64_t base = static_cast<uint64_t>(blockIdx.x) * span; base < A.n; base += stride) {
     uint64_t i0[kFuseGroups];
     bool full[kFuseGroups];
 #pragma unroll
     for (int g = 0; g < kFuseGroups; ++g) {
-      i0[g] = base + (static_cast<uint64_t>(g) * kDeNT + threadIdx.x) * 4;
+      i0[g] = base + (static_cast<uint64_t>(g) * kFuseNT + threadIdx.x) * 4;
       full[g] = i0[g] + 3 < A.n;
     }
     F f[kFuseGroups][4];
@@ -456,59 +598,81 @@ __global__ void __launch_bounds__(kDeNT) k_skf_fuse_vec(FuseArgs A, uint32_t lds
     for (int g = 0; g < kFuseGroups; ++g)
 #pragma unroll
       for (int u = 0; u < 4; ++u) f[g][u] = 0;
-    for (int c = 0; c < A.nk; ++c) {
+    // a key's values (or its rows' slots), as they lie in memory: one or two 16-byte
+    // words per group; the next key's are read while this one's codes are formed
+    uint4 raw[kFuseGroups][2], next[kFuseGroups][2];
+    auto read = [&](int c) {
       const FuseKey &k = A.k[c];
-      if (k.bits == 0) continue;
-      uint64_t code[kFuseGroups][4];
+      const bool by_slot = k.dict && !(kLds && k.lds_slots);
+      const char *src = static_cast<const char *>(by_slot ? static_cast<const void *>(k.loc) : k.a);
+      if (!by_slot && k.wide) {
+#pragma unroll
+        for (int g = 0; g < kFuseGroups; ++g) {
+          const uint64_t i = full[g] ? i0[g] : 0;
+          next[g][0] = *reinterpret_cast<const uint4 *>(src + i * 8);
+          next[g][1] = *reinterpret_cast<const uint4 *>(src + i * 8 + 16);
+        }
+      } else {
+#pragma unroll
+        for (int g = 0; g < kFuseGroups; ++g) next[g][0] = *reinterpret_cast<const uint4 *>(src + (full[g] ? i0[g] : 0) * 4);
+      }
+    };
+    auto first_key = [&](int c) {
+      while (c < A.nk && A.k[c].bits == 0) ++c;
+      return c;
+    };
+    // (an input of fewer than four rows has no whole group to read)
+    const bool any_full = A.n >= 4;
+    int c = first_key(0);
+    if (any_full && c < A.nk) read(c);
+    while (c < A.nk) {
+      const FuseKey &k = A.k[c];
 #pragma unroll
       for (int g = 0; g < kFuseGroups; ++g) {
-        const uint64_t i = i0[g];
-        if (k.dict) {
-          uint32_t sl[4] = {0u, 0u, 0u, 0u};
-          if (full[g]) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(k.loc + i);
-            sl[0] = v.x; sl[1] = v.y; sl[2] = v.z; sl[3] = v.w;
-          } else {
+        raw[g][0] = next[g][0];
+        raw[g][1] = next[g][1];
+      }
+      const int c1 = first_key(c + 1);
+      if (any_full && c1 < A.nk) read(c1);
+      unsigned long long v[kFuseGroups * 4];
+      const bool by_slot = k.dict && !(kLds && k.lds_slots);
+      const bool wide = !by_slot && k.wide;
 #pragma unroll
-            for (int u = 0; u < 4; ++u) sl[u] = i + u < A.n ? k.loc[i + u] : 0u;
-          }
+      for (int g = 0; g < kFuseGroups; ++g) {
+        const uint32_t w[8] = {raw[g][0].x, raw[g][0].y, raw[g][0].z, raw[g][0].w,
+                               raw[g][1].x, raw[g][1].y, raw[g][1].z, raw[g][1].w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          v[g * 4 + u] = wide ? (static_cast<unsigned long long>(w[2 * u + 1]) << 32) | w[2 * u]
+                         : by_slot ? w[u]
+                                   : static_cast<unsigned long long>(static_cast<int64_t>(static_cast<int32_t>(w[u])));
+        if (!full[g]) {  // the last rows, one by one (the last one again past it)
+          const void *src = by_slot ? static_cast<const void *>(k.loc) : k.a;
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            if constexpr (kLdsCodes)
-              code[g][u] = codes[lds_off[c] + sl[u]];
-            else
-              code[g][u] = i + u < A.n ? k.code_of_slot[sl[u]] : 0u;
+            const uint64_t i = std::min(i0[g] + u, A.n - 1);
+            v[g * 4 + u] = wide ? static_cast<const unsigned long long *>(src)[i]
+                           : by_slot ? static_cast<const uint32_t *>(src)[i]
+                                     : static_cast<unsigned long long>(static_cast<int64_t>(static_cast<const int32_t *>(src)[i]));
           }
-        } else if (k.wide) {
-          const int64_t *a = static_cast<const int64_t *>(k.a);
-          int64_t v[4] = {0, 0, 0, 0};
-          if (full[g]) {
-            const longlong2 x = *reinterpret_cast<const longlong2 *>(a + i);
-            const longlong2 y = *reinterpret_cast<const longlong2 *>(a + i + 2);
-            v[0] = x.x; v[1] = x.y; v[2] = y.x; v[3] = y.y;
-          } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = i + u < A.n ? a[i + u] : 0;
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) code[g][u] = static_cast<uint64_t>(v[u]) - k.base;
-        } else {
-          const int32_t *a = static_cast<const int32_t *>(k.a);
-          int32_t v[4] = {0, 0, 0, 0};
-          if (full[g]) {
-            const int4 x = *reinterpret_cast<const int4 *>(a + i);
-            v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
-          } else {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = i + u < A.n ? a[i + u] : 0;
-          }
-          // exact: every key is at least the minimum
-#pragma unroll
-          for (int u = 0; u < 4; ++u) code[g][u] = static_cast<uint64_t>(static_cast<int64_t>(v[u])) - k.base;
         }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) f[g][u] |= static_cast<F>((code[g][u] ^ k.flip) << k.shift);
       }
+      uint32_t code[kFuseGroups * 4];
+      if (by_slot) {
+#pragma unroll
+        for (int q = 0; q < kFuseGroups * 4; ++q) code[q] = k.code_of_slot[v[q]];
+      } else if constexpr (kLds) {
+        if (k.dict) fuse_lookup(k, lds, v, code);
+      }
+#pragma unroll
+      for (int g = 0; g < kFuseGroups; ++g)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          // exact: every frame-of-reference key is at least the minimum
+          const uint64_t x = k.dict ? code[g * 4 + u] : v[g * 4 + u] - k.base;
+          f[g][u] |= static_cast<F>((x ^ k.flip) << k.shift);
+        }
+      c = c1;
     }
 #pragma unroll
     for (int g = 0; g < kFuseGroups; ++g) {
@@ -528,6 +692,35 @@ __global__ void __launch_bounds__(kDeNT) k_skf_fuse_vec(FuseArgs A, uint32_t lds
       }
     }
   }
+}
+
+// What the fusion's 16-byte form takes, decided before the insertion (which writes
+// a slot per row only for keys that the fusion looks up through it).
+struct FusePlan {
+  bool vec;                                // every column one 16-byte aligned array, output too
+  uint32_t lds_slots[EIGER_SKF_MAX_KEYS];  // > 0: dictionary key looked up by value
+  uint32_t lds_at[EIGER_SKF_MAX_KEYS];
+  uint32_t lds_words;
+};
+
+FusePlan fuse_plan(const eiger_skf_plan_t &p, const eiger_column *ka, bool one_relation, const void *out_a) {
+  FusePlan f{};
+  f.vec = one_relation && reinterpret_cast<uintptr_t>(out_a) % 16 == 0;
+  for (int c = 0; c < p.n_keys; ++c) f.vec = f.vec && reinterpret_cast<uintptr_t>(ka[c].data) % 16 == 0;
+  if (!f.vec) return f;
+  // a key's LDS table has the slots of its encoding table, at least twice its values
+  uint32_t at = 0;
+  for (int c = 0; c < p.n_keys; ++c) {
+    const eiger_skf_key_t &k = p.key[c];
+    if (k.code != EIGER_SKF_DICT || k.slots < 16 || k.slots > static_cast<int64_t>(kDsSlots)) continue;
+    const uint32_t slots = static_cast<uint32_t>(k.slots), words = fuse_lds_words(k.dtype == EIGER_INT64, slots);
+    if (at + words > kFuseLdsWords) continue;
+    f.lds_slots[c] = slots;
+    f.lds_at[c] = at;
+    at += words;
+  }
+  f.lds_words = at;
+  return f;
 }
 
 // Sizes the sort workspace for the largest distinct-value sort and the row sort.
@@ -585,10 +778,23 @@ int de_launch_insert(const DictBufs &d, const void *a, const void *b, uint64_t n
   return EIGER_OK;
 }
 
+template <typename K>
+int de_launch_discover(const DictBufs &d, const void *a, uint64_t n, hipStream_t s) {
+  if (n == 0) return EIGER_OK;
+  // twice the global table's slots, so that the LDS table is at most a quarter full
+  const uint32_t slots = static_cast<uint32_t>(std::min<uint64_t>(2 * (d.t.mask + 1), kDsSlots));
+  const uint64_t span = uint64_t(kDsNT) * kDsRows;
+  const unsigned grid = static_cast<unsigned>(std::min<uint64_t>((n + span - 1) / span, uint64_t(device_cu_count()) * 4));
+  EIGER_LAUNCH("dict_insert", k_de_discover<K>, dim3(grid), dim3(kDsNT), 0, s, static_cast<const K *>(a), n, d.t, slots,
+               hash_shift(slots));
+  return EIGER_OK;
+}
+
 // Steps 1-2 for every dictionary key, one read-back of the counts, then steps 3-4.
 // Fills the exact counts and widths into *out.
 int dict_steps(const eiger_skf_plan_t &p, const eiger_column *ka, const eiger_column *kb, uint64_t na, uint64_t n,
-               SkfLayout &L, void *sort_ws, size_t sort_ws_size, eiger_skf_plan_t *out, hipStream_t s) {
+               const FusePlan &fp, SkfLayout &L, void *sort_ws, size_t sort_ws_size, eiger_skf_plan_t *out,
+               hipStream_t s) {
   bool any = false;
   for (int c = 0; c < p.n_keys; ++c) {
     if (p.key[c].code != EIGER_SKF_DICT) continue;
@@ -598,8 +804,11 @@ int dict_steps(const eiger_skf_plan_t &p, const eiger_column *ka, const eiger_co
     if (rc) return rc;
     if ((rc = fill_u32(d.t.ctr, 4, 0u, s))) return rc;
     const void *a = ka[c].data, *b = kb ? kb[c].data : nullptr;
-    rc = p.key[c].dtype == EIGER_INT64 ? de_launch_insert<int64_t>(d, a, b, na, n, s)
-                                       : de_launch_insert<int32_t>(d, a, b, na, n, s);
+    if (fp.lds_slots[c])
+      rc = p.key[c].dtype == EIGER_INT64 ? de_launch_discover<int64_t>(d, a, n, s) : de_launch_discover<int32_t>(d, a, n, s);
+    else
+      rc = p.key[c].dtype == EIGER_INT64 ? de_launch_insert<int64_t>(d, a, b, na, n, s)
+                                         : de_launch_insert<int32_t>(d, a, b, na, n, s);
     if (rc) return rc;
     EIGER_LAUNCH("dict_retrieve", k_de_retrieve, dim3(grid_for(d.t.mask + 1)), dim3(kDeNT), 0, s, d.t,
                  static_cast<uint64_t>(p.key[c].base), d.ukey, d.uslot);
@@ -633,7 +842,7 @@ int dict_steps(const eiger_skf_plan_t &p, const eiger_column *ka, const eiger_co
 }
 
 int launch_fuse(const eiger_skf_plan_t &p, const eiger_column *ka, const eiger_column *kb, uint64_t na, uint64_t n,
-                const SkfLayout &L, void *out_a, void *out_b, hipStream_t s) {
+                const FusePlan &fp, const SkfLayout &L, void *out_a, void *out_b, hipStream_t s) {
   if (n == 0) return EIGER_OK;
   FuseArgs A{};
   A.nk = p.n_keys;
@@ -650,34 +859,31 @@ int launch_fuse(const eiger_skf_plan_t &p, const eiger_column *ka, const eiger_c
     f.dict = k.code == EIGER_SKF_DICT;
     f.loc = L.d[c].loc;
     f.code_of_slot = L.d[c].code_of_slot;
-    f.slots1 = f.dict ? static_cast<uint32_t>(k.slots + 1) : 0u;
+    f.skey = L.d[c].skey;
+    f.vbase = static_cast<uint64_t>(k.base);  // the values were sorted as value - base
+    f.ndv = f.dict ? static_cast<uint32_t>(k.ndv) : 0u;
+    f.lds_slots = fp.lds_slots[c];
+    f.lds_shift = f.lds_slots ? hash_shift(f.lds_slots) : 0u;
+    f.lds_at = fp.lds_at[c];
     f.base = static_cast<uint64_t>(k.base);
     f.bits = k.bits;
     f.shift = k.shift;
     f.flip = k.descending && k.bits ? (k.bits == 64 ? ~0ull : ((1ull << k.bits) - 1)) : 0ull;
   }
-  // 16-byte form: every column one 16-byte aligned array, output too
-  bool vec = na == n && reinterpret_cast<uintptr_t>(out_a) % 16 == 0;
-  uint64_t lds_codes = 0;
-  for (int c = 0; c < p.n_keys; ++c) {
-    vec = vec && reinterpret_cast<uintptr_t>(ka[c].data) % 16 == 0;
-    if (p.key[c].code == EIGER_SKF_DICT && p.key[c].bits) lds_codes += A.k[c].slots1;
-  }
-  if (vec) {
-    const uint64_t units = (n + 4 * kFuseGroups - 1) / (4 * kFuseGroups);
-    const unsigned g = grid_for(units);
-    const bool lds = lds_codes <= kFuseLdsCodes;
-    const uint32_t lt = static_cast<uint32_t>(lds_codes);
+  if (fp.vec) {
+    const uint64_t span = uint64_t(kFuseNT) * 4 * kFuseGroups;
+    const unsigned g = static_cast<unsigned>(std::min<uint64_t>((n + span - 1) / span, uint64_t(device_cu_count()) * 8));
+    const size_t lds = size_t(fp.lds_words) * 8;
     if (p.fused_bytes == 4) {
-      if (lds)
-        EIGER_LAUNCH("skf_fuse", (k_skf_fuse_vec<uint32_t, true>), dim3(g), dim3(kDeNT), 0, s, A, 0u, lt);
+      if (fp.lds_words)
+        EIGER_LAUNCH("skf_fuse", (k_skf_fuse_vec<uint32_t, true>), dim3(g), dim3(kFuseNT), lds, s, A);
       else
-        EIGER_LAUNCH("skf_fuse", (k_skf_fuse_vec<uint32_t, false>), dim3(g), dim3(kDeNT), 0, s, A, 0u, lt);
+        EIGER_LAUNCH("skf_fuse", (k_skf_fuse_vec<uint32_t, false>), dim3(g), dim3(kFuseNT), 0, s, A);
     } else {
-      if (lds)
-        EIGER_LAUNCH("skf_fuse", (k_skf_fuse_vec<uint64_t, true>), dim3(g), dim3(kDeNT), 0, s, A, 0u, lt);
+      if (fp.lds_words)
+        EIGER_LAUNCH("skf_fuse", (k_skf_fuse_vec<uint64_t, true>), dim3(g), dim3(kFuseNT), lds, s, A);
       else
-        EIGER_LAUNCH("skf_fuse", (k_skf_fuse_vec<uint64_t, false>), dim3(g), dim3(kDeNT), 0, s, A, 0u, lt);
+        EIGER_LAUNCH("skf_fuse", (k_skf_fuse_vec<uint64_t, false>), dim3(g), dim3(kFuseNT), 0, s, A);
     }
     return EIGER_OK;
   }
@@ -733,12 +939,13 @@ int skf_run(const eiger_column *ka, const eiger_column *kb, int32_t n_keys, cons
   SkfLayout L;
   const size_t sort_need = skf_layout(ws, *plan, n, sort, &L);
   void *sort_ws = ws.take<char>(sort_need);
-  int rc = dict_steps(*plan, ka, kb, static_cast<uint64_t>(na), n, L, sort_ws, sort_need, out_plan, s);
+  const FusePlan fp = fuse_plan(*plan, ka, nb == 0, sort ? L.fused : out_a);
+  int rc = dict_steps(*plan, ka, kb, static_cast<uint64_t>(na), n, fp, L, sort_ws, sort_need, out_plan, s);
   if (rc) return rc;
   if (out_plan->fused_bytes == 0)
     return fail(EIGER_ERR_UNSUPPORTED, std::string(who) + ": the key codes need more than 64 bits");
-  if (!sort) return launch_fuse(*out_plan, ka, kb, static_cast<uint64_t>(na), n, L, out_a, out_b, s);
-  if ((rc = launch_fuse(*out_plan, ka, nullptr, n, n, L, L.fused, nullptr, s))) return rc;
+  if (!sort) return launch_fuse(*out_plan, ka, kb, static_cast<uint64_t>(na), n, fp, L, out_a, out_b, s);
+  if ((rc = launch_fuse(*out_plan, ka, nullptr, n, n, fp, L, L.fused, nullptr, s))) return rc;
   Workspace sw(sort_ws, sort_need);
   return radix_sort_pairs(out_plan->fused_bytes, L.fused, nullptr, n, out_plan->total_bits,
                           sorted ? sorted : L.sorted, perm, sw, s);
@@ -853,8 +1060,8 @@ extern "C" int eiger_dict_encode(eiger_column col, int64_t slots, uint32_t *out_
   const size_t sort_need = skf_layout(ws, p, static_cast<uint64_t>(col.n), false, &L);
   void *sort_ws = ws.take<char>(sort_need);
   eiger_skf_plan_t fin;
-  int rc = dict_steps(p, &col, nullptr, static_cast<uint64_t>(col.n), static_cast<uint64_t>(col.n), L, sort_ws,
-                      sort_need, &fin, s);
+  int rc = dict_steps(p, &col, nullptr, static_cast<uint64_t>(col.n), static_cast<uint64_t>(col.n),
+                      FusePlan{}, L, sort_ws, sort_need, &fin, s);
   if (rc) return rc;
   const uint64_t ndv = static_cast<uint64_t>(fin.key[0].ndv);
   *out_ndv = fin.key[0].ndv;

@@ -196,3 +196,35 @@ def test_fuse_vector_and_scalar_forms(gpu):
         fa, _, fin = eg.skf_fuse(view, plan=eg.skf_plan([eg.stats(c) for c in view], [False, True, False, False]))
         same_plan(fin, want_plan)
         assert np.array_equal(host(fa).view(np.uint32), skf.fuse(hc, want_plan, codes))
+
+
+@pytest.mark.parametrize("n", [1, 3, 4, 1023, 4097, 100_003])
+@pytest.mark.parametrize("dtype", [torch.int32, torch.int64])
+@pytest.mark.parametrize("slots", [[16, 16], [4096, 1024], [4096, 4096, 512], [512, 8192]])
+def test_fuse_looks_values_up(gpu, n, dtype, slots):
+    """Dictionary keys looked up by value: tables at the smallest and largest size,
+    half full, beside keys whose table no longer fits the workgroup's LDS (4,096 slots
+    of 8-byte keys fill it) or is too large for it, values at the ends of the type, -1 and
+    0 among them, and fewer rows than one 16-byte group."""
+    g = torch.Generator().manual_seed(n)
+    info = torch.iinfo(dtype)
+    cols = []
+    for sl in slots:
+        ndv = sl // 2
+        vals = torch.cat([torch.tensor([info.min, info.max, -1, 0], dtype=torch.int64),
+                          torch.arange(1, max(ndv - 3, 1)) * (info.max // max(ndv, 1))]).to(dtype)
+        rows = vals[torch.randint(0, vals.numel(), (n,), generator=g)]
+        rows[: min(n, vals.numel())] = vals[: min(n, vals.numel())]
+        cols.append(rows[torch.randperm(n, generator=g)].to(gpu))
+    plan = eg.skf_plan([eg.stats(c) for c in cols], for_max_bits=-1)
+    for k, sl in zip(plan.key, slots):
+        assert k.code == eg.SKF_DICT
+        k.slots = sl
+    fa, _, fin = eg.skf_fuse(cols, plan=plan)
+    assert [k.slots for k in fin.key[: len(slots)]] == slots  # nothing had to grow
+    want = np.zeros(n, dtype=np.uint64)
+    for c, k in zip(cols, fin.key):
+        u, code = np.unique(host(c), return_inverse=True)
+        assert k.ndv == len(u)
+        want |= code.astype(np.uint64) << np.uint64(k.shift)
+    assert np.array_equal(host(fa).view(np.uint32 if fin.fused_bytes == 4 else np.uint64).astype(np.uint64), want)
