@@ -422,7 +422,12 @@ __device__ __forceinline__ void emit_range(const unsigned long long *key, const 
   }
 }
 
-__global__ void __launch_bounds__(kGNT) k_gb_clear(GbGlobal g, int nv) {
+// The global table, the output cursor and the overflow flag.
+__global__ void __launch_bounds__(kGNT) k_gb_clear(GbGlobal g, int nv, unsigned long long *cursor) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *cursor = 0;
+    *g.overflow = 0;
+  }
   const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
   for (uint64_t i = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; i <= g.mask; i += stride) {
     g.key[i] = g.sentinel;
@@ -538,8 +543,9 @@ GbLayout gb_layout(Workspace &ws, uint64_t slots, int nv, unsigned long long sen
   for (int v = 0; v < kGMaxVals; ++v) L.g.sum[v] = v < nv ? ws.take<unsigned long long>(slots) : nullptr;
   L.g.mask = slots - 1;
   L.g.sentinel = sentinel;
-  L.cursor = ws.take<unsigned long long>(1);
-  L.overflow = ws.take<uint32_t>(1);
+  L.cursor = ws.take<unsigned long long>(2);  // the flag in the second word, for one copy to the host
+  L.overflow = reinterpret_cast<uint32_t *>(L.cursor + 1);
+  ws.take<uint32_t>(1);
   L.g.overflow = L.overflow;
   return L;
 }
@@ -626,11 +632,9 @@ int gb_impl(const eiger_column &keys, const eiger_column *vals, int32_t nv, cons
   GbOut o = out_in;
   o.cursor = lay->cursor;
   int rc;
-  if ((rc = fill_u64(reinterpret_cast<uint64_t *>(lay->cursor), 1, 0, s))) return rc;
-  if ((rc = fill_u32(lay->overflow, 1, 0, s))) return rc;
   const unsigned cus = static_cast<unsigned>(device_cu_count());
   EIGER_LAUNCH("groupby_clear", k_gb_clear, dim3(std::min<uint64_t>((plan.slots + kGNT - 1) / kGNT, cus * 8)),
-               dim3(kGNT), 0, s, g, nv);
+               dim3(kGNT), 0, s, g, nv, lay->cursor);
   if (n == 0) return EIGER_OK;
   const bool w0 = nv > 0 && vals[0].dtype == EIGER_INT64, w1 = nv > 1 && vals[1].dtype == EIGER_INT64;
   AggCall call{};
@@ -796,8 +800,8 @@ extern "C" int eiger_groupby(eiger_column keys, const eiger_column *vals, int32_
     unsigned long long groups;
     uint32_t overflow;
   } host{};
-  EIGER_HIP(hipMemcpyAsync(&host.groups, lay.cursor, sizeof(host.groups), hipMemcpyDeviceToHost, s));
-  EIGER_HIP(hipMemcpyAsync(&host.overflow, lay.overflow, sizeof(host.overflow), hipMemcpyDeviceToHost, s));
+  static_assert(sizeof(host) == 16, "cursor and flag as they lie in the workspace");
+  EIGER_HIP(hipMemcpyAsync(&host, lay.cursor, sizeof(host), hipMemcpyDeviceToHost, s));
   EIGER_HIP(hipStreamSynchronize(s));
   if (host.overflow)
     return fail(EIGER_ERR_TOO_LARGE, "eiger_groupby: more groups than the plan's table slots (the distinct-count "

@@ -96,8 +96,15 @@ __global__ void k_hash_build(const K *__restrict__ keys, const PB *__restrict__ 
 // Table clear for the key-claiming build: key = sentinel, row id = empty. Slots
 // are 16 or 32 bytes (one or two 16-byte words); each workgroup stores one
 // contiguous chunk of the table with 16-byte stores, as the library's fills do.
+// The first one also zeroes the join's counters and duplicate flag.
 template <typename K, typename PB>
-__global__ void __launch_bounds__(256) k_hash_clear(Slot<K, PB> *__restrict__ slots, uint64_t n, K sentinel) {
+__global__ void __launch_bounds__(256) k_hash_clear(Slot<K, PB> *__restrict__ slots, uint64_t n, K sentinel,
+                                                    HashCounters *__restrict__ c, uint32_t *__restrict__ dup) {
+  static_assert(sizeof(HashCounters) / 8 <= 256, "one word per thread");
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < sizeof(HashCounters) / 8) reinterpret_cast<uint64_t *>(c)[threadIdx.x] = 0;
+    if (threadIdx.x == 0) *dup = 0;
+  }
   constexpr int kWords = sizeof(Slot<K, PB>) / 16;
   static_assert(kWords == 1 || kWords == 2, "16- or 32-byte slots");
   Slot<K, PB> e{};
@@ -205,25 +212,26 @@ int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   if (!ws.base) return EIGER_OK;
   hipStream_t s = a.s;
   int rc;
-  if ((rc = fill_u64(reinterpret_cast<uint64_t *>(hc), sizeof(HashCounters) / 8, 0, s))) return rc;
-  if (a.nR == 0 || a.nS == 0) return EIGER_OK;
-  if ((rc = fill_u32(dup, 1, 0, s))) return rc;
-  HashTab<K, PB> tab{slots, nslots - 1, dup, false};
   K sentinel;
-  if (hash_sentinel<K>(a, &sentinel)) {
+  const bool by_key = a.nR > 0 && a.nS > 0 && hash_sentinel<K>(a, &sentinel);
+  if (!by_key && (rc = fill_u64(reinterpret_cast<uint64_t *>(hc), sizeof(HashCounters) / 8, 0, s))) return rc;
+  if (a.nR == 0 || a.nS == 0) return EIGER_OK;
+  if (!by_key && (rc = fill_u32(dup, 1, 0, s))) return rc;
+  HashTab<K, PB> tab{slots, nslots - 1, dup, false};
+  if (by_key) {
     EIGER_LAUNCH("hash_clear", (k_hash_clear<K, PB>),
                  dim3(static_cast<unsigned>(std::min<uint64_t>((nslots + 1023) / 1024, uint64_t(device_cu_count()) * 16))),
-                 dim3(256), 0, s, slots, nslots, sentinel);
-    EIGER_LAUNCH("hash_build", (k_hash_build_keys<K, PB>), dim3(grid_for(a.nR, 256 * 2, 8)), dim3(256), 0, s,
+                 dim3(256), 0, s, slots, nslots, sentinel, hc, dup);
+    EIGER_LAUNCH("hash_build", (k_hash_build_keys<K, PB>), dim3(grid_for(a.nR, 256, 8)), dim3(256), 0, s,
                  static_cast<const K *>(a.bk), static_cast<const PB *>(a.bp), a.nR, slots, nslots - 1, sentinel,
                  dup, &c->flags);
   } else {
     // keys at both ends of the domain: claim by row id, then a duplicate check
     if ((rc = fill_u32(reinterpret_cast<uint32_t *>(slots), nslots * sizeof(Slot<K, PB>) / 4, kEmpty, s)))
       return rc;
-    EIGER_LAUNCH("hash_build", (k_hash_build<K, PB>), dim3(grid_for(a.nR, 256 * 2, 8)), dim3(256), 0, s,
+    EIGER_LAUNCH("hash_build", (k_hash_build<K, PB>), dim3(grid_for(a.nR, 256, 8)), dim3(256), 0, s,
                  static_cast<const K *>(a.bk), static_cast<const PB *>(a.bp), a.nR, slots, nslots - 1);
-    EIGER_LAUNCH("hash_unique", (k_hash_unique<K, PB>), dim3(grid_for(a.nR, 256 * 2, 8)), dim3(256), 0, s,
+    EIGER_LAUNCH("hash_unique", (k_hash_unique<K, PB>), dim3(grid_for(a.nR, 256, 8)), dim3(256), 0, s,
                  static_cast<const K *>(a.bk), a.nR, tab, dup);
   }
   EmitOut o{a.ob, a.op, a.cap, &c->count, &c->checksum, hc->stripe};

@@ -193,10 +193,14 @@ struct StatsLayout {
   int64_t *mm;
 };
 
+// What the host reads back, registers then min and max, lies together.
+constexpr size_t kStatsBytes = kHllM + 2 * sizeof(int64_t);
+static_assert(kHllM % 256 == 0, "no gap between the registers and what follows them");
+
 StatsLayout stats_layout(Workspace &ws, int groups) {
   StatsLayout L;
-  L.part_regs = ws.take<uint32_t>(size_t(groups) * kWords);
   L.slice_regs = ws.take<uint32_t>(size_t(kSlices) * kWords);
+  L.part_regs = ws.take<uint32_t>(size_t(groups) * kWords);
   L.part_mm = ws.take<int64_t>(size_t(groups) * 2);
   L.regs = ws.take<uint32_t>(kWords);
   L.mm = ws.take<int64_t>(2);
@@ -289,7 +293,10 @@ extern "C" int eiger_stats(eiger_column keys, eiger_stats_t *out, uint8_t *hll_r
     EIGER_LAUNCH("stats_partial", k_stats_partial<int64_t>, dim3(groups), dim3(kStatsThreads), 0, s,
                  static_cast<const int64_t *>(keys.data), uint64_t(keys.n), L.part_regs, L.part_mm);
   }
-  if (groups <= 2 * kSlices) {  // few workgroups: one merge launch over them all
+  const void *result = L.regs;
+  if (groups == 1) {  // one workgroup's registers are the column's (a launch less: 5 us of a small column's 20)
+    result = L.part_regs;
+  } else if (groups <= 2 * kSlices) {  // few workgroups: one merge launch over them all
     EIGER_LAUNCH("stats_final", k_stats_final, dim3(kWords / 256), dim3(256), 0, s, L.part_regs, groups, L.regs,
                  L.part_mm, groups, L.mm);
   } else {
@@ -298,11 +305,11 @@ extern "C" int eiger_stats(eiger_column keys, eiger_stats_t *out, uint8_t *hll_r
     EIGER_LAUNCH("stats_final", k_stats_final, dim3(kWords / 256), dim3(256), 0, s, L.slice_regs, kSlices,
                  L.regs, L.part_mm, groups, L.mm);
   }
-  std::vector<uint8_t> regs(kHllM);
+  std::vector<uint8_t> regs(kStatsBytes);
   int64_t mm[2];
-  EIGER_HIP(hipMemcpyAsync(regs.data(), L.regs, kHllM, hipMemcpyDeviceToHost, s));
-  EIGER_HIP(hipMemcpyAsync(mm, L.mm, sizeof(mm), hipMemcpyDeviceToHost, s));
+  EIGER_HIP(hipMemcpyAsync(regs.data(), result, kStatsBytes, hipMemcpyDeviceToHost, s));
   EIGER_HIP(hipStreamSynchronize(s));
+  std::memcpy(mm, regs.data() + kHllM, sizeof(mm));
   out->n = keys.n;
   out->min = mm[0];
   out->max = mm[1];
