@@ -8,6 +8,7 @@
 // small kernel takes the byte-wise max over the workgroups.
 #include <cmath>
 #include <cstring>
+#include <limits>
 #include <vector>
 
 #include "common.hpp"
@@ -28,7 +29,7 @@ template <>
 struct Vec16<int32_t> {
   using T = v4i32;
   static constexpr int N = 4;
-  __device__ static int64_t get(const T &v, int k) { return v[k]; }
+  __device__ static int32_t get(const T &v, int k) { return v[k]; }
 };
 template <>
 struct Vec16<int64_t> {
@@ -37,13 +38,29 @@ struct Vec16<int64_t> {
   __device__ static int64_t get(const T &v, int k) { return v[k]; }
 };
 
+// fmix64 of the sign-extended key. For a 4-byte key the high half of the first
+// xor-shift is the sign alone, so the first product is two multiplications.
+__device__ __forceinline__ uint64_t stats_hash(int64_t x) { return fmix64(static_cast<uint64_t>(x)); }
+__device__ __forceinline__ uint64_t stats_hash(int32_t x) {
+  constexpr uint64_t c = 0xff51afd7ed558ccdull;
+  const uint32_t sign = static_cast<uint32_t>(x >> 31);  // all ones for a negative key
+  const uint32_t lo = static_cast<uint32_t>(x) ^ (sign >> 1);
+  uint64_t k = static_cast<uint64_t>(lo) * static_cast<uint32_t>(c);
+  k += static_cast<uint64_t>(lo * static_cast<uint32_t>(c >> 32) - (sign & static_cast<uint32_t>(c))) << 32;
+  k ^= k >> 33;
+  k *= 0xc4ceb9fe1a85ec53ull;
+  k ^= k >> 33;
+  return k;
+}
+
+template <typename K>
 struct StatsLane {
-  int64_t mn = INT64_MAX;
-  int64_t mx = INT64_MIN;
-  __device__ __forceinline__ void visit(int64_t x, uint32_t *regs) {
+  K mn = std::numeric_limits<K>::max();
+  K mx = std::numeric_limits<K>::min();
+  __device__ __forceinline__ void visit(K x, uint32_t *regs) {
     mn = x < mn ? x : mn;
     mx = x > mx ? x : mx;
-    const uint64_t h = fmix64(static_cast<uint64_t>(x));
+    const uint64_t h = stats_hash(x);
     const uint32_t idx = static_cast<uint32_t>(h >> (64 - kHllP));
     const uint64_t w = h << kHllP;
     const uint32_t rank = w ? static_cast<uint32_t>(__clzll(w)) + 1u : uint32_t(64 - kHllP + 1);
@@ -61,13 +78,13 @@ __global__ void __launch_bounds__(kStatsThreads)
   __syncthreads();
 
   using V = Vec16<K>;
-  StatsLane lane;
+  StatsLane<K> lane;
   const uint64_t gtid = uint64_t(blockIdx.x) * kStatsThreads + threadIdx.x;
   const uint64_t stride = uint64_t(gridDim.x) * kStatsThreads;
   // scalar head up to the first 16-byte boundary, then 16-byte vectors
   uint64_t head = ((16 - (reinterpret_cast<uintptr_t>(keys) & 15)) & 15) / sizeof(K);
   if (head > n) head = n;
-  if (gtid < head) lane.visit(sext(keys[gtid]), regs);
+  if (gtid < head) lane.visit(keys[gtid], regs);
   keys += head;
   n -= head;
   const uint64_t nvec = n / V::N;
@@ -87,8 +104,9 @@ __global__ void __launch_bounds__(kStatsThreads)
 #pragma unroll
     for (int k = 0; k < V::N; ++k) lane.visit(V::get(b, k), regs);
   }
-  for (uint64_t i = nvec * V::N + gtid; i < n; i += stride) lane.visit(sext(keys[i]), regs);
+  for (uint64_t i = nvec * V::N + gtid; i < n; i += stride) lane.visit(keys[i], regs);
 
+  // (a lane without rows holds the type's ends; some lane of the column has one)
   int64_t mn = wave_min_i64(lane.mn), mx = wave_max_i64(lane.mx);
   const int wave = threadIdx.x / 64;
   if (__lane_id() == 0) {
