@@ -77,7 +77,9 @@ struct PartDigit {
 };
 
 // Workgroups loop over tiles (the grid is sized to the chip): one workgroup
-// per tile was limited by how fast workgroups are dispatched, not by memory.
+// per tile was limited by how fast workgroups are dispatched, not by memory. Each
+// XCD takes a contiguous eighth of the tiles, whose counts share cache lines (2^28
+// 4-byte keys 0.25 ms a pass, 4.4 TB/s; dealt round-robin 0.26).
 // kVec (16-byte aligned keys): each thread reads 16 bytes of consecutive keys
 // per load (counting does not depend on which thread holds which key).
 // Counts go out digit-major (cnt[digit * ntiles + tile], for the scan) or, for the
@@ -89,7 +91,10 @@ __global__ void __launch_bounds__(kHNT) k_sort_hist(const K *__restrict__ keys, 
   constexpr int NV = T / V;                            // 16-byte loads per tile
   static_assert(NV % kHNT == 0, "whole loads");
   __shared__ uint32_t h[kSDigits];
-  for (uint32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
+  const uint32_t per_xcd = (ntiles + kXcds - 1) / kXcds;
+  for (uint32_t x = blockIdx.x / kXcds; x < per_xcd; x += gridDim.x / kXcds) {
+    const uint32_t tile = blockIdx.x % kXcds * per_xcd + x;
+    if (tile >= ntiles) break;
     h[threadIdx.x] = 0;
     __syncthreads();
     const uint64_t base = static_cast<uint64_t>(tile) * T;
@@ -472,8 +477,8 @@ int lsd_passes(const K *kin, LanesIn vin, uint64_t n, int total_bits, K *kout, L
                MakeDigit make, hipStream_t s) {
   constexpr int T = kSNT * kItems;
   const int passes = pass_count(total_bits);
-  const unsigned hist_grid =
-      static_cast<unsigned>(std::min<uint64_t>(b.ntiles, uint64_t(device_cu_count()) * kHistPerCu));
+  const unsigned hist_grid = static_cast<unsigned>(
+      std::min<uint64_t>((b.ntiles + kXcds - 1) / kXcds, uint64_t(device_cu_count()) * kHistPerCu / kXcds) * kXcds);
   const unsigned scat_grid = static_cast<unsigned>((b.ntiles + kXcds - 1) / kXcds * kXcds);
   const uint32_t nt = static_cast<uint32_t>(b.ntiles);
   const bool self_scan = kItems == kItemsSmall && b.ntiles <= kSelfScanTiles;

@@ -78,27 +78,48 @@ __global__ void __launch_bounds__(1024) k_scan_tiles(uint64_t *__restrict__ tile
   }
 }
 
+typedef uint32_t V4u __attribute__((ext_vector_type(4)));
+typedef V4u Word4 __attribute__((aligned(4)));
+
 // Phase 3: exclusive scan inside each tile, offset by the tile's prefix.
 // Each thread owns kScanItems consecutive elements.
 __global__ void __launch_bounds__(kScanThreads) k_scan_down(const uint32_t *in, uint32_t *out,
                                                             uint64_t n,
                                                             const uint64_t *__restrict__ tile_off) {
-  __shared__ uint32_t scratch[kScanThreads / 64 + 1];
+  __shared__ uint32_t scratch[kScanThreads / 64];
   const uint64_t base = uint64_t(blockIdx.x) * kScanTile + uint64_t(threadIdx.x) * kScanItems;
   uint32_t v[kScanItems];
   uint32_t s = 0;
+  const bool full = base + kScanItems <= n;
+  if (full) {  // 64 consecutive bytes of the thread
 #pragma unroll
-  for (int k = 0; k < kScanItems; ++k) {
-    v[k] = (base + k < n) ? in[base + k] : 0u;
-    s += v[k];
+    for (int k = 0; k < kScanItems; k += 4) {
+      const Word4 q = *reinterpret_cast<const Word4 *>(in + base + k);
+      v[k] = q.x, v[k + 1] = q.y, v[k + 2] = q.z, v[k + 3] = q.w;
+    }
+  } else {
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) v[k] = (base + k < n) ? in[base + k] : 0u;
   }
+#pragma unroll
+  for (int k = 0; k < kScanItems; ++k) s += v[k];
   uint32_t total;
   uint32_t run = block_exclusive_scan<kScanThreads>(s, scratch, &total) +
                  static_cast<uint32_t>(tile_off[blockIdx.x]);
 #pragma unroll
   for (int k = 0; k < kScanItems; ++k) {
-    if (base + k < n) out[base + k] = run;
-    run += v[k];
+    const uint32_t t = v[k];
+    v[k] = run;
+    run += t;
+  }
+  if (full) {
+#pragma unroll
+    for (int k = 0; k < kScanItems; k += 4)
+      *reinterpret_cast<Word4 *>(out + base + k) = Word4{v[k], v[k + 1], v[k + 2], v[k + 3]};
+  } else {
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k)
+      if (base + k < n) out[base + k] = v[k];
   }
 }
 
