@@ -2,7 +2,8 @@
 //
 // Section 3.6 (cases 1 and 2): a single numeric key, or several keys fused into
 // one by smart key fusion, are sorted by radix sort. Each pass sorts by one digit
-// of at most 8 bits, least significant digit first; the number of passes follows
+// of at most 8 bits, least significant digit first (a partitioning of many rows: up
+// to 10); the number of passes follows
 // the key's significant width (the fused key's width), not its type.
 //
 // One pass = a per-tile digit histogram (k_sort_hist), an exclusive scan over the
@@ -28,7 +29,7 @@ constexpr int kSNT = 512;  // scatter workgroup
 constexpr int kSWaves = kSNT / 64;
 constexpr int kSDigitBits = 8;
 constexpr int kSDigits = 1 << kSDigitBits;
-static_assert(kSDigits == kHNT && kSDigits <= kSNT, "one thread per digit");
+static_assert(kSDigits == kHNT && kSDigits <= kSNT, "one thread per digit of 8 bits");
 
 // Tiles. Large inputs: 10,240 items (6,144 of 8-byte keys): longer runs per digit
 // against registers (2^28 4-byte pairs, 32 bits, all passes: 12 items per thread
@@ -56,6 +57,7 @@ constexpr uint32_t kXcds = 8;
 // Digit of a plain sort: bits [shift, shift + width) of the key.
 template <typename K>
 struct KeyDigit {
+  static constexpr int kBits = kSDigitBits;
   static constexpr bool kStore = false;  // cheap: recomputed from the key
   int shift;
   uint32_t mask;
@@ -64,8 +66,9 @@ struct KeyDigit {
 
 // Digit of a key's partition id, the top `bits` bits of its partition hash
 // (hash partitioning).
-template <typename K>
+template <typename K, int B>
 struct PartDigit {
+  static constexpr int kBits = B;
   // 8-byte keys: a 64-bit hash per item is kept (its digit, in LDS) for the write-out
   static constexpr bool kStore = sizeof(K) == 8;
   int top;  // 64 - partition bits
@@ -90,12 +93,14 @@ __global__ void __launch_bounds__(kHNT) k_sort_hist(const K *__restrict__ keys, 
   constexpr int V = 16 / static_cast<int>(sizeof(K));  // keys per 16-byte load
   constexpr int NV = T / V;                            // 16-byte loads per tile
   static_assert(NV % kHNT == 0, "whole loads");
-  __shared__ uint32_t h[kSDigits];
+  constexpr int kDigits = 1 << D::kBits;
+  __shared__ uint32_t h[kDigits];
   const uint32_t per_xcd = (ntiles + kXcds - 1) / kXcds;
   for (uint32_t x = blockIdx.x / kXcds; x < per_xcd; x += gridDim.x / kXcds) {
     const uint32_t tile = blockIdx.x % kXcds * per_xcd + x;
     if (tile >= ntiles) break;
-    h[threadIdx.x] = 0;
+#pragma unroll
+    for (int d = threadIdx.x; d < kDigits; d += kHNT) h[d] = 0;
     __syncthreads();
     const uint64_t base = static_cast<uint64_t>(tile) * T;
     if constexpr (kVec) {
@@ -121,10 +126,13 @@ __global__ void __launch_bounds__(kHNT) k_sort_hist(const K *__restrict__ keys, 
       }
     }
     __syncthreads();
-    if constexpr (kTileMajor)
-      cnt[static_cast<uint64_t>(tile) * kSDigits + threadIdx.x] = h[threadIdx.x];
-    else if (threadIdx.x <= dig.mask)
-      cnt[static_cast<uint64_t>(threadIdx.x) * ntiles + tile] = h[threadIdx.x];
+#pragma unroll
+    for (uint32_t d = threadIdx.x; d < kDigits; d += kHNT) {
+      if constexpr (kTileMajor)
+        cnt[static_cast<uint64_t>(tile) * kDigits + d] = h[d];
+      else if (d <= dig.mask)
+        cnt[static_cast<uint64_t>(d) * ntiles + tile] = h[d];
+    }
     __syncthreads();
   }
 }
@@ -143,11 +151,12 @@ struct LanesOut {
 // Stable ranks of a wave's items of one step among the wave's items so far:
 // lanes of the same digit are found with one ballot per digit bit, `cnt` (LDS, the
 // wave's own) holds the running counts. Returns the item's rank in its digit.
+template <int B>
 __device__ __forceinline__ uint32_t wave_rank(uint32_t d, bool ok, int bits, uint16_t *cnt) {
   const uint64_t all = __ballot(ok);
   uint32_t plo = static_cast<uint32_t>(all), phi = static_cast<uint32_t>(all >> 32);
 #pragma unroll
-  for (int b = 0; b < kSDigitBits; ++b) {
+  for (int b = 0; b < B; ++b) {
     if (b < bits) {
       const uint32_t m = static_cast<uint32_t>(static_cast<int32_t>(d << (31 - b)) >> 31);  // all ones when bit b is set
       const uint64_t bb = __ballot(m != 0);
@@ -164,40 +173,53 @@ __device__ __forceinline__ uint32_t wave_rank(uint32_t d, bool ok, int bits, uin
   return pre + before;
 }
 
+// Digits of 2^B a thread of NT sees to in the tile's digit scan: digits
+// threadIdx.x * digits_per<NT, B> and on, while there are any.
+template <int NT, int B>
+constexpr int digits_per = (1 << B) > NT ? (1 << B) / NT : 1;
+
 // Turns the waves' digit counts of a tile into start positions in the tile's
-// digit-major order (wave order = item order) and returns, in thread t < kSDigits,
-// the start of digit t. All threads call it (barriers).
-template <int NT>
-__device__ __forceinline__ uint32_t tile_starts(uint16_t (*wcnt)[kSDigits], uint32_t *scan_tmp) {
-  constexpr int NW = NT / 64;
-  const int t = threadIdx.x;
-  uint32_t c[NW], tot = 0;
-  if (t < kSDigits) {
+// digit-major order (wave order = item order); ds: the starts of this thread's
+// digits. All threads call it (barriers).
+template <int NT, int B>
+__device__ __forceinline__ void tile_starts(uint16_t (*wcnt)[1 << B], uint32_t *scan_tmp,
+                                            uint32_t (&ds)[digits_per<NT, B>]) {
+  constexpr int NW = NT / 64, PER = digits_per<NT, B>;
+  const int t = threadIdx.x * PER;
+  uint32_t c[PER][NW], tot = 0;
+  if (t < (1 << B)) {
 #pragma unroll
-    for (int x = 0; x < NW; ++x) {
-      c[x] = wcnt[x][t];
-      tot += c[x];
+    for (int e = 0; e < PER; ++e) {
+      ds[e] = tot;
+#pragma unroll
+      for (int x = 0; x < NW; ++x) {
+        c[e][x] = wcnt[x][t + e];
+        tot += c[e][x];
+      }
     }
   }
   uint32_t all;
-  const uint32_t ds = block_exclusive_scan<NT, uint32_t>(tot, scan_tmp, &all);
-  if (t < kSDigits) {
-    uint32_t run = ds;
+  const uint32_t first = block_exclusive_scan<NT, uint32_t>(tot, scan_tmp, &all);
+  if (t < (1 << B)) {
 #pragma unroll
-    for (int x = 0; x < NW; ++x) {
-      wcnt[x][t] = static_cast<uint16_t>(run);
-      run += c[x];
+    for (int e = 0; e < PER; ++e) {
+      ds[e] += first;
+      uint32_t run = ds[e];
+#pragma unroll
+      for (int x = 0; x < NW; ++x) {
+        wcnt[x][t + e] = static_cast<uint16_t>(run);
+        run += c[e][x];
+      }
     }
   }
-  return ds;
 }
 
-template <typename K, int kItems, bool kStoreDigit>
+template <typename K, int kItems, bool kStoreDigit, int B>
 struct ScatterLds {
   K sk[kSNT * kItems];  // the tile's keys, then each value lane
   uint8_t sd[kStoreDigit ? kSNT * kItems : 4];
-  __align__(4) uint16_t wcnt[kSWaves][kSDigits];
-  uint32_t adj[kSDigits];
+  __align__(4) uint16_t wcnt[kSWaves][1 << B];
+  uint32_t adj[1 << B];
   uint32_t scan_tmp[kSWaves];
 };
 
@@ -211,7 +233,7 @@ __device__ __forceinline__ void item_fence(int j) {
 // One tile of a scatter pass. kFull: the tile has all its items. Uniform across
 // the workgroup (barriers).
 template <typename K, int kItems, typename D, bool kSelfScan, bool kFull>
-__device__ __forceinline__ void scatter_tile(ScatterLds<K, kItems, D::kStore> &L, const K *__restrict__ kin,
+__device__ __forceinline__ void scatter_tile(ScatterLds<K, kItems, D::kStore, D::kBits> &L, const K *__restrict__ kin,
                                              const LanesIn &vin, uint64_t base, uint32_t in_tile, const D &dig, int bits,
                                              uint32_t tile, uint32_t ntiles, const uint32_t *__restrict__ offs,
                                              K *__restrict__ kout, const LanesOut &vout) {
@@ -219,7 +241,7 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<K, kItems, D::kStore> &L
   const int w = threadIdx.x / 64;
   const uint32_t first = static_cast<uint32_t>(w) * (64 * kItems) + __lane_id();  // this thread's items: first + 64 j
   auto has = [&](uint32_t i) { return kFull || i < in_tile; };
-  for (int x = threadIdx.x; x < kSWaves * kSDigits / 2; x += kSNT) reinterpret_cast<uint32_t *>(L.wcnt)[x] = 0;
+  for (int x = threadIdx.x; x < kSWaves * (1 << D::kBits) / 2; x += kSNT) reinterpret_cast<uint32_t *>(L.wcnt)[x] = 0;
   K key[kItems];
   {
     const K *src = kin + base;
@@ -230,15 +252,18 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<K, kItems, D::kStore> &L
   uint32_t pos[(kItems + 1) / 2];  // two 16-bit positions each
 #pragma unroll
   for (int j = 0; j < kItems; ++j) {
-    const uint32_t r = wave_rank(dig(key[j]), has(first + j * 64), bits, L.wcnt[w]);
+    const uint32_t r = wave_rank<D::kBits>(dig(key[j]), has(first + j * 64), bits, L.wcnt[w]);
     pos[j / 2] = j % 2 ? pos[j / 2] | r << 16 : r;
     item_fence<2>(j);
   }
   __syncthreads();
-  const uint32_t ds = tile_starts<kSNT>(L.wcnt, L.scan_tmp);
+  constexpr int kPer = digits_per<kSNT, D::kBits>;
+  uint32_t ds[kPer];
+  tile_starts<kSNT, D::kBits>(L.wcnt, L.scan_tmp, ds);
   // global start of this tile's run of digit t, minus its start inside the tile
   const uint32_t t = threadIdx.x;
   if constexpr (kSelfScan) {
+    static_assert(D::kBits == kSDigitBits, "one lane per four digits");
     // wave w sums tiles w, w + kSWaves, ...; a lane takes four digits
     uint4 total = make_uint4(0, 0, 0, 0), before = total;
 #pragma unroll 8
@@ -263,9 +288,13 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<K, kItems, D::kStore> &L
     }
     uint32_t all;
     const uint32_t start = block_exclusive_scan<kSNT, uint32_t>(tot, L.scan_tmp, &all);
-    if (t < kSDigits) L.adj[t] = start + bef - ds;
+    if (t < kSDigits) L.adj[t] = start + bef - ds[0];
   } else {
-    if (t < kSDigits) L.adj[t] = t <= dig.mask ? offs[static_cast<uint64_t>(t) * ntiles + tile] - ds : 0u;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+      const uint32_t d = t * kPer + e;
+      if (d < (1u << D::kBits)) L.adj[d] = d <= dig.mask ? offs[static_cast<uint64_t>(d) * ntiles + tile] - ds[e] : 0u;
+    }
   }
   __syncthreads();
 #pragma unroll
@@ -350,7 +379,7 @@ __global__ void __launch_bounds__(kSNT, 4) k_sort_scatter(const K *__restrict__ 
                                                           K *__restrict__ kout, LanesOut vout) {
   constexpr uint32_t T = kSNT * kItems;
   static_assert(T < 65536, "counts and positions of a tile fit 16 bits");
-  __shared__ ScatterLds<K, kItems, D::kStore> L;
+  __shared__ ScatterLds<K, kItems, D::kStore, D::kBits> L;
   const uint32_t per_xcd = (ntiles + kXcds - 1) / kXcds;
   const uint32_t tile = blockIdx.x % kXcds * per_xcd + blockIdx.x / kXcds;
   if (tile >= ntiles) return;
@@ -397,9 +426,10 @@ __global__ void __launch_bounds__(kBNT) k_sort_block(const K *__restrict__ kin, 
     for (int x = threadIdx.x; x < kBNT / 64 * kSDigits / 2; x += kBNT) reinterpret_cast<uint32_t *>(wcnt)[x] = 0;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < kItems; ++j) r[j] = wave_rank(dig(key[j]), first + j * 64 < n, bits, wcnt[w]);
+    for (int j = 0; j < kItems; ++j) r[j] = wave_rank<kSDigitBits>(dig(key[j]), first + j * 64 < n, bits, wcnt[w]);
     __syncthreads();
-    tile_starts<kBNT>(wcnt, scan_tmp);
+    uint32_t ds[1];
+    tile_starts<kBNT, kSDigitBits>(wcnt, scan_tmp, ds);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
@@ -452,10 +482,10 @@ struct PassBufs {
 };
 
 template <typename K>
-PassBufs<K> pass_bufs(Workspace &ws, uint64_t n, int T, int lanes, int passes) {
+PassBufs<K> pass_bufs(Workspace &ws, uint64_t n, int T, int lanes, int passes, int digit_bits = kSDigitBits) {
   PassBufs<K> b{};
   b.ntiles = (n + T - 1) / T;
-  const uint64_t ncnt = b.ntiles * kSDigits;
+  const uint64_t ncnt = b.ntiles << digit_bits;
   b.cnt = ws.take<uint32_t>(ncnt);
   b.tmp = ws.take<uint64_t>(scan_tmp_elems(ncnt));
   b.total = ws.take<uint64_t>(1);
@@ -466,17 +496,17 @@ PassBufs<K> pass_bufs(Workspace &ws, uint64_t n, int T, int lanes, int passes) {
   return b;
 }
 
-int pass_count(int bits) { return (bits + kSDigitBits - 1) / kSDigitBits; }
+int pass_count(int bits, int digit_bits = kSDigitBits) { return (bits + digit_bits - 1) / digit_bits; }
 
 // pass_count(total_bits) stable passes of balanced digit widths, least
 // significant digit first, alternating between (kout, vout) and the
 // temporaries so that the last pass lands in (kout, vout). make(shift, mask)
 // gives the pass's digit functor.
-template <typename K, int kItems, typename MakeDigit>
+template <typename K, int kItems, int B = kSDigitBits, typename MakeDigit>
 int lsd_passes(const K *kin, LanesIn vin, uint64_t n, int total_bits, K *kout, LanesOut vout, const PassBufs<K> &b,
                MakeDigit make, hipStream_t s) {
   constexpr int T = kSNT * kItems;
-  const int passes = pass_count(total_bits);
+  const int passes = pass_count(total_bits, B);
   const unsigned hist_grid = static_cast<unsigned>(
       std::min<uint64_t>((b.ntiles + kXcds - 1) / kXcds, uint64_t(device_cu_count()) * kHistPerCu / kXcds) * kXcds);
   const unsigned scat_grid = static_cast<unsigned>((b.ntiles + kXcds - 1) / kXcds * kXcds);
@@ -579,9 +609,26 @@ void partition_results(uint64_t n, const PartLanes &cols, int bits, Workspace &w
   out->off = ws.take<uint32_t>((uint64_t(1) << bits) + 1);
 }
 
+// Digit width of a partitioning. Large inputs of 4-byte keys that need one or two
+// bits more than a pass of 8 has take them in one pass of 10: its tile holds 10 items
+// per digit instead of 40 and its count table is four times as large, but a whole
+// pass over the rows goes (2^28 int32 keys with two int32 lanes, 9 bits: 2.51 +
+// 0.42 ms in scatter and histogram as two passes, 1.59 + 0.25 as one; 10 bits 2.55 +
+// 0.41 against 1.72 + 0.29; 2^27 rows with two int64 values 2.21 + 0.24 against 1.92
+// + 0.13). Digits of 11 bits need smaller tiles and gain nothing (2.58 + 0.42 ms in
+// two passes, 2.33 + 0.44 and 0.18 more in the scan in one). Small inputs keep 8
+// bits: their tiles of 4,096 items would hold 4 items per digit.
+constexpr int kWideBits = 10;
+template <typename K>
+bool wide_digit(uint64_t n, int bits) {
+  return sizeof(K) == 4 && bits > kSDigitBits && bits <= kWideBits && use_large<K>(n);
+}
+
 template <typename K>
 PassBufs<K> partition_temps(uint64_t n, const PartLanes &cols, int bits, Workspace &ws) {
-  return pass_bufs<K>(ws, n, kSNT * (use_large<K>(n) ? items_large<K>() : kItemsSmall), cols.n, pass_count(bits));
+  const int digit = wide_digit<K>(n, bits) ? kWideBits : kSDigitBits;
+  const int items = use_large<K>(n) ? items_large<K>() : kItemsSmall;
+  return pass_bufs<K>(ws, n, kSNT * items, cols.n, pass_count(bits, digit), digit);
 }
 
 template <typename K>
@@ -600,9 +647,18 @@ int partition_run(const K *keys, uint64_t n, const PartLanes &cols, int bits, Wo
       ov.dst[v] = out.words[v];
     }
     const int top = 64 - bits;
-    const auto make = [top](int shift, uint32_t mask) { return PartDigit<K>{top, shift, mask}; };
-    const int rc = use_large<K>(n) ? lsd_passes<K, items_large<K>()>(keys, in, n, bits, ok, ov, b, make, s)
-                                   : lsd_passes<K, kItemsSmall>(keys, in, n, bits, ok, ov, b, make, s);
+    const auto make = [top](int shift, uint32_t mask) { return PartDigit<K, kSDigitBits>{top, shift, mask}; };
+    int rc = EIGER_OK;
+    if (wide_digit<K>(n, bits)) {
+      if constexpr (sizeof(K) == 4)
+        rc = lsd_passes<K, items_large<K>(), kWideBits>(
+            keys, in, n, bits, ok, ov, b,
+            [top](int shift, uint32_t mask) { return PartDigit<K, kWideBits>{top, shift, mask}; }, s);
+    } else if (use_large<K>(n)) {
+      rc = lsd_passes<K, items_large<K>()>(keys, in, n, bits, ok, ov, b, make, s);
+    } else {
+      rc = lsd_passes<K, kItemsSmall>(keys, in, n, bits, ok, ov, b, make, s);
+    }
     if (rc) return rc;
   }
   EIGER_LAUNCH("part_bounds", k_part_bounds<K>, dim3(static_cast<unsigned>(std::min<uint64_t>((F + 256) / 256, 1024))),

@@ -13,7 +13,7 @@ int radix_sort_pairs(int key_bytes, const void *kin, const uint32_t *vin, uint64
 
 // Hash partitioning with value lanes: rows are ordered by partition id, the top
 // `bits` bits of the key's partition hash (part_hash), by stable passes of the same
-// sort (digits of at most 8 bits); up to kMaxLanes 32-bit lanes move along (lane w
+// sort (digits of at most 8 bits, 10 for many rows); up to kMaxLanes 32-bit lanes move along (lane w
 // of row i is src[w][i * stride[w]]; a NULL lane is the row id i itself). out receives
 // the partitioned keys, the lanes (stride 1) and off[0..2^bits] (partition p is
 // [off[p], off[p + 1])). Always lays out the workspace; enqueues only with a

@@ -148,6 +148,19 @@ def test_groupby_partition_lanes_and_passes(gpu, lanes, bits):
     check(keys, vals, eg.groupby(keys, vals, forced(keys, eg.GB_PARTITION, bits)))
 
 
+# 4-byte keys from 512 tiles of 10,240 rows on: 9 and 10 partition bits go in one
+# pass of 10-bit digits; 8 and 11 bits and one row fewer take the 8-bit passes
+@pytest.mark.parametrize("lanes", LANES[:3], ids=[x[0] for x in LANES[:3]])
+@pytest.mark.parametrize("bits,n", [(8, 5_242_880), (9, 5_242_879), (9, 5_242_880), (10, 5_253_121), (11, 5_242_880)])
+def test_groupby_partition_wide_digit(gpu, lanes, bits, n):
+    _, key_dtype, val_dtypes = lanes
+    keys, vals = synth.groupby_input(seed=bits, n=n, groups=300_000, key_dtype=key_dtype, n_vals=2,
+                                     val_dtype=torch.int64, device=gpu)
+    keys[: n // 2] = keys[0]  # one digit fills whole tiles
+    vals = [v.to(d) for v, d in zip(vals, val_dtypes)]
+    check(keys, vals, eg.groupby(keys, vals, forced(keys, eg.GB_PARTITION, bits)))
+
+
 @pytest.mark.parametrize("key_dtype", [torch.int32, torch.int64])
 def test_groupby_row_group_and_per_row_loads(gpu, key_dtype):
     # aligned columns are read four rows at a time, views one row in per row;
