@@ -205,11 +205,14 @@ template <typename K, typename PB, typename PS>
 int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   const uint64_t nslots = hash_slots(a.nR, a.plan.load_factor);
   HashCounters *hc = ws.take<HashCounters>(1);
-  JoinCounters *c = &hc->total;
   uint32_t *dup = ws.take<uint32_t>(1);
   Slot<K, PB> *slots = ws.take<Slot<K, PB>>(nslots);
+  if (!ws.base) {  // sizing: there are no counters to point at
+    *ctr = nullptr;
+    return EIGER_OK;
+  }
+  JoinCounters *c = &hc->total;
   *ctr = c;
-  if (!ws.base) return EIGER_OK;
   hipStream_t s = a.s;
   int rc;
   K sentinel;
