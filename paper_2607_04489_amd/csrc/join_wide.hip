@@ -27,13 +27,12 @@ constexpr int kMaxCols = 4;            // payload columns per side
 constexpr float kGftrMinMatch = 0.25f;  // AUTO: GFTR from this estimated match ratio up
 
 // One side's materialization: sources (column c as its low / high 32-bit word
-// arrays with a stride in words; hi null for 4-byte columns), optional map from
-// emitted position to row id, and the output columns.
+// arrays, hi null for 4-byte columns; GFUR's 8-byte columns are whole at lo), GFTR's
+// map from emitted position to row id, and the output columns.
 struct GatherSide {
   const uint32_t *rows;
   const uint32_t *lo[kMaxCols];
   const uint32_t *hi[kMaxCols];
-  uint32_t stride[kMaxCols];
   void *dst[kMaxCols];
   int n;
 };
@@ -47,18 +46,21 @@ typedef V2l V2lWord __attribute__((aligned(8)));
 
 // One side's payloads of kGRows consecutive result rows t, t + 1, ... (the first
 // `have` of them): all columns' reads are issued before any is stored.
+template <bool kMapped>
 __device__ __forceinline__ void gather_rows(const GatherSide &g, const uint32_t (&src)[kGRows], uint64_t t, int have) {
   uint64_t val[kMaxCols][kGRows];
 #pragma unroll
   for (int c = 0; c < kMaxCols; ++c) {
     if (c >= g.n) break;
     const uint32_t *lo = g.lo[c], *hi = g.hi[c];
-    if (hi && g.stride[c] == 2) {  // an 8-byte column as it is
+    if (hi) {
 #pragma unroll
-      for (int u = 0; u < kGRows; ++u) val[c][u] = reinterpret_cast<const uint64_t *>(lo)[src[u]];
-    } else if (hi) {
-#pragma unroll
-      for (int u = 0; u < kGRows; ++u) val[c][u] = (uint64_t(hi[src[u]]) << 32) | lo[src[u]];
+      for (int u = 0; u < kGRows; ++u) {
+        if constexpr (kMapped)
+          val[c][u] = (uint64_t(hi[src[u]]) << 32) | lo[src[u]];
+        else
+          val[c][u] = reinterpret_cast<const uint64_t *>(lo)[src[u]];  // an 8-byte column as it is
+      }
     } else {
 #pragma unroll
       for (int u = 0; u < kGRows; ++u) val[c][u] = lo[src[u]];
@@ -109,9 +111,13 @@ __device__ __forceinline__ void map_rows(uint32_t *__restrict__ ids, const uint3
 // the emitted (build, probe) indices, then (GFTR) the indices replaced by row ids.
 // Four consecutive rows a thread, their reads in flight together. 268M rows of a
 // GFTR join, one and two 4-byte columns: 2.01 ms (11 GB, 5.3 TB/s; 3.22 with a row at
-// a time). 121M rows of a GFUR join: 1.41 ms, 0.5 of it the random reads of the
-// build column (a 128-byte fill each, 255 G/s). Rows 64 apart in a thread, so that a
-// wave's reads are contiguous, gave 1.31 there but 2.54 above.
+// a time). 121M rows of a GFUR join: 1.24 ms, 0.5 of it the random reads of the
+// build column (a 128-byte fill each, 255 G/s); 1.41 as one kernel with the other
+// strategy, whose branches held the reads back. Rows 64 apart in a thread, so that a
+// wave's reads are contiguous: 1.30 there and 2.54 above. Writing the columns from
+// the GFTR join itself took 2.95 ms for 1.48 + 2.01: its workgroups' LDS tables leave
+// too few waves for the reads.
+template <bool kMapped>
 __global__ void __launch_bounds__(256)
     k_wide_gather(uint32_t *__restrict__ ob, uint32_t *__restrict__ op, const JoinCounters *__restrict__ ctr,
                   uint64_t cap, GatherSide R, GatherSide S) {
@@ -134,10 +140,12 @@ __global__ void __launch_bounds__(256)
         p[u] = op[u < have ? t + u : t];
       }
     }
-    gather_rows(R, b, t, have);
-    gather_rows(S, p, t, have);
-    if (R.rows) map_rows(ob, R.rows, b, t, have);
-    if (S.rows) map_rows(op, S.rows, p, t, have);
+    gather_rows<kMapped>(R, b, t, have);
+    gather_rows<kMapped>(S, p, t, have);
+    if constexpr (kMapped) {
+      map_rows(ob, R.rows, b, t, have);
+      map_rows(op, S.rows, p, t, have);
+    }
   }
 }
 
@@ -227,12 +235,10 @@ GatherSide gather_side(const eiger_column *cols, int32_t n, void *const *dst, co
     if (src) {  // transformed: one word array per lane, stride 1
       g.lo[c] = src->words[w];
       g.hi[c] = wide ? src->words[w + 1] : nullptr;
-      g.stride[c] = 1;
     } else {
       const uint32_t *base = static_cast<const uint32_t *>(cols[c].data);
       g.lo[c] = base;
       g.hi[c] = wide ? base + 1 : nullptr;
-      g.stride[c] = wide ? 2 : 1;
     }
     w += wide ? 2 : 1;
     g.dst[c] = dst ? dst[c] : nullptr;
@@ -340,8 +346,13 @@ extern "C" int eiger_join_wide(eiger_column build_keys, const eiger_column *buil
     uint64_t g = (want + 256 * kGRows - 1) / (256 * kGRows);
     const uint64_t gmax = uint64_t(device_cu_count()) * 64;
     if (g > gmax) g = gmax;
-    EIGER_LAUNCH("wide_gather", k_wide_gather, dim3(unsigned(g ? g : 1)), dim3(256), 0, s, out_build_rowid,
-                 out_probe_rowid, ctr, want, gr, gp);
+    const dim3 grid(unsigned(g ? g : 1));
+    if (tr)
+      EIGER_LAUNCH("wide_gather", k_wide_gather<true>, grid, dim3(256), 0, s, out_build_rowid, out_probe_rowid, ctr, want,
+                   gr, gp);
+    else
+      EIGER_LAUNCH("wide_gather", k_wide_gather<false>, grid, dim3(256), 0, s, out_build_rowid, out_probe_rowid, ctr, want,
+                   gr, gp);
   }
   JoinCounters host{};
   if ((rc = read_counters(plan->variant, ctr, &host, s))) return rc;
