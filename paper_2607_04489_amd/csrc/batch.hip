@@ -23,7 +23,7 @@
 // contiguous part of them (equal shares of rows), so that a join's table is built
 // and probed through one L2: random 16-byte reads run at 255 G/s from 4 MB of
 // table and at 59 G/s from 64 MB. (256 joins of 2^8..2^18 build rows, items dealt
-// to all XCDs: probe 1.81 ms; see k_batch_probe.)
+// to all XCDs: the same 1.81 ms with the probe of that time.)
 #include <algorithm>
 #include <type_traits>
 #include <vector>
@@ -257,12 +257,17 @@ struct BatchHashTab {
   __device__ __forceinline__ SlotT load(uint64_t i) const { return slots[i]; }
 };
 
-// An item's rows go to the workgroup's waves in turn.
+// An item's rows go to the workgroup's waves in turn; they write their pairs out
+// together (256 joins of 2^8..2^18 build rows: 1.11 ms; 1.19 when each wave took its
+// own output, for four times the atomics on a join's cursor; 1.81 with a row's walk
+// held to its end by its wave). Bound by the random reads of the tables that
+// exceed an XCD's L2.
 template <typename K, typename P>
 __global__ void __launch_bounds__(kBNT) k_batch_probe(XcdItems items, const BatchJoinDev *__restrict__ J,
                                                       BatchState *__restrict__ st, const Slot<K, P> *__restrict__ arena,
                                                       uint32_t *ob, uint32_t *op) {
   __shared__ WaveLds<K, P> L[kBNT / 64];
+  __shared__ WaveJoint<kBNT / 64> joint;
   const uint32_t wave = threadIdx.x / 64;
   constexpr uint64_t block = 64 * kWaveRows, sub = kBNT * kWaveRows;
   for (uint32_t it = items.begin(); it < items.end(); it += items.step()) {
@@ -276,11 +281,11 @@ __global__ void __launch_bounds__(kBNT) k_batch_probe(XcdItems items, const Batc
       const uint64_t mn = static_cast<uint64_t>(s->mn);
       const BatchDirectTab<K, P> tab{arena + d.tab_off, mn, static_cast<uint64_t>(s->mx) - mn + 1};
       WaveProbe<BatchDirectTab<K, P>, K, P> p(tab, L[wave], o);
-      p.template run<1>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, nullptr);
+      p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, joint);
     } else {
       const BatchHashTab<K, P> tab{arena + d.tab_off, d.slots - 1};
       WaveProbe<BatchHashTab<K, P>, K, P, 2> p(tab, L[wave], o);
-      p.template run<1>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, nullptr);
+      p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, joint);
     }
   }
 }
