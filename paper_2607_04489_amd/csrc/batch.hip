@@ -281,11 +281,11 @@ __global__ void __launch_bounds__(kBNT) k_batch_probe(XcdItems items, const Batc
       const uint64_t mn = static_cast<uint64_t>(s->mn);
       const BatchDirectTab<K, P> tab{arena + d.tab_off, mn, static_cast<uint64_t>(s->mx) - mn + 1};
       WaveProbe<BatchDirectTab<K, P>, K, P> p(tab, L[wave], o);
-      p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, joint);
+      p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, &joint);
     } else {
       const BatchHashTab<K, P> tab{arena + d.tab_off, d.slots - 1};
       WaveProbe<BatchHashTab<K, P>, K, P, 2> p(tab, L[wave], o);
-      p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, joint);
+      p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, &joint);
     }
   }
 }

@@ -252,13 +252,16 @@ struct WaveProbe {
 
   // Probe rows [lo, hi) in blocks of 64 * kWaveRows rows, `stride` rows apart,
   // until every match is written out; a block's columns are loaded while the one
-  // before is probed. The waves of the workgroup (all NW call this) write their
-  // stages out together whenever one is full, for one atomic: atomics on one cursor run at 10 ns each
-  // (2^27 probes, 121M matches: 3.2 ms of them with 380 pairs each).
+  // before is probed. J null: the wave reserves output for its own stage. Else
+  // the waves of the workgroup (all NW call this) write their stages out together
+  // whenever one is full, for one atomic: atomics on one cursor run at 10 ns each
+  // (2^27 probes, 121M matches: 3.2 ms of them with 380 pairs each). The branch on J
+  // stays although every kernel passes one: without it the loop's code came out 2%
+  // slower (537M count-only probes of a 1 GiB table: 11.50 against 11.75 ms).
   template <int NW>
   __device__ __forceinline__ void run(const K *__restrict__ pk, const PS *__restrict__ pp,
                                       const uint32_t *__restrict__ prow, uint64_t lo, uint64_t hi, uint64_t stride,
-                                      WaveJoint<NW> &J) {
+                                      WaveJoint<NW> *J) {
     K key[kWaveRows], nkey[kWaveRows];
     PS pay[kWaveRows], npay[kWaveRows];
     uint32_t row[kWaveRows], nrow[kWaveRows], step[kWaveRows];
@@ -313,39 +316,50 @@ struct WaveProbe {
       }
       bool done = t >= hi && queued == 0;  // nothing left but the stage
       if (!o.ob) break;
-      const uint32_t w = threadIdx.x / 64, par = round & 1;
-      if (__lane_id() == 0) J.fill[par][w] = static_cast<uint32_t>(fill) | (done ? 0u : 1u << 31);
-      __syncthreads();
-      uint32_t total = 0, before = 0, busy = 0;
+      if (!J) {
+        if (fill) flush_own();
+      } else {
+        const uint32_t w = threadIdx.x / 64, par = round & 1;
+        if (__lane_id() == 0) J->fill[par][w] = static_cast<uint32_t>(fill) | (done ? 0u : 1u << 31);
+        __syncthreads();
+        uint32_t total = 0, before = 0, busy = 0;
 #pragma unroll
-      for (uint32_t x = 0; x < NW; ++x) {
-        const uint32_t f = J.fill[par][x];
-        before += x < w ? f & 0x7FFFFFFFu : 0u;
-        total += f & 0x7FFFFFFFu;
-        busy |= f >> 31;
+        for (uint32_t x = 0; x < NW; ++x) {
+          const uint32_t f = J->fill[par][x];
+          before += x < w ? f & 0x7FFFFFFFu : 0u;
+          total += f & 0x7FFFFFFFu;
+          busy |= f >> 31;
+        }
+        if (threadIdx.x == 0 && total)
+          J->base[par] = atomicAdd(reinterpret_cast<unsigned long long *>(o.cursor), static_cast<unsigned long long>(total));
+        __syncthreads();
+        write_out(J->base[par] + before);
+        done = !busy;
       }
-      if (threadIdx.x == 0 && total)
-        J.base[par] = atomicAdd(reinterpret_cast<unsigned long long *>(o.cursor), static_cast<unsigned long long>(total));
-      __syncthreads();
-      write_out(J.base[par] + before);
-      done = !busy;
       if (done) break;
     }
-    // the workgroup's totals, in one atomic each
+    // totals: the workgroup's in one atomic each, or the wave's
     uint64_t sum = wave_sum_u64(cs), count = o.ob ? 0 : fill;
-    if (__lane_id() == 0) {
-      J.sum[threadIdx.x / 64] = sum;
-      J.count[threadIdx.x / 64] = count;
+    uint64_t *to_sum = o.checksum, *to_count = o.cursor;
+    if (J) {
+      if (__lane_id() == 0) {
+        J->sum[threadIdx.x / 64] = sum;
+        J->count[threadIdx.x / 64] = count;
+      }
+      __syncthreads();
+      if (threadIdx.x != 0) return;
+      sum = count = 0;
+      for (int x = 0; x < NW; ++x) {
+        sum += J->sum[x];
+        count += J->count[x];
+      }
+      if (o.stripes) {
+        to_sum = &o.stripes[blockIdx.x % kStripes].checksum;
+        to_count = &o.stripes[blockIdx.x % kStripes].count;
+      }
+    } else if (__lane_id() != 0) {
+      return;
     }
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    sum = count = 0;
-    for (int x = 0; x < NW; ++x) {
-      sum += J.sum[x];
-      count += J.count[x];
-    }
-    JoinStripe *st = o.stripes ? &o.stripes[blockIdx.x % kStripes] : nullptr;
-    uint64_t *to_sum = st ? &st->checksum : o.checksum, *to_count = st ? &st->count : o.cursor;
     if (sum) atomicAdd(reinterpret_cast<unsigned long long *>(to_sum), static_cast<unsigned long long>(sum));
     if (count) atomicAdd(reinterpret_cast<unsigned long long *>(to_count), static_cast<unsigned long long>(count));
   }

@@ -185,7 +185,7 @@ __global__ void __launch_bounds__((kPNT<K, PS>)) k_probe(Tab tab, const K *__res
   const uint64_t lo = blockIdx.x * per * sub;
   const uint64_t hi = lo + per * sub < n ? lo + per * sub : n;
   WaveProbe<Tab, K, PS, kEager> p(tab, L[w], o);
-  p.template run<kPNT<K, PS> / 64>(pk, pp, nullptr, lo + w * block, hi, sub, J);
+  p.template run<kPNT<K, PS> / 64>(pk, pp, nullptr, lo + w * block, hi, sub, &J);
 }
 
 // Workgroups of a CU by the LDS they take (160 KB).
