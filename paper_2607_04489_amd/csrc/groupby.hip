@@ -457,7 +457,7 @@ __global__ void __launch_bounds__(kANT, 6) k_gb_hash(const K *__restrict__ keys,
 // PARTITION: work item = one of the S equal slices of a partition (S = 1 when
 // partitions are small). A whole partition that did not spill writes its groups
 // out directly; slices and spilled partitions merge into the global table.
-// 2^28 rows, two 4-byte sums, 2^20 groups in 2^11 partitions: 0.80 ms (4.0 TB/s;
+// 2^28 rows, two 4-byte sums, 2^20 groups in 2^11 partitions: 0.75 ms (4.3 TB/s;
 // 1.78 with one row's walk at a time).
 template <typename K, int NV, bool W0, bool W1>
 __global__ void __launch_bounds__(kANT, 6)

@@ -21,7 +21,8 @@ namespace eiger {
 
 namespace {
 
-constexpr uint64_t kL2Bytes = 4u << 20;  // one XCD's L2
+// Table sizes at which the probe changes (see hash_impl).
+constexpr uint64_t kNearBytes = 8u << 20, kRowsBytes = 16u << 20, kFarBytes = 2ull << 30;
 
 // Probe workgroup: two share a CU's 160 KB of LDS.
 template <typename K, typename PS>
@@ -56,6 +57,25 @@ struct HashTab {
       if (s.key == key) f(s.rowid);
     }
   }
+};
+
+// The same table for a probe that holds each row's walk in its lane: a walk's slot
+// carries its first slot's place in the 64-byte line in bits 61 and 62.
+template <typename K, typename PB>
+struct HashRowTab : HashTab<K, PB> {
+  static constexpr bool kHashed = true;
+  static constexpr bool kRuns = false;
+  static constexpr uint64_t kPer = 64 / sizeof(Slot<K, PB>);
+  __device__ __forceinline__ uint64_t home(K key) const {
+    const uint64_t h = HashTab<K, PB>::home(key);
+    return h | (h & (kPer - 1)) << 61;
+  }
+  __device__ __forceinline__ uint64_t next(uint64_t i) const {
+    const uint64_t first = i >> 61, pos = i & this->mask, q = (pos + 1) & (kPer - 1);
+    const uint64_t line = pos - (pos & (kPer - 1)) + (q == first ? kPer : 0);
+    return (line & this->mask) | q | first << 61;
+  }
+  __device__ __forceinline__ Slot<K, PB> load(uint64_t i) const { return this->slots[i & this->mask]; }
 };
 
 // Sets *dup when some build key occurs more than once: every build row walks
@@ -188,6 +208,26 @@ __global__ void __launch_bounds__((kPNT<K, PS>)) k_probe(Tab tab, const K *__res
   p.template run<kPNT<K, PS> / 64>(pk, pp, nullptr, lo + w * block, hi, sub, &J);
 }
 
+constexpr int kRowNT = 256;
+constexpr int kRowIPT = 5;  // rows per thread
+constexpr int kRowSCAP = 4096;
+
+// Each thread holds the walks of its rows to their end, five first slots in flight.
+template <typename K, typename PB, typename PS>
+__global__ void __launch_bounds__(kRowNT) k_probe_rows(HashRowTab<K, PB> tab, const K *__restrict__ pk,
+                                                     const PS *__restrict__ pp, uint64_t n, EmitOut o) {
+  __shared__ EmitLds<kRowNT, kRowSCAP> L;
+  uint64_t fill = 0, cs = 0;
+  tab.init();
+  constexpr uint64_t sub = uint64_t(kRowNT) * kRowIPT;
+  const uint64_t nsub = (n + sub - 1) / sub;
+  const uint64_t per = (nsub + gridDim.x - 1) / gridDim.x;
+  const uint64_t lo = blockIdx.x * per * sub;
+  const uint64_t hi = lo + per * sub < n ? lo + per * sub : n;
+  probe_range<kRowNT, kRowIPT, kRowSCAP>(tab, pk, pp, static_cast<const uint32_t *>(nullptr), lo, hi, L, fill, o, cs);
+  finish(L, o, fill, cs);
+}
+
 // Workgroups of a CU by the LDS they take (160 KB).
 template <typename K, typename PS>
 constexpr int probe_per_cu() {
@@ -241,11 +281,35 @@ int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   const dim3 grid(grid_for(a.nS, uint64_t(kPNT<K, PS>) * kWaveRows, probe_per_cu<K, PS>()));
   const K *pk = static_cast<const K *>(a.pk);
   const PS *pp = static_cast<const PS *>(a.pp);
-  // A table in an XCD's L2 is bound by the L1's fills, and loading two slots of
-  // every row costs more of them than it saves (2^27 probes of a 2 MiB table: one
-  // 0.97 ms, two 1.14); from larger ones the second slot comes with the first
-  // (33.5M probes of a 64 MiB table: one 0.82 ms, two 0.72; 2^26 of 32 MiB: 1.43 and 1.28).
-  if (nslots * sizeof(Slot<K, PB>) <= kL2Bytes)
+  // Which probe (2^27 probes that all match, half-full tables, ms with pairs / count only;
+  // one and two: slots a wave loads of every row at first):
+  //   32-byte slots   8 MiB: rows 1.88/1.65 one 1.98/1.44 two 2.18/1.53
+  //                  16 MiB: rows 2.11/1.88 one 2.20/1.90 two 2.28/1.78
+  //                  64 MiB: rows 2.89/2.61 one 3.03/2.80 two 2.72/2.48
+  //                   2 GiB: rows 3.61/3.14 one 3.74/3.16 two 3.76/3.00
+  //                   4 GiB: rows 4.06/3.44 one 4.09/3.60 two 5.93/5.58
+  //   16-byte slots   2 MiB: rows 1.45/1.15 one 1.21/0.91 two 1.33/1.00
+  //                   8 MiB: rows 1.75/1.51 one 1.45/1.15 two 1.62/1.28
+  //                  16 MiB: rows 2.03/1.83 one 2.05/1.80 two 1.95/1.75
+  //                   1 GiB: rows 3.04/2.85 one 3.15/3.03 two 3.00/2.68
+  //   (8-byte keys)   1 GiB: rows 3.22/2.97 one 3.16/3.05 two 3.30/2.72
+  //                   4 GiB: rows 3.67/3.15 one 3.73/3.07 two 4.03/3.14
+  // Tables near an XCD's L2 are bound by the L1's fills, and a second slot of every row
+  // costs more of them than it saves; from larger ones it comes with the first; beyond
+  // 2 GiB two slots are two address translations in flight instead of one. With 32-byte
+  // slots the waves' LDS leaves 12 waves a CU to the 16 of the rows' probe, which shows
+  // while the table is near or very far.
+  const uint64_t bytes = nslots * sizeof(Slot<K, PB>);
+  if constexpr (sizeof(Slot<K, PB>) == 32) {
+    if (bytes > kFarBytes || (a.ob && bytes <= kRowsBytes)) {
+      HashRowTab<K, PB> rows;
+      static_cast<HashTab<K, PB> &>(rows) = tab;
+      EIGER_LAUNCH("hash_probe", (k_probe_rows<K, PB, PS>), dim3(grid_for(a.nS, uint64_t(kRowNT) * kRowIPT, 4)),
+                   dim3(kRowNT), 0, s, rows, pk, pp, a.nS, o);
+      return EIGER_OK;
+    }
+  }
+  if (bytes <= kNearBytes || bytes > kFarBytes)
     EIGER_LAUNCH("hash_probe", (k_probe<HashTab<K, PB>, K, PS, 1>), grid, dim3(kPNT<K, PS>), 0, s, tab, pk, pp, a.nS, o);
   else
     EIGER_LAUNCH("hash_probe", (k_probe<HashTab<K, PB>, K, PS, 2>), grid, dim3(kPNT<K, PS>), 0, s, tab, pk, pp, a.nS, o);

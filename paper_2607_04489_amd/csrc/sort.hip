@@ -32,10 +32,10 @@ constexpr int kSDigits = 1 << kSDigitBits;
 static_assert(kSDigits == kHNT && kSDigits <= kSNT, "one thread per digit of 8 bits");
 
 // Tiles. Large inputs: 10,240 items (6,144 of 8-byte keys): longer runs per digit
-// against registers (2^28 4-byte pairs, 32 bits, all passes: 12 items per thread
-// 5.14 ms, 16 4.89, 20 4.77, 24 6.27, where they spill; 2^27 8-byte pairs: 8 items
-// 4.63 ms, 10 3.77, 12 3.76, 16 4.00). Small inputs: 4,096 items, so that there are
-// workgroups for the chip.
+// against registers (2^28 4-byte pairs, 32 bits, all passes, with histograms
+// of 0.30 ms, now 0.25: 12 items per thread 5.14 ms, 16 4.89, 20 4.77, 24 6.27, where
+// they spill; 2^27 8-byte pairs: 8 items 4.63 ms, 10 3.77, 12 3.76, 16 4.00). Small
+// inputs: 4,096 items, so that there are workgroups for the chip.
 constexpr int kItemsSmall = 8;
 template <typename K>
 constexpr int items_large() {
@@ -366,7 +366,7 @@ __device__ __forceinline__ void scatter_tile(ScatterLds<K, kItems, D::kStore, D:
 // in LDS, write each digit's run of the tile to its global position. Keys and
 // value lanes take turns in one LDS copy of the tile, so the tile's size does not
 // depend on the row's width. Bound by memory: 2^28 4-byte pairs move 4.3 GB in
-// 0.93 ms a pass (4.6 TB/s, what a copy reaches); each XCD takes a contiguous
+// 0.86 ms a pass (5.0 TB/s; a copy: 4.6 to 4.8); each XCD takes a contiguous
 // eighth of the tiles, so that the partial lines at the ends of neighbouring
 // tiles' runs meet in one L2 (with tiles dealt round-robin: 1.5 ms).
 // One tile per workgroup: a loop over tiles made the compiler keep every item's

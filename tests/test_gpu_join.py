@@ -36,10 +36,10 @@ def test_sparse_unique64(gpu, spec):
     assert_exact(inp, run(inp, spec))
 
 
-# 131,071 and 131,072 build rows at load factor 0.5: a table of 4 MiB of 16-byte slots, whose
-# probe loads one slot of a row at first, and one of 8 MiB, whose probe loads two (32-byte
-# slots: from 65,536 rows on).
-@pytest.mark.parametrize("n_build", [65535, 65536, 131071, 131072])
+# Build rows of which one more doubles the table at load factor 0.5. 16-byte slots: 2 to
+# 16 MiB, from 16 on the probe loads two slots of a row at first; 32-byte slots: 4 to 32
+# MiB, up to 16 with pairs the rows' own probe, count-only from 16 on two slots.
+@pytest.mark.parametrize("n_build", [65535, 65536, 131071, 131072, 262143, 262144])
 @pytest.mark.parametrize("key,pay", [(torch.int32, torch.int32), (torch.int32, torch.int64), (torch.int64, torch.int64)])
 @pytest.mark.parametrize("shape", ["distinct", "repeated"])
 def test_hash_probe_paths(gpu, n_build, key, pay, shape):
