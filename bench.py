@@ -170,12 +170,16 @@ def kernel_bytes(plan, inp, count):
         b["cache_build"] = nR * (K + PB)
         b["cache_probe"] = nS * (K + PS + 4) + count * 8
     else:
-        passes = 2 if plan.radix_bits > 10 else (1 if plan.radix_bits < 2 else plan.radix_passes)
-        b["radix_hist"] = passes * (nR + nS) * K
+        # 4-byte payloads go through the radix sort's partition passes
+        lanes = PB == 4 and PS == 4
+        if lanes:
+            passes = -(-plan.radix_bits // (10 if K == 4 and plan.radix_bits <= 10 else 8))
+        else:
+            passes = 2 if plan.radix_bits > 10 else (1 if plan.radix_bits < 2 else plan.radix_passes)
+        b["sort_hist" if lanes else "radix_hist"] = passes * (nR + nS) * K
         sc = (nR * (K + PB) + nS * (K + PS)) + (nR * (K + PB + 4) + nS * (K + PS + 4))
-        if passes == 2:
-            sc += 2 * (nR * (K + PB + 4) + nS * (K + PS + 4))
-        b["radix_scatter"] = sc
+        sc += (passes - 1) * 2 * (nR * (K + PB + 4) + nS * (K + PS + 4))
+        b["sort_scatter" if lanes else "radix_scatter"] = sc
         b["radix_join"] = nR * (K + PB + 4) + nS * (K + PS + 4) + count * 8
     return b
 
