@@ -278,9 +278,11 @@ void rule_plan(const eiger_stats_t &b, const eiger_stats_t &p, eiger_plan_t *out
   const double slot = b.dtype == EIGER_INT64 ? 32.0 : 16.0;
   const double table = static_cast<double>(hash_slots(static_cast<uint64_t>(b.n), lf)) * slot;
   // 16-byte slots (4-byte keys): the partitioned join overtakes the in-place
-  // probe above a 1 GiB table (2^24 distinct build rows, a 1 GiB table: 8.3 vs
-  // 8.2 ms; 2^26 rows, 4 GiB: 16.9 vs 12.3 ms, probe side 2^28 rows); 32-byte
-  // slots keep the in-place probe up to the whole budget
+  // probe above a 1 GiB table with the join's own partition passes, which 8-byte
+  // payloads take (2^24 distinct build rows, a 1 GiB table: 8.0 vs 8.3 ms; 2^26
+  // rows, 4 GiB: 15.0 vs 12.0 ms, probe side 2^28 rows), and the statistics do not
+  // tell the payloads' width; through the radix sort's passes 4-byte payloads are
+  // ahead from 2^22 rows (6.3 vs 5.4; 7.8 vs 5.5; 14.9 vs 9.4). 32-byte slots keep the in-place probe up to the whole budget
   const double budget = b.dtype == EIGER_INT64 ? kHashTableBudget : kHashTableBudget / 4;
   if (table <= budget && (!duplicated || table <= 64.0 * 1024 * 1024)) {
     out->variant = EIGER_GLOBAL_HASH;

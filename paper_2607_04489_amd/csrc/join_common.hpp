@@ -27,7 +27,7 @@ struct alignas((sizeof(K) + sizeof(P) + 4 <= 16) ? 16 : 32) Slot {
 // Probe sequence of the open-addressing tables in device memory (power-of-two
 // slots): the slots of the home slot's 64 bytes, wrapping inside them, then the
 // next 64 bytes', and so on, so that the second slot costs no second memory access
-// (2^28 probes of a 1 GiB table of 32-byte slots, two slots a step: 5.78 ms; in
+// (2^28 probes of a 2 GiB table of 32-byte slots, two slots a step: 5.78 ms; in
 // 128-byte groups 6.09; first slot and then plain linear probing 6.12).
 template <typename SlotT>
 __device__ __forceinline__ uint64_t line_walk(uint64_t home, uint32_t steps, uint64_t mask) {
@@ -257,7 +257,7 @@ struct WaveProbe {
   // whenever one is full, for one atomic: atomics on one cursor run at 10 ns each
   // (2^27 probes, 121M matches: 3.2 ms of them with 380 pairs each). The branch on J
   // stays although every kernel passes one: without it the loop's code came out 2%
-  // slower (537M count-only probes of a 1 GiB table: 11.50 against 11.75 ms).
+  // slower (537M count-only probes of a 2 GiB table: 11.50 against 11.75 ms).
   template <int NW>
   __device__ __forceinline__ void run(const K *__restrict__ pk, const PS *__restrict__ pp,
                                       const uint32_t *__restrict__ prow, uint64_t lo, uint64_t hi, uint64_t stride,
