@@ -14,6 +14,8 @@
 //     bound of its last code) once, and every probe row binary-searches only
 //     that window; a key's build rows are one contiguous run of the sorted build
 //     side, emitted straight from it.
+#include <algorithm>
+
 #include "join_common.hpp"
 #include "sort.hpp"
 #include "variants.hpp"
@@ -149,12 +151,18 @@ int smj_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr, uint64_t span
   uint32_t *ridR = ws.take<uint32_t>(a.nR);
   U *uS = ws.take<U>(a.nS), *uSs = ws.take<U>(a.nS);
   uint32_t *ridS = ws.take<uint32_t>(a.nS);
-  // one region for both sorts (they run one after the other on the stream); the
-  // gathered payloads, written after the sorts, lie in the same place
-  Workspace probe_size(nullptr, 0);
-  radix_sort_pairs(sizeof(U), nullptr, nullptr, std::max(a.nR, a.nS), bits, nullptr, nullptr, probe_size, nullptr);
+  // one region for both sorts (they run one after the other on the stream), sized for
+  // each: a sort's tiles, and so its count table, change with its row count, and
+  // the smaller side may need more. The gathered payloads, written after the sorts,
+  // lie in the same place
+  size_t sort_bytes = 0;
+  for (const uint64_t n : {a.nR, a.nS}) {
+    Workspace need(nullptr, 0);
+    radix_sort_pairs(sizeof(U), nullptr, nullptr, n, bits, nullptr, nullptr, need, nullptr);
+    sort_bytes = std::max(sort_bytes, need.used + 256);
+  }
   Workspace pay = ws;
-  char *sort_ws = ws.take<char>(probe_size.used + 256);
+  char *sort_ws = ws.take<char>(sort_bytes);
   PB *payR = pay.take<PB>(a.nR);
   PS *payS = pay.take<PS>(a.nS);
   ws.used = std::max(ws.used, pay.used);
@@ -170,11 +178,11 @@ int smj_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr, uint64_t span
   EIGER_LAUNCH("smj_encode", (k_smj_encode<K, U>), dim3(smj_grid(a.nS, 256 * 4, 8)), dim3(256), 0, s,
                static_cast<const K *>(a.pk), a.nS, min, span, false, uS, &c->flags);
   {
-    Workspace sw(sort_ws, probe_size.used + 256);
+    Workspace sw(sort_ws, sort_bytes);
     if ((rc = radix_sort_pairs(sizeof(U), uR, nullptr, a.nR, bits, uRs, ridR, sw, s))) return rc;
   }
   {
-    Workspace sw(sort_ws, probe_size.used + 256);
+    Workspace sw(sort_ws, sort_bytes);
     if ((rc = radix_sort_pairs(sizeof(U), uS, nullptr, a.nS, bits, uSs, ridS, sw, s))) return rc;
   }
   EIGER_LAUNCH("smj_gather", (k_smj_gather<PB>), dim3(smj_grid(a.nR, 256 * 4, 8)), dim3(256), 0, s, ridR, a.nR,

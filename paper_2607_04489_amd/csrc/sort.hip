@@ -563,6 +563,7 @@ int sort_impl(const K *kin, const uint32_t *vin, uint64_t n, int key_bits, K *ko
   const bool large = use_large<K>(n);
   const PassBufs<K> b = pass_bufs<K>(ws, n, kSNT * (large ? items_large<K>() : kItemsSmall), 1, 2);
   if (!ws.base || n == 0) return EIGER_OK;
+  if (ws.used > ws.cap) return fail(EIGER_ERR_WORKSPACE, "radix sort: its temporaries exceed the region given");
   if (key_bits == 0 || n == 1) {
     const unsigned grid = static_cast<unsigned>(std::min<uint64_t>((n + 255) / 256, 4096));
     EIGER_LAUNCH("sort_copy", k_sort_copy<K>, dim3(grid), dim3(256), 0, s, kin, vin, n, kout, vout);
@@ -635,6 +636,7 @@ template <typename K>
 int partition_run(const K *keys, uint64_t n, const PartLanes &cols, int bits, Workspace &ws, const PartitionOut &out,
                   hipStream_t s) {
   const PassBufs<K> b = partition_temps<K>(n, cols, bits, ws);
+  if (ws.used > ws.cap) return fail(EIGER_ERR_WORKSPACE, "radix partition: its temporaries exceed the region given");
   const uint32_t F = 1u << bits;
   K *ok = static_cast<K *>(out.keys);
   if (n > 0) {
