@@ -16,7 +16,8 @@
  *    host memory owned by the caller.
  *  - Scratch memory is the caller's: size it with the *_workspace_size call
  *    and pass it as (ws, ws_bytes). Its contents on entry do not matter and
- *    are unspecified on return.
+ *    are unspecified on return. The sizes do not fall as row counts rise (the
+ *    other arguments alike), so a workspace sized for the most rows takes fewer.
  *  - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *    Work is ordered on that stream. Calls that return host values
  *    synchronize the stream before returning.

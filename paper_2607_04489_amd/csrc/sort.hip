@@ -44,8 +44,12 @@ constexpr int items_large() {
 // Large tiles from this many of them on (two per CU).
 constexpr uint64_t kLargeTiles = 512;
 template <typename K>
+constexpr uint64_t large_rows() {
+  return kLargeTiles * kSNT * items_large<K>();
+}
+template <typename K>
 bool use_large(uint64_t n) {
-  return n >= kLargeTiles * kSNT * items_large<K>();
+  return n >= large_rows<K>();
 }
 // Up to this many tiles the scatter's workgroups sum the count table's columns
 // themselves instead of three scan launches.
@@ -498,6 +502,18 @@ PassBufs<K> pass_bufs(Workspace &ws, uint64_t n, int T, int lanes, int passes, i
 
 int pass_count(int bits, int digit_bits = kSDigitBits) { return (bits + digit_bits - 1) / digit_bits; }
 
+// Raises ws, which held `from` bytes before a layout for n rows, to what the most rows
+// in small tiles take there: larger tiles need fewer counts and a wider digit fewer
+// passes, and a workspace sized for many rows is to take every smaller input.
+template <typename K>
+void at_least_small(Workspace &ws, size_t from, uint64_t n, int lanes, int passes) {
+  if (!use_large<K>(n)) return;
+  Workspace small(nullptr, 0);
+  small.used = from;
+  pass_bufs<K>(small, large_rows<K>() - 1, kSNT * kItemsSmall, lanes, passes);
+  ws.used = std::max(ws.used, small.used);
+}
+
 // pass_count(total_bits) stable passes of balanced digit widths, least
 // significant digit first, alternating between (kout, vout) and the
 // temporaries so that the last pass lands in (kout, vout). make(shift, mask)
@@ -561,7 +577,9 @@ template <typename K>
 int sort_impl(const K *kin, const uint32_t *vin, uint64_t n, int key_bits, K *kout, uint32_t *vout, Workspace &ws,
               hipStream_t s) {
   const bool large = use_large<K>(n);
+  const size_t from = ws.used;
   const PassBufs<K> b = pass_bufs<K>(ws, n, kSNT * (large ? items_large<K>() : kItemsSmall), 1, 2);
+  at_least_small<K>(ws, from, n, 1, 2);
   if (!ws.base || n == 0) return EIGER_OK;
   if (ws.used > ws.cap) return fail(EIGER_ERR_WORKSPACE, "radix sort: its temporaries exceed the region given");
   if (key_bits == 0 || n == 1) {
@@ -697,8 +715,16 @@ int radix_partition_run(int key_bytes, const void *keys, uint64_t n, const PartL
 int radix_partition_lanes(int key_bytes, const void *keys, uint64_t n, const PartLanes &cols, int bits, Workspace &ws,
                           PartitionOut *out, hipStream_t s, bool run) {
   if (int rc = radix_partition_results(key_bytes, n, cols, bits, ws, out)) return rc;
-  if (ws.base && run) return radix_partition_run(key_bytes, keys, n, cols, bits, ws, *out, s);
-  radix_partition_temps(key_bytes, n, cols, bits, ws);
+  const size_t from = ws.used;
+  if (ws.base && run) {
+    if (int rc = radix_partition_run(key_bytes, keys, n, cols, bits, ws, *out, s)) return rc;
+  } else {
+    radix_partition_temps(key_bytes, n, cols, bits, ws);
+  }
+  if (key_bytes == 8)
+    at_least_small<int64_t>(ws, from, n, cols.n, pass_count(bits));
+  else
+    at_least_small<int32_t>(ws, from, n, cols.n, pass_count(bits));
   return EIGER_OK;
 }
 

@@ -18,8 +18,8 @@ int radix_sort_pairs(int key_bytes, const void *kin, const uint32_t *vin, uint64
 // sort (digits of at most 8 bits, 10 for many rows); up to kMaxLanes 32-bit lanes move along (lane w
 // of row i is src[w][i * stride[w]]; a NULL lane is the row id i itself). out receives
 // the partitioned keys, the lanes (stride 1) and off[0..2^bits] (partition p is
-// [off[p], off[p + 1])). Always lays out the workspace; enqueues only with a
-// workspace base and `run`.
+// [off[p], off[p + 1])). Always lays out the workspace, whose size rises with n;
+// enqueues only with a workspace base and `run`.
 constexpr int kMaxLanes = 9;  // a row id and eight payload words
 struct PartLanes {
   const uint32_t *src[kMaxLanes];
@@ -34,8 +34,9 @@ struct PartitionOut {
 int radix_partition_lanes(int key_bytes, const void *keys, uint64_t n, const PartLanes &cols, int bits, Workspace &ws,
                           PartitionOut *out, hipStream_t s, bool run);
 // The same in parts, so that partitionings that run one after another can share
-// their temporaries: lay out the results, lay out the temporaries (sizing), enqueue
-// (laying out the same temporaries in ws).
+// their temporaries: lay out the results, lay out the temporaries (sizing; no more
+// than they take, which may be less for more rows), enqueue (laying out the same
+// temporaries in ws).
 int radix_partition_results(int key_bytes, uint64_t n, const PartLanes &cols, int bits, Workspace &ws, PartitionOut *out);
 void radix_partition_temps(int key_bytes, uint64_t n, const PartLanes &cols, int bits, Workspace &ws);
 int radix_partition_run(int key_bytes, const void *keys, uint64_t n, const PartLanes &cols, int bits, Workspace &ws,
