@@ -27,6 +27,8 @@ namespace {
 constexpr int kMNT = 256;
 constexpr int kMIPT = 8;
 constexpr int kMSCAP = 4096;
+template <typename U>
+constexpr int kSizedTile = sizeof(U) == 8 ? 4096 : 8192;
 
 template <typename K, typename U>
 __global__ void __launch_bounds__(256) k_smj_encode(const K *__restrict__ keys, uint64_t n, uint64_t min,
@@ -151,21 +153,25 @@ int smj_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr, uint64_t span
   uint32_t *ridR = ws.take<uint32_t>(a.nR);
   U *uS = ws.take<U>(a.nS), *uSs = ws.take<U>(a.nS);
   uint32_t *ridS = ws.take<uint32_t>(a.nS);
-  // one region for both sorts (they run one after the other on the stream), sized for
-  // each: a sort's tiles, and so its count table, change with its row count, and
-  // the smaller side may need more. The gathered payloads, written after the sorts,
-  // lie in the same place
-  size_t sort_bytes = 0;
-  for (const uint64_t n : {a.nR, a.nS}) {
+  // One region: both sorts' temporaries (they run one after the other on the stream),
+  // then the gathered payloads. Its size is that of the payload arrays beside a sort of
+  // the larger side in tiles of kSizedTile codes, whatever tiles the sort takes: the
+  // joins that a fixed scratch array holds (eiger_join_noalloc) stay the same ones. The
+  // payloads' room is more than a sort in smaller tiles takes beyond that.
+  Workspace pay(nullptr, 0);
+  pay.take<PB>(a.nR);
+  pay.take<PS>(a.nS);
+  pay.take<char>(radix_sort_bytes(sizeof(U), std::max(a.nR, a.nS), kSizedTile<U>) + 256);
+  size_t region = pay.used;
+  for (const uint64_t n : {a.nR, a.nS}) {  // (each: the smaller side's sort may need more)
     Workspace need(nullptr, 0);
     radix_sort_pairs(sizeof(U), nullptr, nullptr, n, bits, nullptr, nullptr, need, nullptr);
-    sort_bytes = std::max(sort_bytes, need.used + 256);
+    region = std::max(region, need.used);
   }
-  Workspace pay = ws;
-  char *sort_ws = ws.take<char>(sort_bytes);
+  char *sort_ws = ws.take<char>(region);
+  pay = Workspace(sort_ws, region);
   PB *payR = pay.take<PB>(a.nR);
   PS *payS = pay.take<PS>(a.nS);
-  ws.used = std::max(ws.used, pay.used);
   *ctr = c;
   if (!ws.base) return EIGER_OK;
   hipStream_t s = a.s;
@@ -178,11 +184,11 @@ int smj_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr, uint64_t span
   EIGER_LAUNCH("smj_encode", (k_smj_encode<K, U>), dim3(smj_grid(a.nS, 256 * 4, 8)), dim3(256), 0, s,
                static_cast<const K *>(a.pk), a.nS, min, span, false, uS, &c->flags);
   {
-    Workspace sw(sort_ws, sort_bytes);
+    Workspace sw(sort_ws, region);
     if ((rc = radix_sort_pairs(sizeof(U), uR, nullptr, a.nR, bits, uRs, ridR, sw, s))) return rc;
   }
   {
-    Workspace sw(sort_ws, sort_bytes);
+    Workspace sw(sort_ws, region);
     if ((rc = radix_sort_pairs(sizeof(U), uS, nullptr, a.nS, bits, uSs, ridS, sw, s))) return rc;
   }
   EIGER_LAUNCH("smj_gather", (k_smj_gather<PB>), dim3(smj_grid(a.nR, 256 * 4, 8)), dim3(256), 0, s, ridR, a.nR,

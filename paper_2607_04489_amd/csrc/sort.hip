@@ -737,6 +737,15 @@ int radix_sort_pairs(int key_bytes, const void *kin, const uint32_t *vin, uint64
                              vout, ws, s);
 }
 
+size_t radix_sort_bytes(int key_bytes, uint64_t n, int tile) {
+  Workspace ws(nullptr, 0);
+  if (key_bytes == 8)
+    pass_bufs<uint64_t>(ws, n, tile, 1, 2);
+  else
+    pass_bufs<uint32_t>(ws, n, tile, 1, 2);
+  return ws.used;
+}
+
 }  // namespace eiger
 
 using namespace eiger;

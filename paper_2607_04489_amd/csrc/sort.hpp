@@ -13,6 +13,9 @@ namespace eiger {
 int radix_sort_pairs(int key_bytes, const void *kin, const uint32_t *vin, uint64_t n, int key_bits, void *kout,
                      uint32_t *vout, Workspace &ws, hipStream_t s);
 
+// Bytes of the temporaries of such a sort in tiles of `tile` pairs (sizing only).
+size_t radix_sort_bytes(int key_bytes, uint64_t n, int tile);
+
 // Hash partitioning with value lanes: rows are ordered by partition id, the top
 // `bits` bits of the key's partition hash (part_hash), by stable passes of the same
 // sort (digits of at most 8 bits, 10 for many rows); up to kMaxLanes 32-bit lanes move along (lane w

@@ -61,6 +61,23 @@ def test_sort_merge_workspace_holds_both_sorts(lib, code_bytes, bdt, pdt):
                     assert size - kept >= sort_size(lib, code_bytes, n), (n_build, n_probe, n)
 
 
+@pytest.mark.parametrize("n,payload,fits", [(1_600_000, eg.INT32, True), (1_680_000, eg.INT32, False),
+                                            (1_900_000, eg.INT32, False), (1_380_000, eg.INT64, True), (1_410_000, eg.INT64, False)])
+def test_noalloc_takes_the_same_sort_merge_joins(lib, n, payload, fits):
+    """The 64 MiB scratch array holds the code and row-id arrays, the payloads and one
+    sort beside them (40.1 or 48.1 bytes a row of each side); what is larger is refused on
+    the host."""
+    size = join_size(lib, eg.SORT_MERGE, eg.INT32, payload, payload, n, n, 1 << 20)
+    assert (size <= eg.NOALLOC_SCRATCH_BYTES) == fits
+    if not fits:
+        plan = eg.PlanT()
+        plan.variant, plan.key_dtype, plan.build_max, plan.load_factor = eg.SORT_MERGE, eg.INT32, 1 << 20, 0.5
+        k, p = eg.Column(4096, n, eg.INT32, 0), eg.Column(4096, n, payload, 0)
+        cnt, cs = ctypes.c_int64(), ctypes.c_int64()
+        assert lib.eiger_join_noalloc(k, p, k, p, ctypes.byref(plan), None, None, 0, ctypes.byref(cnt), ctypes.byref(cs),
+                                      None) == eg.EIGER_ERR_TOO_LARGE
+
+
 def rising(sizes):
     return all(a <= b for a, b in zip(sizes, sizes[1:]))
 
