@@ -267,7 +267,8 @@ typedef struct {
     int32_t key_dtype;
     uint32_t flags;           /* EIGER_GB_* */
     int64_t slots;            /* slots of the global group table (power of two >= 1024) */
-    int64_t predicted_groups; /* the distinct-count estimate the plan used */
+    int64_t predicted_groups; /* the distinct-count estimate the plan used; HASH shapes its LDS
+                                 tables for it at first (a wrong one costs time only) */
     int64_t sentinel;         /* a value no key takes: marks empty slots */
     int64_t reserved[2];
 } eiger_groupby_plan_t;

@@ -131,6 +131,10 @@ struct AggShape {
   uint32_t slots, reps, shift;  // slots * reps = kGLds; shift = 32 - log2(slots)
 };
 
+// The whole table, one accumulator a slot.
+__host__ __device__ __forceinline__ AggShape agg_whole() { return AggShape{kGLds, 1, 21}; }
+static_assert(kGLds == 1u << 11, "agg_whole's shift");
+
 // slots: four per expected group
 AggShape agg_shape(double groups) {
   AggShape h{64, 0, 26};
@@ -167,27 +171,28 @@ __device__ __forceinline__ void agg_clear(AggLds<NV, W0> &L, AggOwn<NV> &own, un
 }
 
 // LDS slot of key k, from slot s on, claiming an empty slot while the table takes
-// new groups; -1: not in the table and the table is closed (the row goes global).
+// new groups; kAMiss: not in the table and the table is closed.
+constexpr uint32_t kAMiss = 0xFFFFFFFFu, kASkip = 0xFFFFFFFEu;
 template <int NV, bool W0>
-__device__ __forceinline__ int agg_slot(AggLds<NV, W0> &L, uint32_t slots, uint32_t s, unsigned long long k,
+__device__ __forceinline__ uint32_t agg_slot(AggLds<NV, W0> &L, uint32_t slots, uint32_t s, unsigned long long k,
                                         unsigned long long sentinel) {
   for (uint32_t step = 0; step < slots; ++step) {
     const unsigned long long cur = __atomic_load_n(&L.key[s], __ATOMIC_RELAXED);
-    if (cur == k) return static_cast<int>(s);
+    if (cur == k) return s;
     if (cur == sentinel) {
       // closed for new groups once half the slots were claimed; claims racing with the
       // last one can add at most one per thread of the workgroup
-      if (__atomic_load_n(&L.used, __ATOMIC_RELAXED) >= slots / 2) return -1;
+      if (__atomic_load_n(&L.used, __ATOMIC_RELAXED) >= slots / 2) return kAMiss;
       const unsigned long long old = atomicCAS(&L.key[s], sentinel, k);
       if (old == sentinel) {
         atomicAdd(&L.used, 1u);
-        return static_cast<int>(s);
+        return s;
       }
-      if (old == k) return static_cast<int>(s);
+      if (old == k) return s;
     }
     s = (s + 1) & (slots - 1);
   }
-  return -1;
+  return kAMiss;
 }
 
 typedef uint32_t V4u __attribute__((ext_vector_type(4)));
@@ -249,18 +254,21 @@ struct AggCol {
   }
 };
 
-// Aggregate rows [lo, hi) (at most kAFold of them) into the LDS table; rows that
-// do not fit go global. Uniform across the workgroup.
-template <typename K, int NV, bool W0, bool W1, bool kSplit>
-__device__ __forceinline__ void agg_rows(AggLds<NV, W0> &L, const AggShape &h, const GbGlobal &g,
-                                         const K *__restrict__ keys, const GbVals &vals, uint64_t lo, uint64_t hi) {
+// Aggregate this wave's rows of the steps of [lo, hi) (at most kAFold rows) into the
+// LDS table; rows that do not fit go global. kGrow: while a larger table can be
+// taken, a wave stops instead, before the step in which a row of its does not fit (the
+// keys that the step entered stay, with no row yet). Returns where the wave stopped.
+template <typename K, int NV, bool W0, bool W1, bool kSplit, bool kGrow>
+__device__ __forceinline__ uint64_t agg_rows(AggLds<NV, W0> &L, const AggShape &h, const GbGlobal &g,
+                                             const K *__restrict__ keys, const GbVals &vals, uint64_t lo, uint64_t hi) {
   const uint32_t rep = __lane_id() & (h.reps - 1);
   const uint32_t *kw = reinterpret_cast<const uint32_t *>(keys);
   for (uint64_t base = lo; base < hi; base += kAStep) {
     AggCol<sizeof(K) == 8, false> kc;
     AggCol<W0, kSplit> c0;
     AggCol<W1, kSplit> c1;
-    if (base + kAStep <= hi) {
+    const bool full = base + kAStep <= hi;
+    if (full) {
       kc.load_full(kw, nullptr, base);
       if constexpr (NV > 0) c0.load_full(vals.lo[0], vals.hi[0], base);
       if constexpr (NV > 1) c1.load_full(vals.lo[1], vals.hi[1], base);
@@ -275,7 +283,7 @@ __device__ __forceinline__ void agg_rows(AggLds<NV, W0> &L, const AggShape &h, c
     uint32_t slot[kARows];
 #pragma unroll
     for (int q = 0; q < kARows; ++q) {
-      k[q] = kc.sext64(q);
+      k[q] = full || base + (q / 4 * kANT + threadIdx.x) * 4 + q % 4 < hi ? kc.sext64(q) : g.sentinel;
       slot[q] = agg_hash(k[q], h.shift);
       at[q] = __atomic_load_n(&L.key[slot[q]], __ATOMIC_RELAXED);
     }
@@ -292,21 +300,33 @@ __device__ __forceinline__ void agg_rows(AggLds<NV, W0> &L, const AggShape &h, c
 #pragma unroll
       for (int q = 0; q < kARows; ++q) at[q] = __atomic_load_n(&L.key[slot[q]], __ATOMIC_RELAXED);
     }
+    // rows past the end, and keys new to the workgroup
+    bool odd = false;
+#pragma unroll
+    for (int q = 0; q < kARows; ++q) odd |= at[q] != k[q] || k[q] == g.sentinel;
+    if (__any(odd)) {
+      bool miss = false;
+#pragma unroll
+      for (int q = 0; q < kARows; ++q) {
+        if (k[q] == g.sentinel)  // (no key equals the sentinel)
+          slot[q] = kASkip;
+        else if (at[q] != k[q])
+          slot[q] = agg_slot<NV, W0>(L, h.slots, slot[q], k[q], g.sentinel);
+        miss |= slot[q] == kAMiss;
+      }
+      if (kGrow && h.slots < kGLds && __any(miss)) return base;
+    }
 #pragma unroll
     for (int q = 0; q < kARows; ++q) {
-      // past the end (no key equals the sentinel)
-      if (base + (q / 4 * kANT + threadIdx.x) * 4 + q % 4 >= hi || k[q] == g.sentinel) continue;
-      int s = static_cast<int>(slot[q]);
-      if (at[q] != k[q]) s = agg_slot<NV, W0>(L, h.slots, slot[q], k[q], g.sentinel);
-      if (s >= 0) {
-        const uint32_t i = static_cast<uint32_t>(s) * h.reps + rep;
+      if (slot[q] < kGLds) {
+        const uint32_t i = slot[q] * h.reps + rep;
         if constexpr (kPacked<NV, W0>)
           atomicAdd(&L.a[i], (1ull << 48) | (static_cast<uint32_t>(c0.v[q]) ^ 0x80000000u));
         else
           atomicAdd(&L.c[i], 1u);
         if constexpr (NV > 0 && W0) atomicAdd(&L.a[i], c0.sext64(q));
         if constexpr (NV > 1) atomicAdd(&L.b[i], c1.sext64(q));
-      } else {
+      } else if (slot[q] == kAMiss) {
         L.spilled = 1;
         unsigned long long sv[kGMaxVals] = {0, 0};
         if constexpr (NV > 0) sv[0] = c0.sext64(q);
@@ -315,12 +335,16 @@ __device__ __forceinline__ void agg_rows(AggLds<NV, W0> &L, const AggShape &h, c
       }
     }
   }
+  return hi;
 }
 
 // Accumulators into the owners' registers, cleared for the rows to come. Barriers.
+// Returns whether the table takes no new groups although a larger one would (the same
+// for all waves: none takes a row between the barriers).
 template <int NV, bool W0>
-__device__ __forceinline__ void agg_fold(AggLds<NV, W0> &L, const AggShape &h, AggOwn<NV> &own) {
+__device__ __forceinline__ bool agg_fold(AggLds<NV, W0> &L, const AggShape &h, AggOwn<NV> &own) {
   __syncthreads();
+  const bool closed = h.slots < kGLds && L.used >= h.slots / 2;
 #pragma unroll
   for (int j = 0; j < kAOwn; ++j) {
     const uint32_t s = threadIdx.x + j * kANT;
@@ -347,6 +371,7 @@ __device__ __forceinline__ void agg_fold(AggLds<NV, W0> &L, const AggShape &h, A
     }
   }
   __syncthreads();
+  return closed;
 }
 
 // The folded groups into the global table.
@@ -355,7 +380,7 @@ __device__ __forceinline__ void agg_merge(AggLds<NV, W0> &L, const AggShape &h, 
 #pragma unroll
   for (int j = 0; j < kAOwn; ++j) {
     const uint32_t s = threadIdx.x + j * kANT;
-    if (s >= h.slots || L.key[s] == g.sentinel) continue;
+    if (s >= h.slots || L.key[s] == g.sentinel || own.cnt[j] == 0) continue;
     unsigned long long sv[kGMaxVals] = {0, 0};
     for (int v = 0; v < NV; ++v) sv[v] = own.s[v][j];
     global_add(g, L.key[s], own.cnt[j], sv, NV);
@@ -436,7 +461,12 @@ __global__ void __launch_bounds__(kGNT) k_gb_clear(GbGlobal g, int nv, unsigned 
   }
 }
 
-// HASH: a contiguous range of rows per workgroup, LDS aggregation, one merge.
+// HASH: a contiguous range of rows per workgroup, LDS aggregation, one merge. `h` is
+// the table's shape from the plan's estimate; a workgroup that meets more groups than
+// that takes merges what it has and goes on with the whole table, so that a low
+// estimate costs one more merge and not a global atomic per row (2^26 rows, two 4-byte
+// sums, 1,000 groups planned as one: 0.43 ms, 12.5 while every row that did not fit went
+// global; planned as 1,000: 0.39).
 // 2^28 rows, two 4-byte sums, 100 groups: 0.56 ms (5.8 TB/s; 1.47 with register
 // groups and three 64-bit LDS atomics a row); 1,000 groups: 0.91 ms (2.94), the
 // walks in the half-full table.
@@ -447,9 +477,19 @@ __global__ void __launch_bounds__(kANT, 6) k_gb_hash(const K *__restrict__ keys,
   AggOwn<NV> own;
   const uint64_t lo = uint64_t(blockIdx.x) * per, hi = min(n, lo + per);
   agg_clear<NV, W0>(L, own, g.sentinel);
-  for (uint64_t c = lo; c < hi; c += kAFold) {
-    agg_rows<K, NV, W0, W1, false>(L, h, g, keys, vals, c, min(hi, c + kAFold));
-    agg_fold<NV, W0>(L, h, own);
+  uint64_t at = lo, end = min(hi, lo + kAFold);  // this wave's next step; the next fold (for all waves)
+  for (;;) {
+    at = agg_rows<K, NV, W0, W1, false, true>(L, h, g, keys, vals, at, end);
+    if (agg_fold<NV, W0>(L, h, own)) {
+      agg_merge<NV, W0>(L, h, own, g);
+      __syncthreads();
+      h = agg_whole();
+      agg_clear<NV, W0>(L, own, g.sentinel);
+      continue;
+    }
+    if (end >= hi) break;
+    at = end;
+    end = min(hi, end + kAFold);
   }
   agg_merge<NV, W0>(L, h, own, g);
 }
@@ -473,7 +513,7 @@ __global__ void __launch_bounds__(kANT, 6)
     if (lo == hi) continue;
     agg_clear<NV, W0>(L, own, g.sentinel);
     for (uint64_t c = lo; c < hi; c += kAFold) {
-      agg_rows<K, NV, W0, W1, true>(L, h, g, keys, vals, c, min(hi, c + kAFold));
+      agg_rows<K, NV, W0, W1, true, false>(L, h, g, keys, vals, c, min(hi, c + kAFold));
       agg_fold<NV, W0>(L, h, own);
     }
     if (L.spilled || S > 1) {
@@ -652,7 +692,7 @@ int gb_impl(const eiger_column &keys, const eiger_column *vals, int32_t nv, cons
       if (vals[c].dtype == EIGER_INT64) call.vals.hi[c] = part.words[w++];
     }
     const uint32_t F = 1u << plan.radix_bits;
-    call.shape = agg_shape(kGLds);  // unevenly filled partitions: the whole table
+    call.shape = agg_whole();  // unevenly filled partitions
     if ((rc = run_agg_partition<K>(call, nv, w0, w1, static_cast<const K *>(part.keys), part.off, F,
                                    gb_slices(n, plan.radix_bits), o)))
       return rc;

@@ -88,6 +88,50 @@ def test_groupby_packed_sums_at_their_bounds(gpu, value):
     assert got == {3: (n - 1, (n - 1) * value, (n - 1) * value), 4: (1, value, value)}
 
 
+@pytest.mark.parametrize("n", [2047, 2049, 5_000_011])
+@pytest.mark.parametrize("vals", [(), (torch.int32, torch.int64), (torch.int64,)], ids=["count", "i32_i64", "i64"])
+@pytest.mark.parametrize("order", ["random", "ascending", "late"])
+@pytest.mark.parametrize("predicted,groups", [(0, 1000), (1, 33), (100, 513), (400, 1024), (1, 5000)])
+def test_groupby_hash_with_a_low_estimate(gpu, n, vals, order, predicted, groups):
+    """A plan kept for other data: the workgroups meet more groups than their LDS tables
+    were shaped for, from the first rows on, one after another, or after most rows."""
+    gid = torch.randint(0, groups, (n,), generator=torch.Generator().manual_seed(n))
+    if order == "ascending":
+        gid = gid.sort().values
+    elif order == "late":
+        gid[: n * 3 // 4] = 0
+    keys = (gid * 2654435761 % (1 << 31)).to(torch.int32).to(gpu)
+    cols = [synth.groupby_input(seed=c, n=n, groups=1, n_vals=1, val_dtype=t, device=gpu)[1][0] for c, t in enumerate(vals)]
+    plan = forced(keys, eg.GB_HASH)
+    plan.predicted_groups = predicted
+    check(keys, cols, eg.groupby(keys, cols, plan, capacity=groups))
+
+
+def best_time(*calls):
+    """The fastest of ten runs of each call, in turn, in ms."""
+    best = [float("inf")] * len(calls)
+    for _ in range(11):
+        for c, f in enumerate(calls):
+            start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            f()
+            stop.record()
+            stop.synchronize()
+            best[c] = min(best[c], start.elapsed_time(stop))
+    return best
+
+
+def test_groupby_hash_time_does_not_hang_on_the_estimate(gpu):
+    """1,000 groups planned as one: each workgroup merges once more, rows do not go to
+    global atomics one by one (which took 25 times as long)."""
+    keys, vals = synth.groupby_input(seed=1, n=1 << 25, groups=1000, n_vals=2, device=gpu)
+    plan = forced(keys, eg.GB_HASH)
+    low = forced(keys, eg.GB_HASH)
+    low.predicted_groups = 1
+    t, t_low = best_time(lambda: eg.groupby(keys, vals, plan), lambda: eg.groupby(keys, vals, low, capacity=1000))
+    assert t_low < 3 * t, (t_low, t)
+
+
 def test_groupby_rule_follows_the_estimate(gpu):
     small, sv = synth.groupby_input(seed=1, n=2_000_000, groups=600, device=gpu)
     big, bv = synth.groupby_input(seed=2, n=2_000_000, groups=1_500_000, device=gpu)
