@@ -104,8 +104,8 @@ __device__ __forceinline__ void global_add(const GbGlobal &t, unsigned long long
 // Every kAFold rows the accumulators are folded into registers of the thread that
 // owns the slot, so they never run over and reach the global table once per
 // workgroup. Four rows a thread and at most 80 registers, so that three workgroups
-// of 512 share a CU: with eight rows and two workgroups, 1,000 groups took 1.27 ms
-// instead of 0.91.
+// of 512 share a CU where their LDS lets them (agg_per_cu): with eight rows and two
+// workgroups, 1,000 groups took 1.27 ms instead of 0.91.
 template <int NV, bool W0>
 constexpr bool kPacked = NV > 0 && !W0;
 
@@ -120,6 +120,14 @@ struct AggLds {
   unsigned long long scan[kANT / 64];
   unsigned long long at;
 };
+
+// Workgroups of a CU: three, or the two whose tables fit its 160 KB of LDS (56 KB each
+// where the first of two columns has 8 bytes). The grids are sized by it: with three
+// ranges of rows per CU for the two, 2^26 rows of 1,000 groups and two 8-byte sums
+// took 517 us, now 424.
+template <int NV, bool W0>
+constexpr int agg_per_cu = sizeof(AggLds<NV, W0>) * 3 <= 163840 ? 3 : 2;
+static_assert(sizeof(AggLds<2, true>) * agg_per_cu<2, true> <= 163840, "the largest table");
 
 // A thread's slots threadIdx.x + j * kANT.
 template <int NV>
@@ -539,7 +547,7 @@ __global__ void __launch_bounds__(kGNT) k_gb_clear(GbGlobal g, int nv, unsigned 
 // groups and three 64-bit LDS atomics a row); 1,000 groups: 0.91 ms (2.94), the
 // walks in the half-full table.
 template <typename K, int NV, bool W0, bool W1, bool kRuns>
-__global__ void __launch_bounds__(kANT, 6) k_gb_hash(const K *__restrict__ keys, uint64_t n, GbVals vals, AggShape h,
+__global__ void __launch_bounds__(kANT, (2 * agg_per_cu<NV, W0>)) k_gb_hash(const K *__restrict__ keys, uint64_t n, GbVals vals, AggShape h,
                                                   uint64_t per, GbGlobal g) {
   __shared__ AggLds<NV, W0> L;
   AggOwn<NV> own;
@@ -568,7 +576,7 @@ __global__ void __launch_bounds__(kANT, 6) k_gb_hash(const K *__restrict__ keys,
 // 2^28 rows, two 4-byte sums, 2^20 groups in 2^11 partitions: 0.75 ms (4.3 TB/s;
 // 1.78 with one row's walk at a time).
 template <typename K, int NV, bool W0, bool W1>
-__global__ void __launch_bounds__(kANT, 6)
+__global__ void __launch_bounds__(kANT, (2 * agg_per_cu<NV, W0>))
     k_gb_partition(const K *__restrict__ keys, GbVals vals, const uint32_t *__restrict__ off, uint32_t F, uint32_t S,
                    AggShape h, GbGlobal g, GbOut o) {
   __shared__ AggLds<NV, W0> L;
@@ -668,8 +676,8 @@ struct AggCall {
 
 template <typename K, int NV, bool W0, bool W1>
 int agg_hash_launch(const AggCall &a, const K *keys, uint64_t n) {
-  // contiguous ranges of whole steps, three workgroups per CU (48 KB of LDS each)
-  const uint64_t steps = (n + kAStep - 1) / kAStep, cap = uint64_t(device_cu_count()) * 3;
+  // contiguous ranges of whole steps, all of them in flight together
+  const uint64_t steps = (n + kAStep - 1) / kAStep, cap = uint64_t(device_cu_count()) * agg_per_cu<NV, W0>;
   const uint64_t per = (steps + cap - 1) / cap * kAStep;
   const dim3 grid(static_cast<unsigned>((n + per - 1) / per));
   // With four accumulators a slot or more (up to 128 groups) sorted rows cost no more
@@ -684,7 +692,7 @@ int agg_hash_launch(const AggCall &a, const K *keys, uint64_t n) {
 
 template <typename K, int NV, bool W0, bool W1>
 int agg_partition_launch(const AggCall &a, const K *keys, const uint32_t *off, uint32_t F, uint32_t S, const GbOut &o) {
-  const uint64_t cap = uint64_t(device_cu_count()) * 3;
+  const uint64_t cap = uint64_t(device_cu_count()) * agg_per_cu<NV, W0>;
   EIGER_LAUNCH("groupby_partition", (k_gb_partition<K, NV, W0, W1>),
                dim3(static_cast<unsigned>(std::min<uint64_t>(uint64_t(F) * S, cap))), dim3(kANT), 0, a.s, keys, a.vals,
                off, F, S, a.shape, a.g, o);
