@@ -266,7 +266,7 @@ template <typename K, typename P>
 __global__ void __launch_bounds__(kBNT) k_batch_probe(XcdItems items, const BatchJoinDev *__restrict__ J,
                                                       BatchState *__restrict__ st, const Slot<K, P> *__restrict__ arena,
                                                       uint32_t *ob, uint32_t *op) {
-  __shared__ WaveLds<K, P> L[kBNT / 64];
+  __shared__ WaveLds<K, P, true> L[kBNT / 64];
   __shared__ WaveJoint<kBNT / 64> joint;
   const uint32_t wave = threadIdx.x / 64;
   constexpr uint64_t block = 64 * kWaveRows, sub = kBNT * kWaveRows;
@@ -280,12 +280,12 @@ __global__ void __launch_bounds__(kBNT) k_batch_probe(XcdItems items, const Batc
     if (s->variant == kVarDirect) {
       const uint64_t mn = static_cast<uint64_t>(s->mn);
       const BatchDirectTab<K, P> tab{arena + d.tab_off, mn, static_cast<uint64_t>(s->mx) - mn + 1};
-      WaveProbe<BatchDirectTab<K, P>, K, P> p(tab, L[wave], o);
-      p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, &joint);
+      WaveProbe<BatchDirectTab<K, P>, K, P, 1, true> p(tab, L[wave], o);
+      p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, joint);
     } else {
       const BatchHashTab<K, P> tab{arena + d.tab_off, d.slots - 1};
-      WaveProbe<BatchHashTab<K, P>, K, P, 2> p(tab, L[wave], o);
-      p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, &joint);
+      WaveProbe<BatchHashTab<K, P>, K, P, 2, true> p(tab, L[wave], o);
+      p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, joint);
     }
   }
 }
@@ -475,7 +475,7 @@ int enqueue_batch(const BatchPlan &bp, const BatchLayout &L, uint32_t *ob, uint3
                  L.state, arena);
   }
   if (np) {
-    EIGER_LAUNCH("batch_probe", (k_batch_probe<K, P>), dim3(xcd_grid(np, cus, static_cast<unsigned>(163840 / (sizeof(WaveLds<K, P>) * (kBNT / 64))))), dim3(kBNT), 0, s,
+    EIGER_LAUNCH("batch_probe", (k_batch_probe<K, P>), dim3(xcd_grid(np, cus, static_cast<unsigned>(163840 / (sizeof(WaveLds<K, P, true>) * (kBNT / 64))))), dim3(kBNT), 0, s,
                  pi, L.joins, L.state, static_cast<const Slot<K, P> *>(L.arena), ob, op);
   }
   for (const RadixJob &job : bp.radix) {

@@ -102,7 +102,7 @@ __device__ __forceinline__ void finish(EmitLds<NT, SCAP> &L, const EmitOut &o, u
 //
 // A wave probes on its own. Rows are taken 64 * kWaveRows at a time, their first
 // kEager slots loaded at once. Rows whose walk goes on are packed into a queue in
-// LDS, from which full waves take the next two slots of 64 * kWaveQueued rows. So
+// LDS, from which full waves take the next slots of 64 * kWaveQueued rows, two at a time. So
 // every round trip carries full waves; when a wave walked its rows until the last
 // one ended, it made 8 to 10 for rows that need 1.5 on average. A match is staged
 // the moment it is found. Bound by random accesses: 255 G/s of them from a table
@@ -113,12 +113,12 @@ constexpr uint32_t kWaveStage = 504;
 static_assert(kWaveStage >= 64 * kWaveRows && kWaveStage >= 64 * 2 * kWaveQueued, "a step's matches fit an empty stage");
 constexpr uint32_t kWaveQueue = 64 * (kWaveRows + kWaveQueued);
 
-template <typename K, typename PS>
+template <typename K, typename PS, bool kPairs>
 struct WaveLds {
   K key[kWaveQueue];
   PS pay[kWaveQueue];
   uint32_t row[kWaveQueue], step[kWaveQueue];
-  uint32_t ob[kWaveStage], op[kWaveStage];
+  uint32_t ob[kPairs ? kWaveStage : 1], op[kPairs ? kWaveStage : 1];
 };
 
 // What the waves of a workgroup share to write their stages out together; two
@@ -139,18 +139,19 @@ __device__ __forceinline__ void wave_lds_fence() {
 
 // Tab: SlotT, Index; start(key, in) -> first slot (in: false when the key cannot be
 // there), walk(first, steps) -> the slot `steps` further, load(slot); kWalk: keys may
-// lie further on; unique: build keys known to be distinct.
-template <class Tab, typename K, typename PS, int kEager = 1>
+// lie further on; unique: build keys known to be distinct. kPairs: matches are staged
+// and written out (o.ob, o.op given); else they are counted only.
+template <class Tab, typename K, typename PS, int kEager, bool kPairs>
 struct WaveProbe {
   static_assert(kEager == 1 || kEager == 2, "one or two slots at first");
   const Tab &tab;
-  WaveLds<K, PS> &L;
+  WaveLds<K, PS, kPairs> &L;
   const EmitOut &o;
-  uint64_t fill = 0;    // staged pairs; count-only: all pairs (uniform)
+  uint64_t fill = 0;    // staged pairs, or all pairs counted (uniform)
   uint32_t queued = 0;  // uniform
   uint64_t cs = 0;      // this lane's share of the checksum
 
-  __device__ __forceinline__ WaveProbe(const Tab &t, WaveLds<K, PS> &l, const EmitOut &e) : tab(t), L(l), o(e) {}
+  __device__ __forceinline__ WaveProbe(const Tab &t, WaveLds<K, PS, kPairs> &l, const EmitOut &e) : tab(t), L(l), o(e) {}
 
   // The staged pairs to output positions base, base + 1, ...
   __device__ __forceinline__ void write_out(uint64_t base) {
@@ -161,22 +162,12 @@ struct WaveProbe {
   }
 
   // Whether the stage takes R more matches a lane.
-  __device__ __forceinline__ bool room(int R) const { return !o.ob || fill + 64 * R <= kWaveStage; }
+  __device__ __forceinline__ bool room(int R) const { return !kPairs || fill + 64 * R <= kWaveStage; }
 
-  // The stage written out by the wave alone.
-  __device__ __forceinline__ void flush_own() {
-    unsigned long long at = 0;
-    if (__lane_id() == 0)
-      at = atomicAdd(reinterpret_cast<unsigned long long *>(o.cursor), static_cast<unsigned long long>(fill));
-    write_out((uint64_t(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(at >> 32))) << 32) |
-              static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(at))));
-  }
-
-  // Between two slots of the same rows: distinct build keys match once in all
-  // their slots, so there is room; others may match in each.
-  __device__ __forceinline__ void make_room(int R) {
-    if (!tab.unique && !room(R)) flush_own();
-  }
+  // Whether the second slot of rows already looked at once can be looked at before the
+  // stage is written out: distinct build keys match once in all their slots, so that
+  // there is room; others may match in each.
+  __device__ __forceinline__ bool second(int R) const { return tab.unique || room(R); }
 
   // The next slot of R rows a lane: matches are staged; live: the walks that go on.
   template <int R>
@@ -188,7 +179,7 @@ struct WaveProbe {
       const bool hit = live[r] && sl[r].key == key[r];
       if (hit) cs += static_cast<uint64_t>(sext(sl[r].pay)) * static_cast<uint64_t>(sext(pay[r]));
       const uint64_t hits = __ballot(hit);
-      if (o.ob && hit) {
+      if (kPairs && hit) {
         const uint32_t at = static_cast<uint32_t>(fill) + lane_prefix(hits);
         L.ob[at] = sl[r].rowid;
         L.op[at] = row[r];
@@ -217,12 +208,15 @@ struct WaveProbe {
     wave_lds_fence();
   }
 
-  // Two more steps of the last n queued rows (n <= 64 * kWaveQueued, n <= queued).
+  // The next slots of the last n queued rows (n <= 64 * kWaveQueued, n <= queued): two
+  // or, without room for the second's matches, one. Walks among repeated keys are long
+  // and stay here while most of them go on.
   __device__ __forceinline__ void advance(uint32_t n) {
     K key[kWaveQueued];
     PS pay[kWaveQueued];
     uint32_t row[kWaveQueued], step[kWaveQueued];
     bool live[kWaveQueued];
+    typename Tab::Index home[kWaveQueued];
     typename Tab::SlotT s0[kWaveQueued], s1[kWaveQueued];
     queued -= n;
 #pragma unroll
@@ -234,34 +228,39 @@ struct WaveProbe {
       pay[r] = L.pay[e];
       row[r] = L.row[e];
       step[r] = L.step[e];
-    }
-#pragma unroll
-    for (int r = 0; r < kWaveQueued; ++r) {
       bool in;
-      const typename Tab::Index i = tab.start(key[r], in);
-      s0[r] = tab.load(tab.walk(i, step[r]));
-      s1[r] = tab.load(tab.walk(i, step[r] + 1));
-      step[r] += 2;
+      home[r] = tab.start(key[r], in);
     }
-    wave_lds_fence();
-    visit<kWaveQueued>(key, pay, row, live, s0);
-    make_room(kWaveQueued);
-    visit<kWaveQueued>(key, pay, row, live, s1);
+    for (;;) {
+#pragma unroll
+      for (int r = 0; r < kWaveQueued; ++r) {
+        s0[r] = tab.load(tab.walk(home[r], step[r]));
+        s1[r] = tab.load(tab.walk(home[r], step[r] + 1));
+      }
+      wave_lds_fence();
+      visit<kWaveQueued>(key, pay, row, live, s0);
+      const bool both = second(kWaveQueued);
+      if (both) visit<kWaveQueued>(key, pay, row, live, s1);
+#pragma unroll
+      for (int r = 0; r < kWaveQueued; ++r) step[r] += both ? 2 : 1;
+      if (tab.unique || !room(kWaveQueued)) break;
+      uint32_t on = 0;
+#pragma unroll
+      for (int r = 0; r < kWaveQueued; ++r) on += static_cast<uint32_t>(__popcll(__ballot(live[r])));
+      if (4 * on < 3 * n) break;
+    }
     enqueue<kWaveQueued>(key, pay, row, step, live);
   }
 
   // Probe rows [lo, hi) in blocks of 64 * kWaveRows rows, `stride` rows apart,
   // until every match is written out; a block's columns are loaded while the one
-  // before is probed. J null: the wave reserves output for its own stage. Else
-  // the waves of the workgroup (all NW call this) write their stages out together
-  // whenever one is full, for one atomic: atomics on one cursor run at 10 ns each
-  // (2^27 probes, 121M matches: 3.2 ms of them with 380 pairs each). The branch on J
-  // stays although every kernel passes one: without it the loop's code came out 2%
-  // slower (537M count-only probes of a 2 GiB table: 11.50 against 11.75 ms).
+  // before is probed. The waves of the workgroup (all NW call this) write their stages
+  // out together whenever one is full, for one atomic: atomics on one cursor run at
+  // 10 ns each (2^27 probes, 121M matches: 3.2 ms of them with 380 pairs each).
   template <int NW>
   __device__ __forceinline__ void run(const K *__restrict__ pk, const PS *__restrict__ pp,
                                       const uint32_t *__restrict__ prow, uint64_t lo, uint64_t hi, uint64_t stride,
-                                      WaveJoint<NW> *J) {
+                                      WaveJoint<NW> &J) {
     K key[kWaveRows], nkey[kWaveRows];
     PS pay[kWaveRows], npay[kWaveRows];
     uint32_t row[kWaveRows], nrow[kWaveRows], step[kWaveRows];
@@ -303,8 +302,12 @@ struct WaveProbe {
           visit<kWaveRows>(key, pay, row, live, s0);
           if constexpr (Tab::kWalk) {
             if constexpr (kEager > 1) {
-              make_room(kWaveRows);
-              visit<kWaveRows>(key, pay, row, live, s1);
+              if (second(kWaveRows)) {
+                visit<kWaveRows>(key, pay, row, live, s1);
+              } else {
+#pragma unroll
+                for (int r = 0; r < kWaveRows; ++r) step[r] = 1;
+              }
             }
             enqueue<kWaveRows>(key, pay, row, step, live);
           } else {
@@ -315,50 +318,42 @@ struct WaveProbe {
         }
       }
       bool done = t >= hi && queued == 0;  // nothing left but the stage
-      if (!o.ob) break;
-      if (!J) {
-        if (fill) flush_own();
-      } else {
-        const uint32_t w = threadIdx.x / 64, par = round & 1;
-        if (__lane_id() == 0) J->fill[par][w] = static_cast<uint32_t>(fill) | (done ? 0u : 1u << 31);
-        __syncthreads();
-        uint32_t total = 0, before = 0, busy = 0;
+      if constexpr (!kPairs) break;
+      const uint32_t w = threadIdx.x / 64, par = round & 1;
+      if (__lane_id() == 0) J.fill[par][w] = static_cast<uint32_t>(fill) | (done ? 0u : 1u << 31);
+      __syncthreads();
+      uint32_t total = 0, before = 0, busy = 0;
 #pragma unroll
-        for (uint32_t x = 0; x < NW; ++x) {
-          const uint32_t f = J->fill[par][x];
-          before += x < w ? f & 0x7FFFFFFFu : 0u;
-          total += f & 0x7FFFFFFFu;
-          busy |= f >> 31;
-        }
-        if (threadIdx.x == 0 && total)
-          J->base[par] = atomicAdd(reinterpret_cast<unsigned long long *>(o.cursor), static_cast<unsigned long long>(total));
-        __syncthreads();
-        write_out(J->base[par] + before);
-        done = !busy;
+      for (uint32_t x = 0; x < NW; ++x) {
+        const uint32_t f = J.fill[par][x];
+        before += x < w ? f & 0x7FFFFFFFu : 0u;
+        total += f & 0x7FFFFFFFu;
+        busy |= f >> 31;
       }
+      if (threadIdx.x == 0 && total)
+        J.base[par] = atomicAdd(reinterpret_cast<unsigned long long *>(o.cursor), static_cast<unsigned long long>(total));
+      __syncthreads();
+      write_out(J.base[par] + before);
+      done = !busy;
       if (done) break;
     }
-    // totals: the workgroup's in one atomic each, or the wave's
-    uint64_t sum = wave_sum_u64(cs), count = o.ob ? 0 : fill;
+    // totals: the workgroup's in one atomic each
+    uint64_t sum = wave_sum_u64(cs), count = kPairs ? 0 : fill;
+    if (__lane_id() == 0) {
+      J.sum[threadIdx.x / 64] = sum;
+      J.count[threadIdx.x / 64] = count;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    sum = count = 0;
+    for (int x = 0; x < NW; ++x) {
+      sum += J.sum[x];
+      count += J.count[x];
+    }
     uint64_t *to_sum = o.checksum, *to_count = o.cursor;
-    if (J) {
-      if (__lane_id() == 0) {
-        J->sum[threadIdx.x / 64] = sum;
-        J->count[threadIdx.x / 64] = count;
-      }
-      __syncthreads();
-      if (threadIdx.x != 0) return;
-      sum = count = 0;
-      for (int x = 0; x < NW; ++x) {
-        sum += J->sum[x];
-        count += J->count[x];
-      }
-      if (o.stripes) {
-        to_sum = &o.stripes[blockIdx.x % kStripes].checksum;
-        to_count = &o.stripes[blockIdx.x % kStripes].count;
-      }
-    } else if (__lane_id() != 0) {
-      return;
+    if (o.stripes) {
+      to_sum = &o.stripes[blockIdx.x % kStripes].checksum;
+      to_count = &o.stripes[blockIdx.x % kStripes].count;
     }
     if (sum) atomicAdd(reinterpret_cast<unsigned long long *>(to_sum), static_cast<unsigned long long>(sum));
     if (count) atomicAdd(reinterpret_cast<unsigned long long *>(to_count), static_cast<unsigned long long>(count));
@@ -397,7 +392,7 @@ __device__ __forceinline__ void probe_load(ProbeRegs<IPT, K, PS> &r, const K *__
 
 // Count the matches of every loaded row. Tables of two kinds:
 //  * hashed tables (Tab::kHashed) expose an index type Index, home(key),
-//    next(i), load(i) -> slot and a `unique` flag (build keys known to be
+//    next(i, step) (from a walk's slot i to its step-th), load(i) -> slot and a `unique` flag (build keys known to be
 //    distinct). The first slot of
 //    every row is loaded before any is inspected, so a thread keeps IPT random
 //    loads in flight; only rows whose walk is not finished load again, and a
@@ -441,12 +436,12 @@ __device__ __forceinline__ void count_matches(const Tab &tab, const ProbeRegs<IP
           if (tab.unique) live[k] = false;
         }
         if (live[k]) {
-          idx[k] = tab.next(idx[k]);
+          idx[k] = tab.next(idx[k], 1);
           any = true;
         }
       }
     }
-    while (any) {
+    for (uint32_t step = 2; any; ++step) {
       any = false;
 #pragma unroll
       for (int k = 0; k < IPT; ++k)
@@ -464,7 +459,7 @@ __device__ __forceinline__ void count_matches(const Tab &tab, const ProbeRegs<IP
             if (tab.unique) live[k] = false;
           }
           if (live[k]) {
-            idx[k] = tab.next(idx[k]);
+            idx[k] = tab.next(idx[k], step);
             any = true;
           }
         }

@@ -59,23 +59,27 @@ struct HashTab {
   }
 };
 
-// The same table for a probe that holds each row's walk in its lane: a walk's slot
-// carries its first slot's place in the 64-byte line in bits 61 and 62.
+// The same table of 32-byte slots for a probe that holds each row's walk in its lane:
+// the two slots of the first line, the home slot first, then those of the next, each
+// one step from the slot before.
 template <typename K, typename PB>
 struct HashRowTab : HashTab<K, PB> {
+  static_assert(sizeof(Slot<K, PB>) == 32, "two slots in 64 bytes");
   static constexpr bool kHashed = true;
   static constexpr bool kRuns = false;
-  static constexpr uint64_t kPer = 64 / sizeof(Slot<K, PB>);
-  __device__ __forceinline__ uint64_t home(K key) const {
-    const uint64_t h = HashTab<K, PB>::home(key);
-    return h | (h & (kPer - 1)) << 61;
+  __device__ __forceinline__ uint64_t next(uint64_t i, uint32_t step) const {
+    return step & 1 ? i ^ 1 : ((i ^ 1) + 2) & this->mask;
   }
-  __device__ __forceinline__ uint64_t next(uint64_t i) const {
-    const uint64_t first = i >> 61, pos = i & this->mask, q = (pos + 1) & (kPer - 1);
-    const uint64_t line = pos - (pos & (kPer - 1)) + (q == first ? kPer : 0);
-    return (line & this->mask) | q | first << 61;
+  template <class F>
+  __device__ __forceinline__ void for_each(K key, F f) const {
+    uint64_t i = this->home(key);
+    for (uint32_t step = 1;; ++step) {
+      const Slot<K, PB> s = this->slots[i];
+      if (s.rowid == kEmpty) break;
+      if (s.key == key) f(s.rowid);
+      i = next(i, step);
+    }
   }
-  __device__ __forceinline__ Slot<K, PB> load(uint64_t i) const { return this->slots[i & this->mask]; }
 };
 
 // Sets *dup when some build key occurs more than once: every build row walks
@@ -192,10 +196,10 @@ bool hash_sentinel(const JoinArgs &a, K *out) {
 
 // Each workgroup streams a contiguous range of probe rows (an equal share of
 // whole blocks), its waves taking blocks in turn.
-template <class Tab, typename K, typename PS, int kEager>
+template <class Tab, typename K, typename PS, int kEager, bool kPairs>
 __global__ void __launch_bounds__((kPNT<K, PS>)) k_probe(Tab tab, const K *__restrict__ pk,
                                                const PS *__restrict__ pp, uint64_t n, EmitOut o) {
-  __shared__ WaveLds<K, PS> L[kPNT<K, PS> / 64];
+  __shared__ WaveLds<K, PS, kPairs> L[kPNT<K, PS> / 64];
   __shared__ WaveJoint<kPNT<K, PS> / 64> J;
   tab.init();
   constexpr uint64_t block = 64 * kWaveRows, sub = kPNT<K, PS> * kWaveRows;
@@ -204,8 +208,8 @@ __global__ void __launch_bounds__((kPNT<K, PS>)) k_probe(Tab tab, const K *__res
   const uint64_t per = (nsub + gridDim.x - 1) / gridDim.x;
   const uint64_t lo = blockIdx.x * per * sub;
   const uint64_t hi = lo + per * sub < n ? lo + per * sub : n;
-  WaveProbe<Tab, K, PS, kEager> p(tab, L[w], o);
-  p.template run<kPNT<K, PS> / 64>(pk, pp, nullptr, lo + w * block, hi, sub, &J);
+  WaveProbe<Tab, K, PS, kEager, kPairs> p(tab, L[w], o);
+  p.template run<kPNT<K, PS> / 64>(pk, pp, nullptr, lo + w * block, hi, sub, J);
 }
 
 constexpr int kRowNT = 256;
@@ -229,9 +233,9 @@ __global__ void __launch_bounds__(kRowNT) k_probe_rows(HashRowTab<K, PB> tab, co
 }
 
 // Workgroups of a CU by the LDS they take (160 KB).
-template <typename K, typename PS>
+template <typename K, typename PS, bool kPairs>
 constexpr int probe_per_cu() {
-  return static_cast<int>(163840 / (sizeof(WaveLds<K, PS>) * (kPNT<K, PS> / 64) + sizeof(WaveJoint<kPNT<K, PS> / 64>)));
+  return static_cast<int>(163840 / (sizeof(WaveLds<K, PS, kPairs>) * (kPNT<K, PS> / 64) + sizeof(WaveJoint<kPNT<K, PS> / 64>)));
 }
 
 unsigned grid_for(uint64_t work, uint64_t per_block, int per_cu) {
@@ -239,6 +243,13 @@ unsigned grid_for(uint64_t work, uint64_t per_block, int per_cu) {
   const uint64_t cap = uint64_t(device_cu_count()) * per_cu;
   if (g > cap) g = cap;
   return static_cast<unsigned>(g ? g : 1);
+}
+
+template <typename K, typename PB, typename PS, int kEager, bool kPairs>
+int launch_probe(const HashTab<K, PB> &tab, const K *pk, const PS *pp, uint64_t n, const EmitOut &o, hipStream_t s) {
+  const dim3 grid(grid_for(n, uint64_t(kPNT<K, PS>) * kWaveRows, probe_per_cu<K, PS, kPairs>()));
+  EIGER_LAUNCH("hash_probe", (k_probe<HashTab<K, PB>, K, PS, kEager, kPairs>), grid, dim3(kPNT<K, PS>), 0, s, tab, pk, pp, n, o);
+  return EIGER_OK;
 }
 
 template <typename K, typename PB, typename PS>
@@ -278,7 +289,6 @@ int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
                  static_cast<const K *>(a.bk), a.nR, tab, dup);
   }
   EmitOut o{a.ob, a.op, a.cap, &c->count, &c->checksum, hc->stripe};
-  const dim3 grid(grid_for(a.nS, uint64_t(kPNT<K, PS>) * kWaveRows, probe_per_cu<K, PS>()));
   const K *pk = static_cast<const K *>(a.pk);
   const PS *pp = static_cast<const PS *>(a.pp);
   // Which probe (2^27 probes that all match, half-full tables, ms with pairs / count only;
@@ -309,11 +319,9 @@ int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
       return EIGER_OK;
     }
   }
-  if (bytes <= kNearBytes || bytes > kFarBytes)
-    EIGER_LAUNCH("hash_probe", (k_probe<HashTab<K, PB>, K, PS, 1>), grid, dim3(kPNT<K, PS>), 0, s, tab, pk, pp, a.nS, o);
-  else
-    EIGER_LAUNCH("hash_probe", (k_probe<HashTab<K, PB>, K, PS, 2>), grid, dim3(kPNT<K, PS>), 0, s, tab, pk, pp, a.nS, o);
-  return EIGER_OK;
+  const bool near = bytes <= kNearBytes || bytes > kFarBytes;
+  if (a.ob) return near ? launch_probe<K, PB, PS, 1, true>(tab, pk, pp, a.nS, o, s) : launch_probe<K, PB, PS, 2, true>(tab, pk, pp, a.nS, o, s);
+  return near ? launch_probe<K, PB, PS, 1, false>(tab, pk, pp, a.nS, o, s) : launch_probe<K, PB, PS, 2, false>(tab, pk, pp, a.nS, o, s);
 }
 
 }  // namespace

@@ -1043,16 +1043,16 @@ struct CacheTab {
   __device__ __forceinline__ uint32_t home(K key) const {
     return fastrange32(fmix64(static_cast<uint64_t>(sext(key))), n);
   }
-  __device__ __forceinline__ uint32_t next(uint32_t i) const { return (i + 1 == n) ? 0 : i + 1; }
+  __device__ __forceinline__ uint32_t next(uint32_t i, uint32_t) const { return (i + 1 == n) ? 0 : i + 1; }
   __device__ __forceinline__ SlotT load(uint32_t i) const { return slots[i]; }
   template <class F>
   __device__ __forceinline__ void for_each(K key, F f) const {
     uint32_t i = home(key);
-    for (;;) {
+    for (uint32_t step = 1;; ++step) {
       const Slot<K, PB> s = slots[i];
       if (s.rowid == kEmpty) break;
       if (s.key == key) f(s.rowid);
-      i = next(i);
+      i = next(i, step);
     }
   }
 };

@@ -62,6 +62,30 @@ def test_hash_probe_paths(gpu, n_build, key, pay, shape):
         assert (cnt.count, cnt.checksum) == (res.count, res.checksum)
 
 
+def test_hash_pairs_of_repeated_keys_time(gpu):
+    """1,000 keys of 16 rows: writing the pairs out takes no more than as long again as
+    counting them (2.4 times as long while waves reserved output one by one)."""
+    g = torch.Generator(device=gpu).manual_seed(1)
+    keys = torch.arange(1000, device=gpu) * 1103515245 & ((1 << 31) - 1)
+    bk = keys.repeat_interleave(16)[torch.randperm(16000, generator=g, device=gpu)].int()
+    pk = keys[torch.randint(0, 1000, (1 << 20,), generator=g, device=gpu)].int()
+    one, outs = torch.ones_like(pk), [torch.empty(1 << 24, dtype=torch.int32, device=gpu) for _ in range(2)]
+    plan = eg.join_plan(eg.stats(bk), eg.stats(pk), eg.SEL_FORCED, eg.make_plan(eg.GLOBAL_HASH, 0, 0, 0.5))
+    ws = torch.empty(eg.join_workspace_size(plan, bk, bk, pk, one), dtype=torch.uint8, device=gpu)
+
+    def call(**kw):
+        start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        assert eg.join(bk, bk, pk, one, plan, workspace=ws, **kw).count == 1 << 24
+        stop.record()
+        stop.synchronize()
+        return start.elapsed_time(stop)
+
+    t = [(call(outputs=outs), call(count_only=True)) for _ in range(11)]
+    pairs, count = (min(x) for x in zip(*t))
+    assert pairs < 2 * count, (pairs, count)
+
+
 def test_direct_refuses_sparse_range(gpu):
     inp = synth.sparse_unique64(seed=4, n_build=1000, n_probe=1000, device=gpu)
     with pytest.raises(eg.EigerError) as e:
