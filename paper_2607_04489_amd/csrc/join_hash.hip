@@ -22,7 +22,7 @@ namespace eiger {
 namespace {
 
 // Table sizes at which the probe changes (see hash_impl).
-constexpr uint64_t kNearBytes = 8u << 20, kRowsBytes = 16u << 20, kFarBytes = 2ull << 30;
+constexpr uint64_t kNearBytes = 8u << 20, kFarBytes = 2ull << 30;
 
 // Probe workgroup: two share a CU's 160 KB of LDS.
 template <typename K, typename PS>
@@ -195,13 +195,16 @@ bool hash_sentinel(const JoinArgs &a, K *out) {
 }
 
 // Each workgroup streams a contiguous range of probe rows (an equal share of
-// whole blocks), its waves taking blocks in turn.
+// whole blocks), its waves taking blocks in turn. repeated_only: tables of distinct
+// keys are k_probe_rows'.
 template <class Tab, typename K, typename PS, int kEager, bool kPairs>
 __global__ void __launch_bounds__((kPNT<K, PS>)) k_probe(Tab tab, const K *__restrict__ pk,
-                                               const PS *__restrict__ pp, uint64_t n, EmitOut o) {
+                                               const PS *__restrict__ pp, uint64_t n, EmitOut o,
+                                               bool repeated_only) {
   __shared__ WaveLds<K, PS, kPairs> L[kPNT<K, PS> / 64];
   __shared__ WaveJoint<kPNT<K, PS> / 64> J;
   tab.init();
+  if (repeated_only && tab.unique) return;
   constexpr uint64_t block = 64 * kWaveRows, sub = kPNT<K, PS> * kWaveRows;
   const uint32_t w = threadIdx.x / 64;
   const uint64_t nsub = (n + sub - 1) / sub;
@@ -217,12 +220,15 @@ constexpr int kRowIPT = 5;  // rows per thread
 constexpr int kRowSCAP = 4096;
 
 // Each thread holds the walks of its rows to their end, five first slots in flight.
+// distinct_only: tables of repeated keys are k_probe's.
 template <typename K, typename PB, typename PS>
 __global__ void __launch_bounds__(kRowNT) k_probe_rows(HashRowTab<K, PB> tab, const K *__restrict__ pk,
-                                                     const PS *__restrict__ pp, uint64_t n, EmitOut o) {
+                                                     const PS *__restrict__ pp, uint64_t n, EmitOut o,
+                                                     bool distinct_only) {
   __shared__ EmitLds<kRowNT, kRowSCAP> L;
   uint64_t fill = 0, cs = 0;
   tab.init();
+  if (distinct_only && !tab.unique) return;
   constexpr uint64_t sub = uint64_t(kRowNT) * kRowIPT;
   const uint64_t nsub = (n + sub - 1) / sub;
   const uint64_t per = (nsub + gridDim.x - 1) / gridDim.x;
@@ -246,9 +252,11 @@ unsigned grid_for(uint64_t work, uint64_t per_block, int per_cu) {
 }
 
 template <typename K, typename PB, typename PS, int kEager, bool kPairs>
-int launch_probe(const HashTab<K, PB> &tab, const K *pk, const PS *pp, uint64_t n, const EmitOut &o, hipStream_t s) {
+int launch_probe(const HashTab<K, PB> &tab, const K *pk, const PS *pp, uint64_t n, const EmitOut &o, bool repeated_only,
+                 hipStream_t s) {
   const dim3 grid(grid_for(n, uint64_t(kPNT<K, PS>) * kWaveRows, probe_per_cu<K, PS, kPairs>()));
-  EIGER_LAUNCH("hash_probe", (k_probe<HashTab<K, PB>, K, PS, kEager, kPairs>), grid, dim3(kPNT<K, PS>), 0, s, tab, pk, pp, n, o);
+  EIGER_LAUNCH("hash_probe", (k_probe<HashTab<K, PB>, K, PS, kEager, kPairs>), grid, dim3(kPNT<K, PS>), 0, s, tab, pk, pp, n, o,
+               repeated_only);
   return EIGER_OK;
 }
 
@@ -307,21 +315,31 @@ int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   // Tables near an XCD's L2 are bound by the L1's fills, and a second slot of every row
   // costs more of them than it saves; from larger ones it comes with the first; beyond
   // 2 GiB two slots are two address translations in flight instead of one. With 32-byte
-  // slots the waves' LDS leaves 12 waves a CU to the 16 of the rows' probe, which shows
-  // while the table is near or very far.
+  // slots the rows' probe has 16 waves a CU to the waves' 12 where pairs are written. It
+  // is behind from 64 MiB to 2 GiB (above; 11% where hardly any probe matches) but
+  // ahead where most probes stay near, by more (90% of the probes on one key: 33.5M of a
+  // 64 MiB table 0.49 ms for 0.60, 134M of a 1 GiB table 3.13 for 3.53). Walks among
+  // repeated keys are long, and there the waves' probe is the faster (2^22 probes of
+  // 4,000 keys of 8 rows: 0.95 ms for 2.00; 2^24 of 250,000 of 4: 2.3 for 5.2). The build
+  // tells which it is: both are launched, one returns at once.
   const uint64_t bytes = nslots * sizeof(Slot<K, PB>);
+  const bool near = bytes <= kNearBytes, far = bytes > kFarBytes;
+  bool by_rows = false;
   if constexpr (sizeof(Slot<K, PB>) == 32) {
-    if (bytes > kFarBytes || (a.ob && bytes <= kRowsBytes)) {
+    by_rows = a.ob || far;
+    if (by_rows) {
       HashRowTab<K, PB> rows;
       static_cast<HashTab<K, PB> &>(rows) = tab;
       EIGER_LAUNCH("hash_probe", (k_probe_rows<K, PB, PS>), dim3(grid_for(a.nS, uint64_t(kRowNT) * kRowIPT, 4)),
-                   dim3(kRowNT), 0, s, rows, pk, pp, a.nS, o);
-      return EIGER_OK;
+                   dim3(kRowNT), 0, s, rows, pk, pp, a.nS, o, a.ob != nullptr);
+      if (!a.ob) return EIGER_OK;  // (counted pairs of repeated keys: 15.4 ms for 16.3 at 4 GiB)
     }
   }
-  const bool near = bytes <= kNearBytes || bytes > kFarBytes;
-  if (a.ob) return near ? launch_probe<K, PB, PS, 1, true>(tab, pk, pp, a.nS, o, s) : launch_probe<K, PB, PS, 2, true>(tab, pk, pp, a.nS, o, s);
-  return near ? launch_probe<K, PB, PS, 1, false>(tab, pk, pp, a.nS, o, s) : launch_probe<K, PB, PS, 2, false>(tab, pk, pp, a.nS, o, s);
+  if (a.ob)
+    return near || far ? launch_probe<K, PB, PS, 1, true>(tab, pk, pp, a.nS, o, by_rows, s)
+                       : launch_probe<K, PB, PS, 2, true>(tab, pk, pp, a.nS, o, by_rows, s);
+  return near || far ? launch_probe<K, PB, PS, 1, false>(tab, pk, pp, a.nS, o, false, s)
+                     : launch_probe<K, PB, PS, 2, false>(tab, pk, pp, a.nS, o, false, s);
 }
 
 }  // namespace

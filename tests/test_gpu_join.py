@@ -38,7 +38,7 @@ def test_sparse_unique64(gpu, spec):
 
 # Build rows of which one more doubles the table at load factor 0.5. 16-byte slots: 2 to
 # 16 MiB, from 16 on the probe loads two slots of a row at first; 32-byte slots: 4 to 32
-# MiB, up to 16 with pairs the rows' own probe, count-only from 16 on two slots.
+# MiB, pairs of distinct keys by the rows' own probe, the others from 16 on two slots.
 @pytest.mark.parametrize("n_build", [65535, 65536, 131071, 131072, 262143, 262144])
 @pytest.mark.parametrize("key,pay", [(torch.int32, torch.int32), (torch.int32, torch.int64), (torch.int64, torch.int64)])
 @pytest.mark.parametrize("shape", ["distinct", "repeated"])
@@ -60,6 +60,29 @@ def test_hash_probe_paths(gpu, n_build, key, pay, shape):
         assert_exact(inp, res)
         cnt = run(inp, ("hash", eg.GLOBAL_HASH, 0, 0, 0.5), count_only=True)
         assert (cnt.count, cnt.checksum) == (res.count, res.checksum)
+
+
+@pytest.mark.parametrize("repeats", [1, 2])
+def test_hash_probe_of_a_far_table(gpu, repeats):
+    """A 4 GiB table of 32-byte slots: counted by the rows' probe, pairs by it (distinct
+    keys) or by the waves (repeated ones). Count and checksum in closed form."""
+    print(f"[far] {repeats}", flush=True)
+    n, n_probe = (1 << 26) + 2, (1 << 20) + 77
+    nd = n // repeats
+    keys = torch.arange(nd, device=gpu).repeat(repeats) * 0x9E3779B97F4A7C1 - (1 << 60)
+    bp = (torch.arange(nd, device=gpu) % 1009 - 500).repeat(repeats)
+    hit = torch.randint(0, nd + nd // 4, (n_probe,), generator=torch.Generator().manual_seed(3)).to(gpu)
+    pk, pp = hit * 0x9E3779B97F4A7C1 - (1 << 60), torch.arange(n_probe, device=gpu) % 777 - 300
+    found = hit < nd
+    want = (int(found.sum()) * repeats, int((pp * (hit % 1009 - 500))[found].sum()) * repeats)
+    plan = eg.join_plan(eg.stats(keys), eg.stats(pk), eg.SEL_FORCED, eg.make_plan(eg.GLOBAL_HASH, 0, 0, 0.5))
+    cnt = eg.join(keys, bp, pk, pp, plan, count_only=True)
+    assert (cnt.count, cnt.checksum) == want
+    res = eg.join(keys, bp, pk, pp, plan)
+    assert (res.count, res.checksum) == want
+    b, p = res.build_rowid.long(), res.probe_rowid.long()
+    assert torch.equal(keys[b], pk[p])
+    assert torch.unique((b << 32) | p).numel() == want[0]
 
 
 def test_hash_pairs_of_repeated_keys_time(gpu):
