@@ -37,6 +37,7 @@ namespace {
 
 constexpr uint32_t kBuildTile = 2048;
 constexpr int kBNT = 256;
+constexpr uint64_t kFarBytes = 2ull << 30;
 constexpr uint32_t kVarDirect = 0, kVarHash = 1, kVarRadix = 2;
 
 struct BatchJoinDev {
@@ -261,7 +262,8 @@ struct BatchHashTab {
 // together (256 joins of 2^8..2^18 build rows: 1.11 ms; 1.19 when each wave took its
 // own output, for four times the atomics on a join's cursor; 1.81 with a row's walk
 // held to its end by its wave). Bound by the random reads of the tables that
-// exceed an XCD's L2.
+// exceed an XCD's L2. Tables beyond kFarBytes: one slot of a row at first (89.9M 64-bit
+// build rows, an 8 GiB table, 180M probes: the batch 18.9 ms, 21.4 with two).
 template <typename K, typename P>
 __global__ void __launch_bounds__(kBNT) k_batch_probe(XcdItems items, const BatchJoinDev *__restrict__ J,
                                                       BatchState *__restrict__ st, const Slot<K, P> *__restrict__ arena,
@@ -284,8 +286,13 @@ __global__ void __launch_bounds__(kBNT) k_batch_probe(XcdItems items, const Batc
       p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, joint);
     } else {
       const BatchHashTab<K, P> tab{arena + d.tab_off, d.slots - 1};
-      WaveProbe<BatchHashTab<K, P>, K, P, 2, true> p(tab, L[wave], o);
-      p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, joint);
+      if (d.slots * sizeof(Slot<K, P>) <= kFarBytes) {
+        WaveProbe<BatchHashTab<K, P>, K, P, 2, true> p(tab, L[wave], o);
+        p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, joint);
+      } else {  // two slots at first would be two address translations in flight for every row
+        WaveProbe<BatchHashTab<K, P>, K, P, 1, true> p(tab, L[wave], o);
+        p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, joint);
+      }
     }
   }
 }

@@ -93,6 +93,29 @@ def test_batch_agrees_with_single_joins(gpu):
     assert not flags.any()
 
 
+def test_batch_of_a_far_table(gpu):
+    """64-bit build keys whose open-addressing table takes 8 GiB, probed one slot of a row
+    at first, beside a small join; count and checksum in closed form."""
+    print("[batch] far table", flush=True)
+    n, n_probe = (1 << 26) + 3, (1 << 20) + 77
+    small = synth.batched_join(8, 1, 8.0, 10.0, device=gpu)
+    small = tuple(t.long() for t in as_tuple(small))
+    keys = torch.arange(n, device=gpu) * 0x9E3779B97F4A7C1 - (1 << 60)
+    bp = torch.arange(n, device=gpu) % 1009 - 500
+    hit = torch.randint(0, n + n // 4, (n_probe,), generator=torch.Generator().manual_seed(3)).to(gpu)
+    pk, pp = hit * 0x9E3779B97F4A7C1 - (1 << 60), torch.arange(n_probe, device=gpu) % 777 - 300
+    b = eg.Batch([small, (keys, bp, pk, pp)])
+    b.launch()
+    counts, sums, variants, flags = b.results()
+    found = hit < n
+    want = int(found.sum())
+    assert (counts[1], sums[1]) == (want, int((pp * (hit % 1009 - 500))[found].sum()))
+    assert variants[1] == eg.GLOBAL_HASH and not flags.any()
+    ob, op = (t.long() for t in b.pairs(1, want))
+    assert torch.equal(keys[ob], pk[op]) and torch.unique(op).numel() == want
+    assert (counts[0], sums[0]) == oracle.join_sortmerge(*small)[1:]
+
+
 def test_batch_rejects_bad_descriptors(gpu):
     inp = synth.batched_joins(7, 2, device=gpu)
     with pytest.raises(eg.EigerError):
