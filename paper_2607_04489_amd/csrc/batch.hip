@@ -19,11 +19,14 @@
 //             its own output range; a collect kernel copies their counters
 // Stages never wait on each other inside a kernel, so no workgroup spins.
 //
-// The items of a join lie together in the lists, and each XCD takes one
-// contiguous part of them (equal shares of rows), so that a join's table is built
-// and probed through one L2: random 16-byte reads run at 255 G/s from 4 MB of
-// table and at 59 G/s from 64 MB. (256 joins of 2^8..2^18 build rows, items dealt
-// to all XCDs: the same 1.81 ms with the probe of that time.)
+// Each XCD takes one contiguous part of the joins (equal shares of rows), so that a
+// join's table is built and probed through one L2: random 16-byte reads run at 255 G/s
+// from 4 MB of table and at 59 G/s from 64 MB. (A batch of 256 joins of 2^8..2^18 build
+// rows 2.00 ms, 2.28 with items dealt to all XCDs; 64 joins of 2^16..2^18 2.10 and 2.32.)
+// Joins whose table exceeds kSharedBytes are dealt: eight tables at a time do not fit
+// the 256 MB memory-side cache, one does (eight joins of 2^20 build rows, 64-bit columns,
+// 128 MiB tables: 2.75 ms, 2.91 to 3.03 in parts; 32-bit ones, 64 MiB tables: 2.17 either
+// way, but with 90% of the probes on one key 1.28 in parts and 1.48 dealt).
 #include <algorithm>
 #include <type_traits>
 #include <vector>
@@ -37,7 +40,7 @@ namespace {
 
 constexpr uint32_t kBuildTile = 2048;
 constexpr int kBNT = 256;
-constexpr uint64_t kFarBytes = 2ull << 30;
+constexpr uint64_t kSharedBytes = 64ull << 20, kFarBytes = 2ull << 30;
 constexpr uint32_t kVarDirect = 0, kVarHash = 1, kVarRadix = 2;
 
 struct BatchJoinDev {
@@ -331,14 +334,41 @@ struct RadixJob {
   size_t ws_off, ws_bytes;
 };
 
+// Work items in the order of the XCDs that take them: XCD x's are [first[x], first[x + 1]).
+struct XcdList {
+  std::vector<Item> items;
+  uint32_t first[kXcds + 1];
+};
+
 // Host-side description of a batch (descriptors, work items, sizes).
 struct BatchPlan {
   std::vector<BatchJoinDev> joins;
-  std::vector<Item> build, probe;
+  XcdList build, probe;
   std::vector<RadixJob> radix;
   uint64_t arena_slots = 0, out_total = 0;
   size_t radix_ws = 0;
 };
+
+// Puts the items of a batch's joins in the XCDs' order: those of joins with tables up to
+// kSharedBytes in one contiguous part per XCD, of equal rows, the others dealt to all.
+void order_items(XcdList &l, const std::vector<BatchJoinDev> &joins, size_t slot) {
+  std::vector<Item> own, shared;
+  uint64_t total = 0, run = 0;
+  for (const Item &i : l.items) {
+    const bool big = joins[i.join].slots * slot > kSharedBytes;
+    (big ? shared : own).push_back(i);
+    if (!big) total += i.hi - i.lo;
+  }
+  l.items.clear();
+  size_t at = 0;
+  for (uint32_t k = 0; k < kXcds; ++k) {
+    l.first[k] = static_cast<uint32_t>(l.items.size());
+    const uint64_t upto = total / kXcds * (k + 1) + total % kXcds * (k + 1) / kXcds;
+    while (at < own.size() && run < upto) run += own[at].hi - own[at].lo, l.items.push_back(own[at++]);
+    for (size_t i = k; i < shared.size(); i += kXcds) l.items.push_back(shared[i]);
+  }
+  l.first[kXcds] = static_cast<uint32_t>(l.items.size());
+}
 
 int plan_batch(const eiger_batch_join *joins, int32_t n, int32_t kdt, int32_t pdt, const eiger_batch_tune *tune,
                BatchPlan *bp) {
@@ -403,13 +433,15 @@ int plan_batch(const eiger_batch_join *joins, int32_t n, int32_t kdt, int32_t pd
     bp->out_total += uint64_t(q.n_probe);
     bp->arena_slots += slots;
     for (uint64_t lo = 0; lo < uint64_t(q.n_build); lo += kBuildTile)
-      bp->build.push_back(Item{uint32_t(j), 0, lo, std::min<uint64_t>(q.n_build, lo + kBuildTile)});
+      bp->build.items.push_back(Item{uint32_t(j), 0, lo, std::min<uint64_t>(q.n_build, lo + kBuildTile)});
     if (q.n_build > 0)
       for (uint64_t lo = 0; lo < uint64_t(q.n_probe); lo += uint64_t(t.probe_tile))
-        bp->probe.push_back(Item{uint32_t(j), 0, lo, std::min<uint64_t>(q.n_probe, lo + t.probe_tile)});
+        bp->probe.items.push_back(Item{uint32_t(j), 0, lo, std::min<uint64_t>(q.n_probe, lo + t.probe_tile)});
   }
-  if (bp->build.size() >= (1ull << 32) || bp->probe.size() >= (1ull << 32))
+  if (bp->build.items.size() >= (1ull << 32) || bp->probe.items.size() >= (1ull << 32))
     return fail(EIGER_ERR_TOO_LARGE, "batch: too many work items");
+  order_items(bp->build, bp->joins, slot_bytes(kdt, pdt));
+  order_items(bp->probe, bp->joins, slot_bytes(kdt, pdt));
   return EIGER_OK;
 }
 
@@ -425,8 +457,8 @@ BatchLayout batch_layout(Workspace &ws, const BatchPlan &bp, size_t slot_bytes_)
   BatchLayout L;
   L.joins = ws.take<BatchJoinDev>(bp.joins.size());
   L.state = ws.take<BatchState>(bp.joins.size());
-  L.build = ws.take<Item>(std::max<size_t>(bp.build.size(), 1));
-  L.probe = ws.take<Item>(std::max<size_t>(bp.probe.size(), 1));
+  L.build = ws.take<Item>(std::max<size_t>(bp.build.items.size(), 1));
+  L.probe = ws.take<Item>(std::max<size_t>(bp.probe.items.size(), 1));
   L.arena = ws.take<char>(bp.arena_slots * slot_bytes_);
   L.radix_ws = ws.take<char>(bp.radix_ws);
   return L;
@@ -439,19 +471,10 @@ struct BatchHandle {
   BatchState *state = nullptr;
 };
 
-// Splits a list of work items into one contiguous part per XCD, of equal rows.
-XcdItems xcd_items(const std::vector<Item> &v, const Item *dev) {
+XcdItems xcd_items(const XcdList &l, const Item *dev) {
   XcdItems x{};
   x.items = dev;
-  uint64_t total = 0, run = 0;
-  for (const Item &i : v) total += i.hi - i.lo;
-  uint32_t at = 0;
-  for (uint32_t k = 0; k < kXcds; ++k) {
-    x.first[k] = at;
-    const uint64_t upto = total / kXcds * (k + 1) + total % kXcds * (k + 1) / kXcds;
-    while (at < v.size() && run < upto) run += v[at].hi - v[at].lo, ++at;
-  }
-  x.first[kXcds] = static_cast<uint32_t>(v.size());
+  std::copy(l.first, l.first + kXcds + 1, x.first);
   return x;
 }
 
@@ -463,7 +486,7 @@ unsigned xcd_grid(unsigned n, unsigned cus, unsigned per_cu) {
 template <typename K, typename P>
 int enqueue_batch(const BatchPlan &bp, const BatchLayout &L, uint32_t *ob, uint32_t *op, hipStream_t s) {
   const int n = static_cast<int>(bp.joins.size());
-  const unsigned nb = static_cast<unsigned>(bp.build.size()), np = static_cast<unsigned>(bp.probe.size());
+  const unsigned nb = static_cast<unsigned>(bp.build.items.size()), np = static_cast<unsigned>(bp.probe.items.size());
   const unsigned cus = static_cast<unsigned>(device_cu_count());
   const XcdItems bi = xcd_items(bp.build, L.build), pi = xcd_items(bp.probe, L.probe);
   int rc;
@@ -537,10 +560,9 @@ extern "C" int eiger_join_batch_create(const eiger_batch_join *joins, int32_t n_
   hipStream_t s = static_cast<hipStream_t>(stream);
   // descriptors and work items, copied once (outside the graph)
   EIGER_HIP(hipMemcpyAsync(L.joins, bp.joins.data(), bp.joins.size() * sizeof(BatchJoinDev), hipMemcpyHostToDevice, s));
-  if (!bp.build.empty())
-    EIGER_HIP(hipMemcpyAsync(L.build, bp.build.data(), bp.build.size() * sizeof(Item), hipMemcpyHostToDevice, s));
-  if (!bp.probe.empty())
-    EIGER_HIP(hipMemcpyAsync(L.probe, bp.probe.data(), bp.probe.size() * sizeof(Item), hipMemcpyHostToDevice, s));
+  for (const auto &[list, dev] : {std::pair<const XcdList &, Item *>(bp.build, L.build), {bp.probe, L.probe}})
+    if (!list.items.empty())
+      EIGER_HIP(hipMemcpyAsync(dev, list.items.data(), list.items.size() * sizeof(Item), hipMemcpyHostToDevice, s));
   EIGER_HIP(hipStreamSynchronize(s));
   auto *h = new BatchHandle();
   h->n = n_joins;

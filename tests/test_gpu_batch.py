@@ -93,6 +93,24 @@ def test_batch_agrees_with_single_joins(gpu):
     assert not flags.any()
 
 
+def test_batch_of_small_and_large_tables(gpu):
+    """Joins with tables above 64 MiB, whose items are dealt to all XCDs, between joins
+    whose items lie in one XCD's part, dense and sparse, the last one empty."""
+    inputs = synth.batched_joins(9, 9, log2_lo=4.0, log2_hi=12.0, device=gpu)
+    for j in (2, 5):  # 128 MiB of 16-byte slots, open addressing and direct
+        n = (1 << 21) + 5
+        keys = torch.arange(n, device=gpu) * (977 if j == 2 else 1)
+        pk = torch.randint(0, n + n // 4, (700_001,), generator=torch.Generator().manual_seed(j)).to(gpu) * (977 if j == 2 else 1)
+        inputs[j] = synth.JoinInput("large", keys.int(), (keys % 1009 - 500).int(), pk.int(),
+                                    (torch.arange(pk.numel(), device=gpu) % 777 - 300).int())
+    inputs[8] = synth.JoinInput("empty", inputs[8].build_keys, inputs[8].build_payload, inputs[8].probe_keys[:0],
+                                inputs[8].probe_payload[:0])
+    b = eg.Batch([as_tuple(i) for i in inputs], tune={b: (0.25, 16384) for b in range(33)})
+    b.launch()
+    _, _, variants, _ = check_batch(b, inputs)
+    assert (variants[2], variants[5]) == (eg.GLOBAL_HASH, eg.DIRECT)
+
+
 def test_batch_of_a_far_table(gpu):
     """64-bit build keys whose open-addressing table takes 8 GiB, probed one slot of a row
     at first, beside a small join; count and checksum in closed form."""
