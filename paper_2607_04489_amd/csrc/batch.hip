@@ -40,6 +40,9 @@ namespace {
 
 constexpr uint32_t kBuildTile = 2048;
 constexpr int kBNT = 256;
+// Pairs a probe wave stages. Sixteen waves a CU for every type would leave 312 of 8-byte
+// keys and payloads (eight joins of 2^20 rows: 2.2 ms for 2.1; the narrow types gain 1%).
+constexpr uint32_t kBStage = 504;
 constexpr uint64_t kSharedBytes = 64ull << 20, kFarBytes = 2ull << 30;
 constexpr uint32_t kVarDirect = 0, kVarHash = 1, kVarRadix = 2;
 
@@ -271,7 +274,7 @@ template <typename K, typename P>
 __global__ void __launch_bounds__(kBNT) k_batch_probe(XcdItems items, const BatchJoinDev *__restrict__ J,
                                                       BatchState *__restrict__ st, const Slot<K, P> *__restrict__ arena,
                                                       uint32_t *ob, uint32_t *op) {
-  __shared__ WaveLds<K, P, true> L[kBNT / 64];
+  __shared__ WaveLds<K, P, kBStage> L[kBNT / 64];
   __shared__ WaveJoint<kBNT / 64> joint;
   const uint32_t wave = threadIdx.x / 64;
   constexpr uint64_t block = 64 * kWaveRows, sub = kBNT * kWaveRows;
@@ -285,15 +288,15 @@ __global__ void __launch_bounds__(kBNT) k_batch_probe(XcdItems items, const Batc
     if (s->variant == kVarDirect) {
       const uint64_t mn = static_cast<uint64_t>(s->mn);
       const BatchDirectTab<K, P> tab{arena + d.tab_off, mn, static_cast<uint64_t>(s->mx) - mn + 1};
-      WaveProbe<BatchDirectTab<K, P>, K, P, 1, true> p(tab, L[wave], o);
+      WaveProbe<BatchDirectTab<K, P>, K, P, 1, kBStage> p(tab, L[wave], o);
       p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, joint);
     } else {
       const BatchHashTab<K, P> tab{arena + d.tab_off, d.slots - 1};
       if (d.slots * sizeof(Slot<K, P>) <= kFarBytes) {
-        WaveProbe<BatchHashTab<K, P>, K, P, 2, true> p(tab, L[wave], o);
+        WaveProbe<BatchHashTab<K, P>, K, P, 2, kBStage> p(tab, L[wave], o);
         p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, joint);
       } else {  // two slots at first would be two address translations in flight for every row
-        WaveProbe<BatchHashTab<K, P>, K, P, 1, true> p(tab, L[wave], o);
+        WaveProbe<BatchHashTab<K, P>, K, P, 1, kBStage> p(tab, L[wave], o);
         p.template run<kBNT / 64>(pk, pp, nullptr, w.lo + wave * block, w.hi, sub, joint);
       }
     }
@@ -505,7 +508,7 @@ int enqueue_batch(const BatchPlan &bp, const BatchLayout &L, uint32_t *ob, uint3
                  L.state, arena);
   }
   if (np) {
-    EIGER_LAUNCH("batch_probe", (k_batch_probe<K, P>), dim3(xcd_grid(np, cus, static_cast<unsigned>(163840 / (sizeof(WaveLds<K, P, true>) * (kBNT / 64))))), dim3(kBNT), 0, s,
+    EIGER_LAUNCH("batch_probe", (k_batch_probe<K, P>), dim3(xcd_grid(np, cus, static_cast<unsigned>(163840 / (sizeof(WaveLds<K, P, kBStage>) * (kBNT / 64))))), dim3(kBNT), 0, s,
                  pi, L.joins, L.state, static_cast<const Slot<K, P> *>(L.arena), ob, op);
   }
   for (const RadixJob &job : bp.radix) {

@@ -102,23 +102,37 @@ __device__ __forceinline__ void finish(EmitLds<NT, SCAP> &L, const EmitOut &o, u
 //
 // A wave probes on its own. Rows are taken 64 * kWaveRows at a time, their first
 // kEager slots loaded at once. Rows whose walk goes on are packed into a queue in
-// LDS, from which full waves take the next slots of 64 * kWaveQueued rows, two at a time. So
-// every round trip carries full waves; when a wave walked its rows until the last
-// one ended, it made 8 to 10 for rows that need 1.5 on average. A match is staged
-// the moment it is found. Bound by random accesses: 255 G/s of them from a table
-// in an XCD's L2, 55-59 G/s from a larger one.
+// LDS, and as soon as it holds a full wave of them the next slots of up to
+// 64 * kWaveQueued rows are loaded, two at a time. So every round trip carries full
+// waves; when a wave walked its rows until the last one ended, it made 8 to 10 for rows
+// that need 1.5 on average. A match is staged the moment it is found. Bound by random
+// accesses: 255 G/s of them from a table in an XCD's L2, 55-59 G/s from a larger one.
+//
+// Probes that find their slots in the L1 (sorted ones, one key) are bound by what comes
+// between the loads instead: the stage is written out by the whole workgroup, so it
+// holds more than one block's matches, and a queue of one wave's rows, not of two,
+// leaves the LDS for that and for more waves (2^23 sorted probes of 60,000 int32 keys,
+// int64 payloads: 140 us; with stages of 504 pairs, 12 waves a CU and queues of 384
+// rows 199; probes in random order 165 and 216).
 constexpr int kWaveRows = 4;     // rows a lane takes from the input together
 constexpr int kWaveQueued = 2;   // rows a lane takes from the queue together
-constexpr uint32_t kWaveStage = 504;
-static_assert(kWaveStage >= 64 * kWaveRows && kWaveStage >= 64 * 2 * kWaveQueued, "a step's matches fit an empty stage");
-constexpr uint32_t kWaveQueue = 64 * (kWaveRows + kWaveQueued);
+constexpr uint32_t kWaveFull = 64;  // queued rows that are not left for later
+constexpr uint32_t kWaveQueue = 64 * kWaveRows + kWaveFull;
+// Pairs that each wave can stage when `waves` of them share a CU's LDS (160 KB, of
+// which 1 KB is left for what the workgroups share).
+template <typename K, typename PS>
+constexpr uint32_t wave_stage(uint32_t waves) {
+  return ((163840 - 1024) / waves - kWaveQueue * (sizeof(K) + sizeof(PS) + 8)) / 16 * 2;
+}
 
-template <typename K, typename PS, bool kPairs>
+template <typename K, typename PS, uint32_t kStage>
 struct WaveLds {
+  static_assert(kStage == 0 || (kStage >= 64 * kWaveRows && kStage >= 64 * 2 * kWaveQueued),
+                "a step's matches fit an empty stage");
   K key[kWaveQueue];
   PS pay[kWaveQueue];
   uint32_t row[kWaveQueue], step[kWaveQueue];
-  uint32_t ob[kPairs ? kWaveStage : 1], op[kPairs ? kWaveStage : 1];
+  uint32_t ob[kStage ? kStage : 1], op[kStage ? kStage : 1];
 };
 
 // What the waves of a workgroup share to write their stages out together; two
@@ -139,19 +153,20 @@ __device__ __forceinline__ void wave_lds_fence() {
 
 // Tab: SlotT, Index; start(key, in) -> first slot (in: false when the key cannot be
 // there), walk(first, steps) -> the slot `steps` further, load(slot); kWalk: keys may
-// lie further on; unique: build keys known to be distinct. kPairs: matches are staged
-// and written out (o.ob, o.op given); else they are counted only.
-template <class Tab, typename K, typename PS, int kEager, bool kPairs>
+// lie further on; unique: build keys known to be distinct. kStage: pairs staged
+// before they are written out (o.ob, o.op given); 0: matches are counted only.
+template <class Tab, typename K, typename PS, int kEager, uint32_t kStage>
 struct WaveProbe {
+  static constexpr bool kPairs = kStage > 0;
   static_assert(kEager == 1 || kEager == 2, "one or two slots at first");
   const Tab &tab;
-  WaveLds<K, PS, kPairs> &L;
+  WaveLds<K, PS, kStage> &L;
   const EmitOut &o;
   uint64_t fill = 0;    // staged pairs, or all pairs counted (uniform)
   uint32_t queued = 0;  // uniform
   uint64_t cs = 0;      // this lane's share of the checksum
 
-  __device__ __forceinline__ WaveProbe(const Tab &t, WaveLds<K, PS, kPairs> &l, const EmitOut &e) : tab(t), L(l), o(e) {}
+  __device__ __forceinline__ WaveProbe(const Tab &t, WaveLds<K, PS, kStage> &l, const EmitOut &e) : tab(t), L(l), o(e) {}
 
   // The staged pairs to output positions base, base + 1, ...
   __device__ __forceinline__ void write_out(uint64_t base) {
@@ -162,7 +177,7 @@ struct WaveProbe {
   }
 
   // Whether the stage takes R more matches a lane.
-  __device__ __forceinline__ bool room(int R) const { return !kPairs || fill + 64 * R <= kWaveStage; }
+  __device__ __forceinline__ bool room(int R) const { return !kPairs || fill + 64 * R <= kStage; }
 
   // Whether the second slot of rows already looked at once can be looked at before the
   // stage is written out: distinct build keys match once in all their slots, so that
@@ -277,7 +292,7 @@ struct WaveProbe {
     if (t < hi) load(t);
     for (uint32_t round = 0;; ++round) {
       for (;;) {
-        if (Tab::kWalk && (queued >= 64 * kWaveQueued || (t >= hi && queued))) {
+        if (Tab::kWalk && (queued >= kWaveFull || (t >= hi && queued))) {
           if (!room(kWaveQueued)) break;
           if constexpr (Tab::kWalk) advance(queued < 64 * kWaveQueued ? queued : 64 * kWaveQueued);
         } else if (t < hi) {

@@ -24,9 +24,16 @@ namespace {
 // Table sizes at which the probe changes (see hash_impl).
 constexpr uint64_t kNearBytes = 8u << 20, kFarBytes = 2ull << 30;
 
-// Probe workgroup: two share a CU's 160 KB of LDS.
-template <typename K, typename PS>
-constexpr int kPNT = sizeof(K) + sizeof(PS) == 8 ? 512 : 384;
+// Probe workgroups of a CU, their threads, and the pairs that a wave stages in the LDS
+// that the queues leave: 632 of 4-byte keys and payloads in 16 waves a CU; 652 where one
+// has 8 bytes, 492 where both have, in 14 (16 waves with fewer pairs, 2^23 probes of one
+// int32 key with int64 payloads: 10% slower). Counting takes 24 or 16.
+template <typename K, typename PS, bool kPairs>
+constexpr int kPPerCu = !kPairs && sizeof(K) + sizeof(PS) == 8 ? 3 : 2;
+template <typename K, typename PS, bool kPairs>
+constexpr int kPNT = kPairs && sizeof(K) + sizeof(PS) > 8 ? 448 : 512;
+template <typename K, typename PS, bool kPairs>
+constexpr uint32_t kPStage = kPairs ? wave_stage<K, PS>(kPNT<K, PS, true> / 64 * kPPerCu<K, PS, true>) : 0;
 
 template <typename K, typename PB>
 struct HashTab {
@@ -198,21 +205,24 @@ bool hash_sentinel(const JoinArgs &a, K *out) {
 // whole blocks), its waves taking blocks in turn. repeated_only: tables of distinct
 // keys are k_probe_rows'.
 template <class Tab, typename K, typename PS, int kEager, bool kPairs>
-__global__ void __launch_bounds__((kPNT<K, PS>)) k_probe(Tab tab, const K *__restrict__ pk,
+__global__ void __launch_bounds__((kPNT<K, PS, kPairs>)) k_probe(Tab tab, const K *__restrict__ pk,
                                                const PS *__restrict__ pp, uint64_t n, EmitOut o,
                                                bool repeated_only) {
-  __shared__ WaveLds<K, PS, kPairs> L[kPNT<K, PS> / 64];
-  __shared__ WaveJoint<kPNT<K, PS> / 64> J;
+  constexpr int kNT = kPNT<K, PS, kPairs>;
+  constexpr uint32_t kStage = kPStage<K, PS, kPairs>;
+  __shared__ WaveLds<K, PS, kStage> L[kNT / 64];
+  __shared__ WaveJoint<kNT / 64> J;
+  static_assert((sizeof(L) + sizeof(J)) * kPPerCu<K, PS, kPairs> <= 163840, "the workgroups of a CU share its LDS");
   tab.init();
   if (repeated_only && tab.unique) return;
-  constexpr uint64_t block = 64 * kWaveRows, sub = kPNT<K, PS> * kWaveRows;
+  constexpr uint64_t block = 64 * kWaveRows, sub = kNT * kWaveRows;
   const uint32_t w = threadIdx.x / 64;
   const uint64_t nsub = (n + sub - 1) / sub;
   const uint64_t per = (nsub + gridDim.x - 1) / gridDim.x;
   const uint64_t lo = blockIdx.x * per * sub;
   const uint64_t hi = lo + per * sub < n ? lo + per * sub : n;
-  WaveProbe<Tab, K, PS, kEager, kPairs> p(tab, L[w], o);
-  p.template run<kPNT<K, PS> / 64>(pk, pp, nullptr, lo + w * block, hi, sub, J);
+  WaveProbe<Tab, K, PS, kEager, kStage> p(tab, L[w], o);
+  p.template run<kNT / 64>(pk, pp, nullptr, lo + w * block, hi, sub, J);
 }
 
 constexpr int kRowNT = 256;
@@ -238,12 +248,6 @@ __global__ void __launch_bounds__(kRowNT) k_probe_rows(HashRowTab<K, PB> tab, co
   finish(L, o, fill, cs);
 }
 
-// Workgroups of a CU by the LDS they take (160 KB).
-template <typename K, typename PS, bool kPairs>
-constexpr int probe_per_cu() {
-  return static_cast<int>(163840 / (sizeof(WaveLds<K, PS, kPairs>) * (kPNT<K, PS> / 64) + sizeof(WaveJoint<kPNT<K, PS> / 64>)));
-}
-
 unsigned grid_for(uint64_t work, uint64_t per_block, int per_cu) {
   uint64_t g = (work + per_block - 1) / per_block;
   const uint64_t cap = uint64_t(device_cu_count()) * per_cu;
@@ -254,8 +258,8 @@ unsigned grid_for(uint64_t work, uint64_t per_block, int per_cu) {
 template <typename K, typename PB, typename PS, int kEager, bool kPairs>
 int launch_probe(const HashTab<K, PB> &tab, const K *pk, const PS *pp, uint64_t n, const EmitOut &o, bool repeated_only,
                  hipStream_t s) {
-  const dim3 grid(grid_for(n, uint64_t(kPNT<K, PS>) * kWaveRows, probe_per_cu<K, PS, kPairs>()));
-  EIGER_LAUNCH("hash_probe", (k_probe<HashTab<K, PB>, K, PS, kEager, kPairs>), grid, dim3(kPNT<K, PS>), 0, s, tab, pk, pp, n, o,
+  const dim3 grid(grid_for(n, uint64_t(kPNT<K, PS, kPairs>) * kWaveRows, kPPerCu<K, PS, kPairs>));
+  EIGER_LAUNCH("hash_probe", (k_probe<HashTab<K, PB>, K, PS, kEager, kPairs>), grid, dim3(kPNT<K, PS, kPairs>), 0, s, tab, pk, pp, n, o,
                repeated_only);
   return EIGER_OK;
 }
@@ -315,10 +319,10 @@ int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   // Tables near an XCD's L2 are bound by the L1's fills, and a second slot of every row
   // costs more of them than it saves; from larger ones it comes with the first; beyond
   // 2 GiB two slots are two address translations in flight instead of one. With 32-byte
-  // slots the rows' probe has 16 waves a CU to the waves' 12 where pairs are written. It
-  // is behind from 64 MiB to 2 GiB (above; 11% where hardly any probe matches) but
-  // ahead where most probes stay near, by more (90% of the probes on one key: 33.5M of a
-  // 64 MiB table 0.49 ms for 0.60, 134M of a 1 GiB table 3.13 for 3.53). Walks among
+  // slots the rows' probe, whose workgroups write out every 1,024 rows' matches
+  // together, is the slower one at random probes from 64 MiB to 2 GiB (above), but ahead
+  // where most probes stay near, and by more (sorted probes of 60,000 and 400,000 rows:
+  // the waves' take 1.03 to 1.09 times as long, probes of one key up to 1.28). Walks among
   // repeated keys are long, and there the waves' probe is the faster (2^22 probes of
   // 4,000 keys of 8 rows: 0.95 ms for 2.00; 2^24 of 250,000 of 4: 2.3 for 5.2). The build
   // tells which it is: both are launched, one returns at once.

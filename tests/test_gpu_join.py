@@ -36,6 +36,49 @@ def test_sparse_unique64(gpu, spec):
     assert_exact(inp, run(inp, spec))
 
 
+@pytest.mark.parametrize("key,bpay,ppay", [(torch.int32, torch.int32, torch.int32), (torch.int32, torch.int64, torch.int64),
+                                           (torch.int64, torch.int32, torch.int32), (torch.int64, torch.int32, torch.int64)])
+@pytest.mark.parametrize("order", ["sorted", "one key"])
+def test_hash_probes_that_stay_near(gpu, order, key, bpay, ppay):
+    """Probes in key order and probes of one key, all matching: every block fills a wave's
+    stage by the same amount, in workgroups of each shape, one row short of and beyond
+    their shares."""
+    g = torch.Generator().manual_seed(9)
+    keys = torch.randperm(400_000, generator=g) * 4999 - 77
+    for n_probe in (7 * 256 * 3 - 1, 8 * 256 * 5 + 1, 3_000_001):
+        hit = torch.randint(0, 400_000, (n_probe,), generator=g).sort().values if order == "sorted" else torch.full((n_probe,), 5)
+        inp = synth.JoinInput("near", keys.to(key).to(gpu), torch.randint(-999, 999, (400_000,), generator=g).to(bpay).to(gpu),
+                              (hit * 4999 - 77).to(key).to(gpu), torch.randint(-999, 999, (n_probe,), generator=g).to(ppay).to(gpu))
+        res = run(inp, ("hash", eg.GLOBAL_HASH, 0, 0, 0.5))
+        assert_exact(inp, res)
+        cnt = run(inp, ("hash", eg.GLOBAL_HASH, 0, 0, 0.5), count_only=True)
+        assert (cnt.count, cnt.checksum) == (res.count, res.checksum)
+
+
+def test_hash_sorted_probes_of_wide_payloads_time(gpu):
+    """Sorted probes, pairs: 8-byte payloads take no more over 4-byte ones than their
+    share of the bytes, 20 to 16 a row (1.5 times while fewer waves staged fewer pairs)."""
+    g = torch.Generator(device=gpu).manual_seed(1)
+    n = 1 << 23
+    bk = (torch.randperm(60_000, generator=g, device=gpu) * 4999 - 77).int()
+    pk = bk[torch.randint(0, 60_000, (n,), generator=g, device=gpu)].sort().values
+    pays, outs = [torch.ones(n, dtype=t, device=gpu) for t in (torch.int32, torch.int64)], [torch.empty_like(pk) for _ in range(2)]
+    plan = eg.join_plan(eg.stats(bk), eg.stats(pk), eg.SEL_FORCED, eg.make_plan(eg.GLOBAL_HASH, 0, 0, 0.5))
+    ws = torch.empty(eg.join_workspace_size(plan, bk, bk, pk, pays[1]), dtype=torch.uint8, device=gpu)
+
+    def call(pp):
+        start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        assert eg.join(bk, bk, pk, pp, plan, workspace=ws, outputs=outs).count == n
+        stop.record()
+        stop.synchronize()
+        return start.elapsed_time(stop)
+
+    t = [[call(pp) for pp in pays] for _ in range(15)]
+    narrow, wide = (min(x) for x in zip(*t))
+    assert wide < 1.25 * narrow, (wide, narrow)
+
+
 # Build rows of which one more doubles the table at load factor 0.5. 16-byte slots: 2 to
 # 16 MiB, from 16 on the probe loads two slots of a row at first; 32-byte slots: 4 to 32
 # MiB, pairs of distinct keys by the rows' own probe, the others from 16 on two slots.
