@@ -319,7 +319,7 @@ int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   // Tables near an XCD's L2 are bound by the L1's fills, and a second slot of every row
   // costs more of them than it saves; from larger ones it comes with the first; beyond
   // 2 GiB two slots are two address translations in flight instead of one. With 32-byte
-  // slots the rows' probe, whose workgroups write out every 1,024 rows' matches
+  // slots the rows' probe, whose workgroups write out every 1,280 rows' matches
   // together, is the slower one at random probes from 64 MiB to 2 GiB (above), but ahead
   // where most probes stay near, and by more (sorted probes of 60,000 and 400,000 rows:
   // the waves' take 1.03 to 1.09 times as long, probes of one key up to 1.28). Walks among
