@@ -781,7 +781,7 @@ int de_launch_insert(const DictBufs &d, const void *a, const void *b, uint64_t n
 template <typename K>
 int de_launch_discover(const DictBufs &d, const void *a, uint64_t n, hipStream_t s) {
   if (n == 0) return EIGER_OK;
-  // twice the global table's slots, so that the LDS table is at most a quarter full
+  // twice the global table's slots: at most a quarter full, half where that is kDsSlots
   const uint32_t slots = static_cast<uint32_t>(std::min<uint64_t>(2 * (d.t.mask + 1), kDsSlots));
   const uint64_t span = uint64_t(kDsNT) * kDsRows;
   const unsigned grid = static_cast<unsigned>(std::min<uint64_t>((n + span - 1) / span, uint64_t(device_cu_count()) * 4));
@@ -834,7 +834,7 @@ int dict_steps(const eiger_skf_plan_t &p, const eiger_column *ka, const eiger_co
     Workspace sw(sort_ws, sort_ws_size);
     int rc = radix_sort_pairs(8, d.ukey, d.uslot, ndv, p.key[c].range_bits, d.skey, d.sslot, sw, s);
     if (rc) return rc;
-    if (ndv)
+    if (ndv && !fp.lds_slots[c])  // the fusion looks those up by value
       EIGER_LAUNCH("dict_scatter", k_de_scatter, dim3(grid_for(ndv)), dim3(kDeNT), 0, s, d.sslot, ndv,
                    d.code_of_slot);
   }

@@ -228,3 +228,19 @@ def test_fuse_looks_values_up(gpu, n, dtype, slots):
         assert k.ndv == len(u)
         want |= code.astype(np.uint64) << np.uint64(k.shift)
     assert np.array_equal(host(fa).view(np.uint32 if fin.fused_bytes == 4 else np.uint64).astype(np.uint64), want)
+
+
+def test_codes_by_slot_only_where_they_are_read(gpu):
+    """One key looked up by value and one through its slots: one scatter of codes."""
+    g = torch.Generator().manual_seed(4)
+    cols = [(torch.randint(0, ndv, (50_000,), generator=g) * 40_009).int().to(gpu) for ndv in (300, 9000)]
+    plan = eg.skf_plan([eg.stats(c) for c in cols], for_max_bits=-1)
+    assert [k.code for k in plan.key[:2]] == [eg.SKF_DICT] * 2 and plan.key[0].slots <= 4096 < plan.key[1].slots
+    eg.profile_enable(True)
+    try:
+        eg.skf_fuse(cols, plan=plan)
+        torch.cuda.synchronize()
+        launches = {name: n for name, (n, _) in eg.profile_read().items()}
+    finally:
+        eg.profile_enable(False)
+    assert (launches["dict_insert"], launches["dict_scatter"]) == (2, 1)
