@@ -661,7 +661,6 @@ GbLayout gb_layout(Workspace &ws, uint64_t slots, int nv, unsigned long long sen
   L.g.sentinel = sentinel;
   L.cursor = ws.take<unsigned long long>(2);  // the flag in the second word, for one copy to the host
   L.overflow = reinterpret_cast<uint32_t *>(L.cursor + 1);
-  ws.take<uint32_t>(1);
   L.g.overflow = L.overflow;
   return L;
 }

@@ -313,7 +313,7 @@ __global__ void __launch_bounds__(kGradNT) k_mlp_grad_adam(GradLayer l1, GradLay
 
 // Inference without scratch memory: one 64-thread workgroup per row at a time,
 // hidden activations in LDS; each output is the same ordered fused sum as in
-// k_mlp_layer, so the result equals the layer-by-layer forward bit for bit.
+// k_mlp_forward_train, so the result equals the training forward bit for bit.
 __global__ void __launch_bounds__(64) k_mlp_forward_rows(const float *__restrict__ P, const float *__restrict__ x,
                                                          int batch, float *__restrict__ y) {
   __shared__ float xs[kIn], h1[kHid], h2[kHid];
@@ -340,8 +340,6 @@ __global__ void __launch_bounds__(64) k_mlp_forward_rows(const float *__restrict
     __syncthreads();
   }
 }
-
-unsigned blocks(int64_t n, int per = 256) { return static_cast<unsigned>((n + per - 1) / per); }
 
 struct TrainWs {
   float *h1, *h2, *y, *dy, *dh2, *dh1, *lossv;
