@@ -150,9 +150,15 @@ def esize(t):
     return t.element_size()
 
 
-def kernel_bytes(plan, inp, count):
+# Rows from which one pass of the radix sort's partitioning sorts up to ten bits of int32 keys.
+WIDE_DIGIT_ROWS = 512 * 512 * 20
+
+
+def kernel_bytes(plan, inp, count, launched):
     """Algorithmic bytes per step of each kernel: every input element the
-    kernel's definition consumes is read once, every output element written once."""
+    kernel's definition consumes is read once, every output element written once.
+    `launched` holds the names of the kernels that ran: a RADIX join partitions by the
+    radix sort's passes or by its own, whichever its workspace holds."""
     import paper_2607_04489_amd as eg
     nR, nS = inp.n_build, inp.n_probe
     K, PB, PS = esize(inp.build_keys), esize(inp.build_payload), esize(inp.probe_payload)
@@ -170,16 +176,20 @@ def kernel_bytes(plan, inp, count):
         b["cache_build"] = nR * (K + PB)
         b["cache_probe"] = nS * (K + PS + 4) + count * 8
     else:
-        # 4-byte payloads go through the radix sort's partition passes
-        lanes = PB == 4 and PS == 4
-        if lanes:
-            passes = -(-plan.radix_bits // (10 if K == 4 and plan.radix_bits <= 10 else 8))
-        else:
-            passes = 2 if plan.radix_bits > 10 else (1 if plan.radix_bits < 2 else plan.radix_passes)
-        b["sort_hist" if lanes else "radix_hist"] = passes * (nR + nS) * K
-        sc = (nR * (K + PB) + nS * (K + PS)) + (nR * (K + PB + 4) + nS * (K + PS + 4))
-        sc += (passes - 1) * 2 * (nR * (K + PB + 4) + nS * (K + PS + 4))
-        b["sort_scatter" if lanes else "radix_scatter"] = sc
+        lanes = "sort_scatter" in launched
+
+        def passes(n):
+            if not lanes:
+                return 2 if plan.radix_bits > 10 else (1 if plan.radix_bits < 2 else plan.radix_passes)
+            wide = K == 4 and plan.radix_bits <= 10 and n >= WIDE_DIGIT_ROWS
+            return -(-plan.radix_bits // (10 if wide else 8))
+
+        hist = scatter = 0
+        for n, P in ((nR, PB), (nS, PS)):  # the first pass makes the row ids
+            hist += passes(n) * n * K
+            scatter += n * (K + P) + n * (K + P + 4) + (passes(n) - 1) * 2 * n * (K + P + 4)
+        b["sort_hist" if lanes else "radix_hist"] = hist
+        b["sort_scatter" if lanes else "radix_scatter"] = scatter
         b["radix_join"] = nR * (K + PB + 4) + nS * (K + PS + 4) + count * 8
     return b
 
@@ -747,7 +757,7 @@ def main():
         expect_cs = int((inp.build_payload[src[hit]] * inp.probe_payload[hit]).sum())
         verified = (res.count == expect_cnt and res.checksum == expect_cs)
 
-    kb = kernel_bytes(pl, inp, res.count)
+    kb = kernel_bytes(pl, inp, res.count, prof)
     rows = []
     for name, (launches, total_ms) in prof.items():
         per_step_ms = total_ms / args.steps

@@ -4,11 +4,16 @@ same plan and the kernel's current sources."""
 import json
 import os
 import sys
+import types
+
+import pytest
+import torch
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 
 import bench  # noqa: E402
+import paper_2607_04489_amd as eg  # noqa: E402
 
 PLAN = {"variant": "global_hash", "predicted_out": 1000, "load_factor": 0.25}
 
@@ -50,3 +55,19 @@ def test_committed_records_name_their_plan():
         recs = json.load(f)
     for name, rec in recs.items():
         assert rec["kernel"] == name and isinstance(rec.get("plan"), dict) and rec["plan"]["variant"]
+
+
+@pytest.mark.parametrize("rows", [bench.WIDE_DIGIT_ROWS - 1, bench.WIDE_DIGIT_ROWS])
+def test_radix_bytes_follow_the_passes_that_ran(rows):
+    """Ten bits of int32 keys, 4-byte payloads: the join's own single pass, or the radix
+    sort's, one from WIDE_DIGIT_ROWS rows a side on and two below."""
+    col = torch.empty(0, dtype=torch.int32)
+    inp = types.SimpleNamespace(n_build=1000, n_probe=rows, build_keys=col, build_payload=col, probe_payload=col)
+    plan = eg.make_plan(eg.RADIX, 10, 1, 0.5)
+    own = bench.kernel_bytes(plan, inp, 7, {"radix_hist": 0, "radix_scatter": 0, "radix_join": 0})
+    assert "sort_scatter" not in own and own["radix_scatter"] == (1000 + rows) * 20
+    got = bench.kernel_bytes(plan, inp, 7, {"sort_hist": 0, "sort_scatter": 0, "radix_join": 0})
+    n = 1 if rows >= bench.WIDE_DIGIT_ROWS else 2
+    assert "radix_scatter" not in got
+    assert got["sort_hist"] == 4 * (2 * 1000 + n * rows)
+    assert got["sort_scatter"] == 20 * (1000 + rows) + 24 * (1000 + (n - 1) * rows)
