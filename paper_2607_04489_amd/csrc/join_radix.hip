@@ -6,14 +6,19 @@
 // here for gfx950:
 //  * Both sides are partitioned on the top bits of part_hash(key) (hashing before
 //    partitioning evens out partition sizes, as the paper does for its
-//    partitioned group-by, Section 3.3), in one or two passes of at most 9 bits.
-//  * A pass is histogram -> exclusive scan -> scatter. The scatter sorts a tile
-//    of 2048 tuples by partition in LDS first, so consecutive threads write
-//    consecutive addresses of one partition. Key, payload and row id travel
-//    together (the GFTR idea, Section 3.2: payloads follow the keys' transform),
-//    so the join phase reads only partitioned, contiguous data.
-//  * Pass 2 partitions every pass-1 partition on the next bits ("segments"); a
-//    workgroup handles a chunk of one segment.
+//    partitioned group-by, Section 3.3). Key, payload and row id travel together
+//    (the GFTR idea, Section 3.2: payloads follow the keys' transform), so the join
+//    phase reads only partitioned, contiguous data. There are two ways:
+//    - This file's own: radix_passes passes of at most ten bits, each histogram ->
+//      exclusive scan -> scatter. The scatter sorts a tile of 2048 tuples by partition
+//      in LDS first, so consecutive threads write consecutive addresses of one
+//      partition. Pass 2 partitions every pass-1 partition on the next bits
+//      ("segments"); a workgroup handles a chunk of one segment.
+//    - With 4-byte payloads on both sides, the radix sort's partition passes, least
+//      significant digit first, as many as its digits take whatever radix_passes says.
+//      They need the workspace of the first way to hold their layout (radix_impl's
+//      `end <= ws.used`): two passes' does; one pass's often does not, whose counts
+//      the sort keeps for smaller tiles.
 //  * Join: one work item per (partition, probe tile). The workgroup builds an
 //    LDS open-addressing table (multiset, CAS on the row-id word) from the
 //    partition's build rows -- in several chunks when they do not fit -- and
@@ -859,9 +864,10 @@ int radix_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   if (ws.base && (rc = zero_counters(c, s))) return rc;
   // 4-byte payloads go through the radix sort's partition passes, with the row id
   // as a second lane: 168M rows, 2^16 partitions, 1.74 ms of scatters (2.84 through the
-  // scatter below). The sides share their temporaries there; where that layout would still take more than the one above
-  // (single passes, whose count tables differ), it is not taken, so that every join
-  // keeps the workspace size of the layout above.
+  // scatter below). The sides share their temporaries there. Where that layout would
+  // still take more than the one above (single passes, whose count tables differ), it is
+  // not taken, so that every join keeps the workspace size of the layout above: this
+  // line lies at the bytes, not where the times cross.
   if constexpr (sizeof(PB) == 4 && sizeof(PS) == 4) {
     w.take<JoinCounters>(1);  // c
     uint64_t *scan = w.take<uint64_t>(scan_tmp_elems(F + 1)), *sum = w.take<uint64_t>(1);
