@@ -39,11 +39,13 @@ KERNEL_SOURCES = {
     "groupby_partition": ["groupby.hip", "common.hpp"],
 }
 # Kernel symbol fragments of each timed name (to find them in rocprofv3 output).
+# What each timed kernel is called; a hash probe of 32-byte slots launches both of its
+# kernels where pairs are written, and one returns at once.
 KERNEL_SYMBOLS = {
-    "hash_probe": "k_probe<eiger::(anonymous namespace)::HashTab", "hash_build": "k_hash_build",
-    "direct_probe": "k_probe<eiger::(anonymous namespace)::DirectTab", "radix_scatter": "k_part_scatter",
-    "radix_join": "k_radix_join", "radix_hist": "k_part_hist", "cache_probe": "k_cache_probe",
-    "stats_partial": "k_stats_partial", "sort_scatter": "k_sort_scatter", "groupby_partition": "k_gb_partition",
+    "hash_probe": ("k_probe<eiger::(anonymous namespace)::HashTab", "k_probe_rows<"), "hash_build": ("k_hash_build",),
+    "direct_probe": ("k_probe<eiger::(anonymous namespace)::DirectTab",), "radix_scatter": ("k_part_scatter",),
+    "radix_join": ("k_radix_join",), "radix_hist": ("k_part_hist",), "cache_probe": ("k_cache_probe",),
+    "stats_partial": ("k_stats_partial",), "sort_scatter": ("k_sort_scatter",), "groupby_partition": ("k_gb_partition",),
 }
 
 
@@ -87,17 +89,25 @@ def summarize_profile(d, workload, kernel, plan=None):
         return (1 << 30) / 1024.0 / max(vals)  # KiB counted per KiB copied, inverted
 
     fs, ws_ = scale("p_cfetch", "FETCH_SIZE"), scale("p_cwrite", "WRITE_SIZE")
-    sym = KERNEL_SYMBOLS[kernel]
+    launches = {}
 
-    def biggest(sub, counter):
-        v = [(int(r["Grid_Size"]), float(r["Counter_Value"])) for r in rows(sub, "run_counter_collection.csv")
-             if sym in r["Kernel_Name"] and r["Counter_Name"] == counter]
-        g = max(x for x, _ in v)
-        sel = [c for x, c in v if x == g]
-        return sum(sel) / len(sel) * 1024.0  # bytes
+    def mean(sub, counter, key):
+        v = launches[sub, counter][key]
+        return sum(v) / len(v) * 1024.0  # bytes
 
-    fetch = biggest("p_fetch", "FETCH_SIZE") * fs
-    write = biggest("p_write", "WRITE_SIZE") * ws_
+    for sub, counter in (("p_fetch", "FETCH_SIZE"), ("p_write", "WRITE_SIZE")):
+        groups = launches[sub, counter] = {}
+        for r in rows(sub, "run_counter_collection.csv"):
+            sym = next((y for y in KERNEL_SYMBOLS[kernel] if y in r["Kernel_Name"]), None)
+            if sym and r["Counter_Name"] == counter:
+                groups.setdefault((sym, int(r["Grid_Size"])), []).append(float(r["Counter_Value"]))
+    # of each of its kernels the launches of the largest grid, of these the one that read the most
+    largest = [max(k for k in launches["p_fetch", "FETCH_SIZE"] if k[0] == sym)
+               for sym in {k[0] for k in launches["p_fetch", "FETCH_SIZE"]}]
+    key = max(largest, key=lambda k: mean("p_fetch", "FETCH_SIZE", k))
+
+    fetch = mean("p_fetch", "FETCH_SIZE", key) * fs
+    write = mean("p_write", "WRITE_SIZE", key) * ws_
     stats = rows("p_trace", "run_kernel_stats.csv")
     table = []
     for r in stats:

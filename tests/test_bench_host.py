@@ -71,3 +71,23 @@ def test_radix_bytes_follow_the_passes_that_ran(rows):
     assert "radix_scatter" not in got
     assert got["sort_hist"] == 4 * (2 * 1000 + n * rows)
     assert got["sort_scatter"] == 20 * (1000 + rows) + 24 * (1000 + (n - 1) * rows)
+
+
+def test_traffic_record_is_of_the_probe_that_ran(tmp_path, capsys):
+    """Of the two probes launched for 32-byte slots the record takes the working one."""
+    def write(sub, fname, text):
+        os.makedirs(tmp_path / sub, exist_ok=True)
+        (tmp_path / sub / fname).write_text(text)
+
+    head = "Kernel_Name,Grid_Size,Counter_Name,Counter_Value\n"
+    for sub, counter, value in (("p_fetch", "FETCH_SIZE", 2000), ("p_write", "WRITE_SIZE", 700)):
+        rows = [
+            ("void eiger::(anonymous namespace)::k_probe<eiger::(anonymous namespace)::HashTab<long; long> >", 300, 3),
+            ("void eiger::(anonymous namespace)::k_probe_rows<long; long; long>", 200, value),
+            ("void eiger::(anonymous namespace)::k_probe_rows<long; long; long>", 100, 9999)]
+        write(sub, "run_counter_collection.csv", head + "".join(f"{n},{g},{counter},{v}\n" for n, g, v in rows))
+        write("p_c" + sub[2:], "run_counter_collection.csv", head + f"copy,1,{counter},{1 << 20}\n")
+    write("p_trace", "run_kernel_stats.csv", "Name,TotalDurationNs,Calls,AverageNs\n")
+    bench.summarize_profile(str(tmp_path), "w", "hash_probe", PLAN)
+    rec = json.loads(capsys.readouterr().out.splitlines()[0])
+    assert (rec["fetch_bytes_per_launch"], rec["write_bytes_per_launch"]) == (2000 * 1024, 700 * 1024)
