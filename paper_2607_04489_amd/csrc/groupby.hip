@@ -543,8 +543,8 @@ __global__ void __launch_bounds__(kGNT) k_gb_clear(GbGlobal g, int nv, unsigned 
 // estimate costs one more merge and not a global atomic per row (2^26 rows, two 4-byte
 // sums, 1,000 groups planned as one: 0.43 ms, 12.5 while every row that did not fit went
 // global; planned as 1,000: 0.39).
-// 2^28 rows, two 4-byte sums, 100 groups: 0.56 ms (5.8 TB/s; 1.47 with register
-// groups and three 64-bit LDS atomics a row); 1,000 groups: 0.91 ms (2.94), the
+// 2^28 rows, two 4-byte sums, 100 groups: 0.57 ms (5.6 TB/s; 1.47 with register
+// groups and three 64-bit LDS atomics a row); 1,000 groups: 0.90 ms (2.94), the
 // walks in the half-full table.
 template <typename K, int NV, bool W0, bool W1, bool kRuns>
 __global__ void __launch_bounds__(kANT, (2 * agg_per_cu<NV, W0>)) k_gb_hash(const K *__restrict__ keys, uint64_t n, GbVals vals, AggShape h,
@@ -573,7 +573,7 @@ __global__ void __launch_bounds__(kANT, (2 * agg_per_cu<NV, W0>)) k_gb_hash(cons
 // PARTITION: work item = one of the S equal slices of a partition (S = 1 when
 // partitions are small). A whole partition that did not spill writes its groups
 // out directly; slices and spilled partitions merge into the global table.
-// 2^28 rows, two 4-byte sums, 2^20 groups in 2^11 partitions: 0.75 ms (4.3 TB/s;
+// 2^28 rows, two 4-byte sums, 2^20 groups in 2^11 partitions: 0.72 ms (4.5 TB/s;
 // 1.78 with one row's walk at a time).
 template <typename K, int NV, bool W0, bool W1>
 __global__ void __launch_bounds__(kANT, (2 * agg_per_cu<NV, W0>))

@@ -303,28 +303,31 @@ int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   EmitOut o{a.ob, a.op, a.cap, &c->count, &c->checksum, hc->stripe};
   const K *pk = static_cast<const K *>(a.pk);
   const PS *pp = static_cast<const PS *>(a.pp);
-  // Which probe (2^27 probes that all match, half-full tables, ms with pairs / count only;
-  // one and two: slots a wave loads of every row at first):
-  //   32-byte slots   8 MiB: rows 1.88/1.65 one 1.98/1.44 two 2.18/1.53
-  //                  16 MiB: rows 2.11/1.88 one 2.20/1.90 two 2.28/1.78
-  //                  64 MiB: rows 2.89/2.61 one 3.03/2.80 two 2.72/2.48
-  //                   2 GiB: rows 3.61/3.14 one 3.74/3.16 two 3.76/3.00
-  //                   4 GiB: rows 4.06/3.44 one 4.09/3.60 two 5.93/5.58
-  //   16-byte slots   2 MiB: rows 1.45/1.15 one 1.21/0.91 two 1.33/1.00
-  //                   8 MiB: rows 1.75/1.51 one 1.45/1.15 two 1.62/1.28
-  //                  16 MiB: rows 2.03/1.83 one 2.05/1.80 two 1.95/1.75
-  //                   1 GiB: rows 3.04/2.85 one 3.15/3.03 two 3.00/2.68
-  //   (8-byte keys)   1 GiB: rows 3.22/2.97 one 3.16/3.05 two 3.30/2.72
-  //                   4 GiB: rows 3.67/3.15 one 3.73/3.07 two 4.03/3.14
-  // Tables near an XCD's L2 are bound by the L1's fills, and a second slot of every row
-  // costs more of them than it saves; from larger ones it comes with the first; beyond
-  // 2 GiB two slots are two address translations in flight instead of one. With 32-byte
-  // slots the rows' probe, whose workgroups write out every 1,280 rows' matches
-  // together, is the slower one at random probes from 64 MiB to 2 GiB (above), but ahead
-  // where most probes stay near, and by more (sorted probes of 60,000 and 400,000 rows:
-  // the waves' take 1.03 to 1.09 times as long, probes of one key up to 1.28). Walks among
+  // Which probe (2^27 probes in random order that all match, half-full tables, ms with
+  // pairs / count only; one and two: slots a wave loads of every row at first):
+  //   32-byte slots   8 MiB: rows 2.65/2.47 one 2.16/1.71 two 2.11/1.71
+  //                  16 MiB: rows 2.81/2.61 one 2.67/2.45 two 2.39/2.13
+  //                  64 MiB: rows 3.10/2.90 one 3.61/3.41 two 3.01/2.81
+  //                   2 GiB: rows 4.08/3.76 one 4.03/3.77 two 3.65/3.19
+  //                   4 GiB: rows 4.39/4.10 one 4.70/4.39 two 6.36/6.06
+  //   16-byte slots   2 MiB:                one 1.35/1.03 two 1.35/1.00
+  //                   8 MiB:                one 1.71/1.43 two 1.70/1.35
+  //                  16 MiB:                one 2.34/2.18 two 2.16/1.98
+  //                   1 GiB:                one 3.55/3.47 two 3.26/2.97
+  //   (8-byte keys)   1 GiB:                one 3.58/3.49 two 3.30/3.00
+  //                   4 GiB:                one 3.59/3.46 two 3.55/3.31
+  // Small tables are bound by the L1's fills, and a second slot of every row costs more
+  // of them than it saves: it loses 2 to 8% of 2^22 probes of 1,000 and 2,000 keys, where
+  // the L1 holds some of the table, is even from 2 to 8 MiB (5% behind in a quarter-full
+  // table, 9% ahead where no probe matches) and from larger tables comes with the first.
+  // Beyond 2 GiB two slots are two address translations in flight instead of one; the
+  // line lies where 32-byte slots need it. With 32-byte slots and pairs the rows' probe,
+  // whose workgroups write out every 1,280 rows' matches together, is the slower one in
+  // random order up to 2 GiB (above), but ahead where most probes stay near, where
+  // the waves' falls behind what a thread a row had always taken (sorted probes of
+  // 60,000 and 400,000 rows 1.03 to 1.09 times, of one key up to 1.28). Walks among
   // repeated keys are long, and there the waves' probe is the faster (2^22 probes of
-  // 4,000 keys of 8 rows: 0.95 ms for 2.00; 2^24 of 250,000 of 4: 2.3 for 5.2). The build
+  // 4,000 keys of 8 rows: 0.74 ms for 2.00; 2^24 of 250,000 of 4: 2.6 for 5.2). The build
   // tells which it is: both are launched, one returns at once.
   const uint64_t bytes = nslots * sizeof(Slot<K, PB>);
   const bool near = bytes <= kNearBytes, far = bytes > kFarBytes;
