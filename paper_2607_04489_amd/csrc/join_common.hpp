@@ -83,6 +83,32 @@ __device__ __forceinline__ void flush(EmitLds<NT, SCAP> &L, const EmitOut &o, ui
   __syncthreads();
 }
 
+// block_exclusive_scan with the waves' totals in scalar registers. The emission's callers
+// keep whole sub-tiles of rows in theirs and launch four workgroups of 256 a CU, 128
+// registers a thread: with the totals in vector registers as well k_probe<DirectTab> took
+// 130 to 140 of them, three workgroups, and the fourth ran alone (2^26 sorted probes of 2^23
+// dense int32 keys, pairs: 0.87 ms of probe for 0.51).
+template <int NT>
+__device__ __forceinline__ uint64_t emit_scan(uint64_t v, uint64_t *scratch, uint64_t *total) {
+  constexpr int NW = NT / 64;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 64);
+  const uint64_t inc = wave_inclusive_scan<uint64_t>(v);
+  if (__lane_id() == 63) scratch[wave] = inc;
+  __syncthreads();
+  uint64_t before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const uint64_t lds = scratch[w];
+    const uint64_t t = (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(static_cast<int>(lds >> 32)))) << 32) |
+                       uint32_t(__builtin_amdgcn_readfirstlane(static_cast<int>(lds)));
+    before += w < wave ? t : 0;
+    all += t;
+  }
+  *total = all;
+  __syncthreads();
+  return before + inc - v;
+}
+
 // Finish a workgroup's share: flush the stage and add its checksum part. In
 // count-only mode `fill` is instead the workgroup's whole pair count (uniform).
 template <int NT, int SCAP>
@@ -523,7 +549,7 @@ __device__ __forceinline__ void probe_process(const Tab &tab, const ProbeRegs<IP
     mine += cnt[k];
   }
   uint64_t total;
-  const uint64_t off = block_exclusive_scan<NT, uint64_t>(mine, L.scan, &total);
+  const uint64_t off = emit_scan<NT>(mine, L.scan, &total);
   if (total == 0) return;
   if (!o.ob) {  // count-only: no positions are needed, so nothing is reserved
     fill += total;
@@ -560,7 +586,7 @@ __device__ __forceinline__ void probe_process(const Tab &tab, const ProbeRegs<IP
         uint64_t v = 0;
 #pragma unroll
         for (int k = 0; k < IPT; ++k) v |= static_cast<uint64_t>(cnt[k]) << (16 * k);
-        pk_ok = block_exclusive_scan<NT, uint64_t>(v, L.scan, &pk_tot);
+        pk_ok = emit_scan<NT>(v, L.scan, &pk_tot);
       }
 #pragma unroll
       for (int k = 0; k < IPT; ++k) {
@@ -569,7 +595,7 @@ __device__ __forceinline__ void probe_process(const Tab &tab, const ProbeRegs<IP
           ok = (pk_ok >> (16 * k)) & 0xFFFFu;
           tk = (pk_tot >> (16 * k)) & 0xFFFFu;
         } else {
-          ok = block_exclusive_scan<NT, uint64_t>(cnt[k], L.scan, &tk);
+          ok = emit_scan<NT>(cnt[k], L.scan, &tk);
         }
         if (tk == 0) continue;
         if (tk >= (uint64_t(1) << 32)) {  // offsets do not fit the row table: per row
@@ -621,7 +647,7 @@ __device__ __forceinline__ void probe_process(const Tab &tab, const ProbeRegs<IP
 #pragma unroll
     for (int k = 0; k < IPT; ++k) {
       uint64_t tk;
-      const uint64_t ok = block_exclusive_scan<NT, uint64_t>(cnt[k], L.scan, &tk);
+      const uint64_t ok = emit_scan<NT>(cnt[k], L.scan, &tk);
       if (tk == 0) continue;
       if (tk > SCAP) {
         uint64_t pos = base + done + ok;

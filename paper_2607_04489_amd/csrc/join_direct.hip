@@ -81,7 +81,7 @@ __global__ void k_direct_fill(const K *__restrict__ keys, const PB *__restrict__
 // Each workgroup streams a contiguous range of probe rows (an equal share of
 // whole sub-tiles).
 template <class Tab, typename K, typename PS>
-__global__ void __launch_bounds__(kNT) k_probe(Tab tab, const K *__restrict__ pk,
+__global__ void __launch_bounds__(kNT, 4) k_probe(Tab tab, const K *__restrict__ pk,
                                                const PS *__restrict__ pp, uint64_t n, EmitOut o) {
   __shared__ EmitLds<kNT, kSCAP> L;
   uint64_t fill = 0;

@@ -112,7 +112,7 @@ __device__ __forceinline__ uint32_t bound(const U *__restrict__ code, uint32_t n
 }
 
 template <typename U, typename PB, typename PS>
-__global__ void __launch_bounds__(kMNT) k_smj_merge(SortTab<U, PB> tab, uint32_t nR, const U *__restrict__ sk,
+__global__ void __launch_bounds__(kMNT, 4) k_smj_merge(SortTab<U, PB> tab, uint32_t nR, const U *__restrict__ sk,
                                                     const PS *__restrict__ sp, const uint32_t *__restrict__ srid,
                                                     uint64_t nS, EmitOut o) {
   __shared__ EmitLds<kMNT, kMSCAP> L;
