@@ -83,11 +83,14 @@ __device__ __forceinline__ void flush(EmitLds<NT, SCAP> &L, const EmitOut &o, ui
   __syncthreads();
 }
 
-// block_exclusive_scan with the waves' totals in scalar registers. The emission's callers
-// keep whole sub-tiles of rows in theirs and launch four workgroups of 256 a CU, 128
-// registers a thread: with the totals in vector registers as well k_probe<DirectTab> took
-// 130 to 140 of them, three workgroups, and the fourth ran alone (2^26 sorted probes of 2^23
-// dense int32 keys, pairs: 0.87 ms of probe for 0.51).
+// block_exclusive_scan for the emission, whose callers keep whole sub-tiles of rows in
+// their registers: the waves' totals are not held in vector registers as well. Four
+// waves: in scalar ones (with the totals in vector registers k_probe<DirectTab> took 130
+// to 140 of the 128 that its four workgroups a CU leave, and the fourth ran alone: 2^26
+// sorted probes of 2^23 dense int32 keys, pairs: 0.87 ms of probe for 0.51). Eight: one
+// thread adds them up in LDS, as their scalars spill (k_radix_join, 67M x 268M skewed
+// int32 rows: 5.15 ms; 5.26 in scalar registers, 5.20 in vector ones). `scratch` holds
+// NT / 64 + 1 words.
 template <int NT>
 __device__ __forceinline__ uint64_t emit_scan(uint64_t v, uint64_t *scratch, uint64_t *total) {
   constexpr int NW = NT / 64;
@@ -96,13 +99,27 @@ __device__ __forceinline__ uint64_t emit_scan(uint64_t v, uint64_t *scratch, uin
   if (__lane_id() == 63) scratch[wave] = inc;
   __syncthreads();
   uint64_t before = 0, all = 0;
+  if constexpr (NW <= 4) {
 #pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    const uint64_t lds = scratch[w];
-    const uint64_t t = (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(static_cast<int>(lds >> 32)))) << 32) |
-                       uint32_t(__builtin_amdgcn_readfirstlane(static_cast<int>(lds)));
-    before += w < wave ? t : 0;
-    all += t;
+    for (int w = 0; w < NW; ++w) {
+      const uint64_t lds = scratch[w];
+      const uint64_t t = (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(static_cast<int>(lds >> 32)))) << 32) |
+                         uint32_t(__builtin_amdgcn_readfirstlane(static_cast<int>(lds)));
+      before += w < wave ? t : 0;
+      all += t;
+    }
+  } else {
+    if (threadIdx.x == 0) {
+      for (int w = 0; w < NW; ++w) {
+        const uint64_t t = scratch[w];
+        scratch[w] = all;
+        all += t;
+      }
+      scratch[NW] = all;
+    }
+    __syncthreads();
+    before = scratch[wave];
+    all = scratch[NW];
   }
   *total = all;
   __syncthreads();
