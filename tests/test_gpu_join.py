@@ -79,6 +79,30 @@ def test_hash_sorted_probes_of_wide_payloads_time(gpu):
     assert wide < 1.25 * narrow, (wide, narrow)
 
 
+def test_hash_build_of_repeated_keys_time(gpu):
+    """563,000 build rows: repeated keys take less than two and a half times as long as
+    distinct ones (the walks over their copies; 3.5 while every wave raised the flag)."""
+    g = torch.Generator(device=gpu).manual_seed(1)
+    n = 562_928
+    rep = torch.randint(0, n, (n,), generator=g, device=gpu).int() * 3
+    pk, one = rep[:255], torch.ones(n, dtype=torch.int32, device=gpu)
+
+    def build(keys):
+        plan = eg.join_plan(eg.stats(keys), eg.stats(pk), eg.SEL_FORCED, eg.make_plan(eg.GLOBAL_HASH, 0, 0, 0.5))
+        best = []
+        for _ in range(11):
+            eg.profile_enable(True)
+            try:
+                eg.join(keys, one, pk, one[:255], plan, count_only=True)
+                torch.cuda.synchronize()
+                best.append(eg.profile_read()["hash_build"][1])
+            finally:
+                eg.profile_enable(False)
+        return min(best)
+
+    assert build(rep) < 2.5 * build(torch.arange(n, device=gpu).int() * 3)
+
+
 # Build rows of which one more doubles the table at load factor 0.5. 16-byte slots: 2 to
 # 16 MiB, from 16 on the probe loads two slots of a row at first; 32-byte slots: 4 to 32
 # MiB, pairs of distinct keys by the rows' own probe, the others from 16 on two slots.
