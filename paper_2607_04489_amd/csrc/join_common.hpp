@@ -318,14 +318,16 @@ struct WaveProbe {
   template <int NW>
   __device__ __forceinline__ void run(const K *__restrict__ pk, const PS *__restrict__ pp,
                                       const uint32_t *__restrict__ prow, uint64_t lo, uint64_t hi, uint64_t stride,
-                                      WaveJoint<NW> &J) {
+                                      WaveJoint<NW> &J, uint32_t block = 64 * kWaveRows) {
     K key[kWaveRows], nkey[kWaveRows];
     PS pay[kWaveRows], npay[kWaveRows];
     uint32_t row[kWaveRows], nrow[kWaveRows], step[kWaveRows];
+    auto end_of = [&](uint64_t t) { return block < 64 * kWaveRows && t + block < hi ? t + block : hi; };
     auto load = [&](uint64_t t) {
+      const uint64_t e = end_of(t);
 #pragma unroll
       for (int r = 0; r < kWaveRows; ++r) {
-        const uint64_t j = t + r * 64 + __lane_id(), i = j < hi ? j : hi - 1;
+        const uint64_t j = t + r * 64 + __lane_id(), i = j < e ? j : e - 1;
         nkey[r] = pk[i];
         npay[r] = pp[i];
         nrow[r] = prow ? prow[i] : static_cast<uint32_t>(i);
@@ -343,6 +345,7 @@ struct WaveProbe {
           bool live[kWaveRows];
           typename Tab::Index home[kWaveRows];
           typename Tab::SlotT s0[kWaveRows], s1[kWaveRows];
+          const uint64_t e = end_of(t);
 #pragma unroll
           for (int r = 0; r < kWaveRows; ++r) {
             key[r] = nkey[r];
@@ -351,7 +354,7 @@ struct WaveProbe {
             step[r] = kEager;
             bool in;
             home[r] = tab.start(key[r], in);
-            live[r] = in && t + r * 64 + __lane_id() < hi;
+            live[r] = in && t + r * 64 + __lane_id() < e;
             s0[r] = tab.load(home[r]);
             if constexpr (Tab::kWalk && kEager > 1) s1[r] = tab.load(tab.walk(home[r], 1));
           }

@@ -209,7 +209,7 @@ bool hash_sentinel(const JoinArgs &a, K *out) {
 template <class Tab, typename K, typename PS, int kEager, bool kPairs>
 __global__ void __launch_bounds__((kPNT<K, PS, kPairs>)) k_probe(Tab tab, const K *__restrict__ pk,
                                                const PS *__restrict__ pp, uint64_t n, EmitOut o,
-                                               bool repeated_only) {
+                                               bool repeated_only, uint32_t block) {
   constexpr int kNT = kPNT<K, PS, kPairs>;
   constexpr uint32_t kStage = kPStage<K, PS, kPairs>;
   __shared__ WaveLds<K, PS, kStage> L[kNT / 64];
@@ -217,14 +217,14 @@ __global__ void __launch_bounds__((kPNT<K, PS, kPairs>)) k_probe(Tab tab, const 
   static_assert((sizeof(L) + sizeof(J)) * kPPerCu<K, PS, kPairs> <= 163840, "the workgroups of a CU share its LDS");
   tab.init();
   if (repeated_only && tab.unique) return;
-  constexpr uint64_t block = 64 * kWaveRows, sub = kNT * kWaveRows;
+  const uint64_t sub = kNT / 64 * block;
   const uint32_t w = threadIdx.x / 64;
   const uint64_t nsub = (n + sub - 1) / sub;
   const uint64_t per = (nsub + gridDim.x - 1) / gridDim.x;
   const uint64_t lo = blockIdx.x * per * sub;
   const uint64_t hi = lo + per * sub < n ? lo + per * sub : n;
   WaveProbe<Tab, K, PS, kEager, kStage> p(tab, L[w], o);
-  p.template run<kNT / 64>(pk, pp, nullptr, lo + w * block, hi, sub, J);
+  p.template run<kNT / 64>(pk, pp, nullptr, lo + w * block, hi, sub, J, block);
 }
 
 constexpr int kRowNT = 256;
@@ -257,12 +257,24 @@ unsigned grid_for(uint64_t work, uint64_t per_block, int per_cu) {
   return static_cast<unsigned>(g ? g : 1);
 }
 
+// Rows that a wave of the probe takes together: 64 * kWaveRows, fewer where the probe side
+// leaves waves without any (256 probes of 64 matches each: 49 us of probe, 131 when one
+// wave took them all).
+template <typename K, typename PS, bool kPairs>
+uint32_t probe_block(uint64_t n) {
+  const uint64_t waves = uint64_t(device_cu_count()) * kPPerCu<K, PS, kPairs> * (kPNT<K, PS, kPairs> / 64);
+  uint32_t block = 64;
+  while (block < 64 * kWaveRows && n > waves * block) block *= 2;
+  return block;
+}
+
 template <typename K, typename PB, typename PS, int kEager, bool kPairs>
 int launch_probe(const HashTab<K, PB> &tab, const K *pk, const PS *pp, uint64_t n, const EmitOut &o, bool repeated_only,
                  hipStream_t s) {
-  const dim3 grid(grid_for(n, uint64_t(kPNT<K, PS, kPairs>) * kWaveRows, kPPerCu<K, PS, kPairs>));
+  const uint32_t block = probe_block<K, PS, kPairs>(n);
+  const dim3 grid(grid_for(n, kPNT<K, PS, kPairs> / 64 * uint64_t(block), kPPerCu<K, PS, kPairs>));
   EIGER_LAUNCH("hash_probe", (k_probe<HashTab<K, PB>, K, PS, kEager, kPairs>), grid, dim3(kPNT<K, PS, kPairs>), 0, s, tab, pk, pp, n, o,
-               repeated_only);
+               repeated_only, block);
   return EIGER_OK;
 }
 
@@ -330,12 +342,15 @@ int hash_impl(const JoinArgs &a, Workspace &ws, JoinCounters **ctr) {
   // 60,000 and 400,000 rows 1.03 to 1.09 times, of one key up to 1.28). Walks among
   // repeated keys are long, and there the waves' probe is the faster (2^22 probes of
   // 4,000 keys of 8 rows: 0.74 ms for 2.00; 2^24 of 250,000 of 4: 2.6 for 5.2). The build
-  // tells which it is: both are launched, one returns at once.
+  // tells which it is: both are launched, one returns at once. Small probe sides are left
+  // to the waves' alone: with a row a lane the matches of distinct keys fit a wave's stage,
+  // and of two kernels the second comes late (90 x 136 rows of repeated keys: 72 us of
+  // join, 95 with both).
   const uint64_t bytes = nslots * sizeof(Slot<K, PB>);
   const bool near = bytes <= kNearBytes, far = bytes > kFarBytes;
   bool by_rows = false;
   if constexpr (sizeof(Slot<K, PB>) == 32) {
-    by_rows = a.ob || far;
+    by_rows = (a.ob && probe_block<K, PS, true>(a.nS) > 64) || far;
     if (by_rows) {
       HashRowTab<K, PB> rows;
       static_cast<HashTab<K, PB> &>(rows) = tab;

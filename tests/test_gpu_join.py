@@ -103,6 +103,49 @@ def test_hash_build_of_repeated_keys_time(gpu):
     assert build(rep) < 2.5 * build(torch.arange(n, device=gpu).int() * 3)
 
 
+@pytest.mark.parametrize("key,pay", [(torch.int32, torch.int32), (torch.int32, torch.int64), (torch.int64, torch.int64)])
+@pytest.mark.parametrize("repeats", [1, 40])
+def test_hash_probe_of_small_sides(gpu, repeats, key, pay):
+    """Probe sides around a wave's rows, a workgroup's and the sizes at which a wave takes
+    twice as many, whole and half matching, of distinct and of repeated keys."""
+    g = torch.Generator().manual_seed(2)
+    keys = (torch.arange(120) * 7919 - 5000).repeat(repeats)
+    waves = 2 * 256 * (8 if key == pay == torch.int32 else 7)
+    for n_probe in (1, 63, 65, 448, 513, 64 * waves, 64 * waves + 1, 128 * waves + 1):
+        if repeats > 1 and n_probe > 1000:
+            continue
+        inp = synth.JoinInput("small", keys.to(key).to(gpu), torch.randint(-999, 999, keys.shape, generator=g).to(pay).to(gpu),
+                              (torch.randint(0, 240, (n_probe,), generator=g) * 7919 - 5000).to(key).to(gpu),
+                              torch.randint(-999, 999, (n_probe,), generator=g).to(pay).to(gpu))
+        res = run(inp, ("hash", eg.GLOBAL_HASH, 0, 0, 0.5))
+        assert_exact(inp, res)
+        cnt = run(inp, ("hash", eg.GLOBAL_HASH, 0, 0, 0.5), count_only=True)
+        assert (cnt.count, cnt.checksum) == (res.count, res.checksum)
+
+
+def test_hash_probe_of_few_rows_time(gpu):
+    """256 probe rows of 64 matches each, pairs: less than half as long again as 64 of them,
+    since other waves take the rest (2.5 times as long while one wave took them all)."""
+    bk = torch.full((64,), 7, device=gpu)
+    pk, one = bk.repeat(4), torch.ones(256, dtype=torch.int64, device=gpu)
+    plan = eg.join_plan(eg.stats(bk), eg.stats(pk), eg.SEL_FORCED, eg.make_plan(eg.GLOBAL_HASH, 0, 0, 0.5))
+    outs = [torch.empty(64 * 256, dtype=torch.int32, device=gpu) for _ in range(2)]
+
+    def probe(n):
+        best = []
+        for _ in range(11):
+            eg.profile_enable(True)
+            try:
+                assert eg.join(bk, one[:64], pk[:n], one[:n], plan, outputs=outs).count == 64 * n
+                torch.cuda.synchronize()
+                best.append(eg.profile_read()["hash_probe"][1])
+            finally:
+                eg.profile_enable(False)
+        return min(best)
+
+    assert probe(256) < 1.5 * probe(64)
+
+
 # Build rows of which one more doubles the table at load factor 0.5. 16-byte slots: 2 to
 # 16 MiB, from 16 on the probe loads two slots of a row at first; 32-byte slots: 4 to 32
 # MiB, pairs of distinct keys by the rows' own probe, the others from 16 on two slots.
