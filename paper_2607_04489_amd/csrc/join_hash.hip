@@ -55,15 +55,6 @@ struct HashTab {
   }
   __device__ __forceinline__ uint64_t walk(uint64_t i, uint32_t steps) const { return line_walk<SlotT>(i, steps, mask); }
   __device__ __forceinline__ SlotT load(uint64_t i) const { return slots[i]; }
-  template <class F>
-  __device__ __forceinline__ void for_each(K key, F f) const {
-    const uint64_t i = home(key);
-    for (uint32_t step = 0;; ++step) {
-      const Slot<K, PB> s = slots[walk(i, step)];
-      if (s.rowid == kEmpty) break;
-      if (s.key == key) f(s.rowid);
-    }
-  }
 };
 
 // The same table of 32-byte slots for a probe that holds each row's walk in its lane:
@@ -89,19 +80,34 @@ struct HashRowTab : HashTab<K, PB> {
   }
 };
 
-// Sets *dup when some build key occurs more than once: every build row walks
-// its key's cluster and counts equal keys. Afterwards probes of a table with
-// distinct keys stop at their first match.
+// Sets *dup when some build key occurs more than once: every build row walks its key's
+// cluster, 64 bytes a step, until it meets the key again or the flag is found set.
+// Afterwards probes of a table with distinct keys stop at their first match. (No key
+// lies past an empty slot of its walk, so that all slots of a line can be counted.)
 template <typename K, typename PB>
 __global__ void k_hash_unique(const K *__restrict__ keys, uint64_t n, HashTab<K, PB> tab,
                               uint32_t *dup) {
+  constexpr uint64_t per = 64 / sizeof(Slot<K, PB>);
   const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
   for (uint64_t r = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; r < n; r += stride) {
-    if (*static_cast<volatile uint32_t *>(dup)) return;
     const K key = keys[r];
+    uint64_t at = tab.home(key) & ~(per - 1);
     uint32_t c = 0;
-    tab.for_each(key, [&](uint32_t) { ++c; });
-    if (c > 1) atomicOr(dup, 1u);
+    for (uint32_t line = 0;; ++line) {
+      if (line % 16 == 0 && *static_cast<volatile uint32_t *>(dup)) return;
+      Slot<K, PB> s[per];
+#pragma unroll
+      for (uint32_t q = 0; q < per; ++q) s[q] = tab.slots[at + q];
+      bool last = false;
+#pragma unroll
+      for (uint32_t q = 0; q < per; ++q) {
+        last |= s[q].rowid == kEmpty;
+        c += s[q].rowid != kEmpty && s[q].key == key;
+      }
+      if (c > 1) atomicOr(dup, 1u);
+      if (last || c > 1) break;
+      at = (at + per) & tab.mask;
+    }
   }
 }
 

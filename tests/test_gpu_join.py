@@ -146,6 +146,48 @@ def test_hash_probe_of_few_rows_time(gpu):
     assert probe(256) < 1.5 * probe(64)
 
 
+@pytest.mark.parametrize("key,pay", [(torch.int32, torch.int32), (torch.int64, torch.int32), (torch.int64, torch.int64)])
+@pytest.mark.parametrize("lf", [0.25, 0.9])
+def test_hash_duplicate_check_finds_one_pair(gpu, lf, key, pay):
+    """Keys at both ends of the domain, so that the build does not see duplicates itself:
+    one key twice among distinct ones, first and last row or next to each other."""
+    info = torch.iinfo(key)
+    for n in (3, 30, 1021, 7373, 29491):
+        keys = torch.arange(n) * 40009 - 3
+        keys[0], keys[1] = info.min, info.max
+        for a, b in ((0, n - 1), (n // 2, n // 2 + 1), (2, 2)):
+            bk = keys.clone()
+            bk[b] = bk[a]
+            inp = synth.JoinInput("pair", bk.to(key).to(gpu), torch.arange(n).to(pay).to(gpu),
+                                  bk[torch.arange(0, n, 7)].repeat(2).to(key).to(gpu), torch.arange(len(range(0, n, 7)) * 2).to(pay).to(gpu))
+            assert_exact(inp, run(inp, ("hash", eg.GLOBAL_HASH, 0, 0, lf)))
+
+
+def test_hash_duplicate_check_time(gpu):
+    """30,000 rows, a tenth of them each of three keys at and between the ends of the
+    domain: looking for duplicates takes a tenth of the build at most (0.22 of it while
+    every row walked to its cluster's end)."""
+    g = torch.Generator(device=gpu).manual_seed(1)
+    info, n = torch.iinfo(torch.int64), 30_000
+    m = torch.rand(n, generator=g, device=gpu)
+    bk = torch.randint(0, n, (n,), generator=g, device=gpu)
+    for k, at in enumerate((info.min, info.max, -1)):
+        bk = torch.where((m >= k / 10) & (m < (k + 1) / 10), torch.full_like(bk, at), bk)
+    plan = eg.join_plan(eg.stats(bk), eg.stats(bk[:9]), eg.SEL_FORCED, eg.make_plan(eg.GLOBAL_HASH, 0, 0, 0.5))
+    t = []
+    for _ in range(5):
+        eg.profile_enable(True)
+        try:
+            eg.join(bk, bk.int(), bk[:9], bk[:9].int(), plan, count_only=True)
+            torch.cuda.synchronize()
+            prof = eg.profile_read()
+            t.append((prof["hash_unique"][1], prof["hash_build"][1]))
+        finally:
+            eg.profile_enable(False)
+    unique, build = (min(x) for x in zip(*t))
+    assert unique < 0.1 * build, (unique, build)
+
+
 # Build rows of which one more doubles the table at load factor 0.5. 16-byte slots: 2 to
 # 16 MiB, from 16 on the probe loads two slots of a row at first; 32-byte slots: 4 to 32
 # MiB, pairs of distinct keys by the rows' own probe, the others from 16 on two slots.
